@@ -2286,6 +2286,29 @@ __device__ inline uint32_t prefix_match_one(const Table &t, uint32_t d, const ui
     return j;
 }
 
+// The same by kMatchLanes neighbouring lanes, a block each per step: a lookup
+// is a chain of three dependent loads (buckets, holder value, bitmap word),
+// and one thread walking a run of a hundred resident blocks keeps its
+// workgroup waiting for 100 us.  Every lane of the wavefront must call it;
+// n = 0 for those without a request.  All lanes of a group get the result.
+constexpr uint32_t kMatchLanes = 16;
+__device__ inline uint32_t prefix_match_lanes(const Table &t, uint32_t d, const uint64_t *__restrict__ run,
+                                              uint32_t n) {
+    const uint32_t sub = threadIdx.x % kMatchLanes, seg0 = (threadIdx.x % kWave) - sub;
+    uint32_t j = n;
+    bool act = n > 0;
+    for (uint32_t k0 = 0; __any(act); k0 += kMatchLanes) {
+        const uint32_t k = k0 + sub;
+        const bool miss = act && (k >= n || !holds(t, run[k], d));
+        const uint32_t m = (uint32_t)(__ballot(miss) >> seg0) & ((1u << kMatchLanes) - 1u);
+        if (act && m) {
+            j = k0 + (uint32_t)__builtin_ctz(m);
+            act = false;
+        }
+    }
+    return j;
+}
+
 __global__ void commit_count_kernel(Snap s, Table t, Reqs rq, const int32_t *__restrict__ sel,
                                     uint32_t *__restrict__ cnt, uint32_t *__restrict__ adm,
                                     unsigned long long *__restrict__ bytes, uint32_t *__restrict__ err) {
@@ -2311,21 +2334,109 @@ __global__ void commit_count_kernel(Snap s, Table t, Reqs rq, const int32_t *__r
     atomicAdd(bytes + d, (unsigned long long)s_eff);
 }
 
+// Between-batch update of one counter entry i (of 4 P in-flight counters,
+// then D decodes) from the batch's sums.
+__device__ inline void commit_entry(uint32_t i, uint32_t P, uint32_t cap, uint32_t mu, uint32_t c,
+                                    unsigned long long b, uint16_t *__restrict__ n_inflight,
+                                    uint32_t *__restrict__ queue, uint64_t *__restrict__ free_mem,
+                                    uint64_t *__restrict__ adm_prev) {
+    if (i < 4 * P) {
+        n_inflight[i] = (uint16_t)(c < cap ? c : cap);
+        return;
+    }
+    const uint32_t d = i - 4 * P;
+    const int64_t nq = (int64_t)queue[d] + (int64_t)c - (int64_t)mu;
+    queue[d] = (uint32_t)(nq < 0 ? 0 : nq);
+    uint64_t m = free_mem[d];
+    m = m > b ? m - b : 0;
+    free_mem[d] = m + adm_prev[d];
+    adm_prev[d] = b;
+}
+
 __global__ void commit_apply_kernel(uint32_t P, uint32_t D, uint32_t cap, uint32_t mu,
                                     const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ adm,
                                     const unsigned long long *__restrict__ bytes,
                                     uint16_t *__restrict__ n_inflight, uint32_t *__restrict__ queue,
                                     uint64_t *__restrict__ free_mem, uint64_t *__restrict__ adm_prev) {
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < 4 * P) n_inflight[i] = (uint16_t)(cnt[i] < cap ? cnt[i] : cap);
-    if (i < D) {
-        int64_t nq = (int64_t)queue[i] + (int64_t)adm[i] - (int64_t)mu;
-        queue[i] = (uint32_t)(nq < 0 ? 0 : nq);
-        uint64_t m = free_mem[i], b = bytes[i];
-        m = m > b ? m - b : 0;
-        free_mem[i] = m + adm_prev[i];
-        adm_prev[i] = b;
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 4 * P + D) return;
+    const uint32_t d = i - 4 * P;
+    commit_entry(i, P, cap, mu, i < 4 * P ? cnt[i] : adm[d], i < 4 * P ? 0ull : bytes[d], n_inflight, queue, free_mem,
+                 adm_prev);
+}
+
+// The same sums without device-wide atomics: a batch puts R / (4 P) and
+// R / D requests on each counter, and same-address atomics of all
+// workgroups are served one after another (245 us for 65,536 requests on
+// 16 x 48 instances, 0.18 us per atomic of one address).  Each workgroup
+// sums its requests in LDS (cnt[4 P], adm[D], bytes[D]) and writes its sums
+// to its own row; commit_sum_kernel adds the rows.
+constexpr uint32_t kCommitThreads = 1024;
+constexpr uint32_t kCommitRows = 256;             // most workgroups (rows)
+constexpr uint64_t kCommitLds = 64ull << 10;      // LDS of one workgroup's sums
+
+__global__ __launch_bounds__(kCommitThreads) void commit_rows_kernel(Snap s, Table t, Reqs rq,
+                                                                     const int32_t *__restrict__ sel,
+                                                                     uint32_t *__restrict__ rows,
+                                                                     unsigned long long *__restrict__ brows,
+                                                                     uint32_t *__restrict__ err) {
+    extern __shared__ unsigned long long csum[];   // bytes[D], then counts [4 P + D]
+    uint32_t *cnt = (uint32_t *)(csum + s.D);
+    const uint32_t n = 4 * s.P + s.D;
+    for (uint32_t i = threadIdx.x; i < s.D; i += kCommitThreads) csum[i] = 0;
+    for (uint32_t i = threadIdx.x; i < n; i += kCommitThreads) cnt[i] = 0;
+    __syncthreads();
+    uint32_t bad = 0;
+    constexpr uint32_t kPer = kCommitThreads / kMatchLanes;   // requests per workgroup and step
+    const bool head = threadIdx.x % kMatchLanes == 0;
+    for (uint64_t r0 = (uint64_t)blockIdx.x * kPer; r0 < rq.n_req; r0 += (uint64_t)gridDim.x * kPer) {
+        const uint64_t r = r0 + threadIdx.x / kMatchLanes;
+        int32_t d = r < rq.n_req ? sel[r] : -1;
+        uint32_t p = 0, len = 0, nb = 0;
+        uint64_t a = 0;
+        if (d >= 0 && (uint32_t)d >= s.D) {
+            bad |= kErrSelection;
+            d = -1;
+        }
+        if (d >= 0 && !request_ok(rq, s, (uint32_t)r, p, len, a, nb)) {
+            bad |= kErrRequest;
+            d = -1;
+        }
+        const uint32_t j = prefix_match_lanes(t, (uint32_t)d, rq.hashes + a, d < 0 ? 0u : nb);
+        if (d >= 0 && head) {
+            const uint32_t tau = s.tier_map[(uint64_t)p * s.D + (uint32_t)d] & 3u;
+            atomicAdd(cnt + tau * s.P + p, 1u);
+            atomicAdd(cnt + 4 * s.P + (uint32_t)d, 1u);
+            atomicAdd(csum + d, (unsigned long long)((uint64_t)s.bpt * (uint64_t)(len - s.block_tokens * j)));
+        }
     }
+    if (bad) atomicOr(err, bad);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += kCommitThreads) rows[(uint64_t)blockIdx.x * n + i] = cnt[i];
+    for (uint32_t i = threadIdx.x; i < s.D; i += kCommitThreads) brows[(uint64_t)blockIdx.x * s.D + i] = csum[i];
+}
+
+// One wavefront per counter entry: the sum over the rows, then the update.
+__global__ __launch_bounds__(256) void commit_sum_kernel(uint32_t P, uint32_t D, uint32_t cap, uint32_t mu,
+                                                         uint32_t nrow, const uint32_t *__restrict__ rows,
+                                                         const unsigned long long *__restrict__ brows,
+                                                         uint16_t *__restrict__ n_inflight,
+                                                         uint32_t *__restrict__ queue,
+                                                         uint64_t *__restrict__ free_mem,
+                                                         uint64_t *__restrict__ adm_prev) {
+    const uint32_t n = 4 * P + D;
+    const uint32_t i = blockIdx.x * kWavesPerBlock + wave_index(), lane = threadIdx.x % kWave;
+    if (i >= n) return;
+    uint32_t c = 0;
+    unsigned long long b = 0;
+    for (uint32_t w = lane; w < nrow; w += kWave) {
+        c += rows[(uint64_t)w * n + i];
+        if (i >= 4 * P) b += brows[(uint64_t)w * D + (i - 4 * P)];
+    }
+    c = wave_sum_u32(c);
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) b += __shfl_xor(b, m, kWave);
+    if (lane == 0) commit_entry(i, P, cap, mu, c, b, n_inflight, queue, free_mem, adm_prev);
 }
 
 // ---------------------------------------------------------------- tier counts
@@ -4443,6 +4554,34 @@ netkv_status netkv_commit_batch(netkv_handle h, const netkv_requests_t *req, con
     if ((st = ready(h))) return st;
     DeviceGuard g(h->device);
     hipStream_t s = (hipStream_t)stream;
+    const uint64_t entries = 4ull * h->P + h->D;
+    const uint64_t lds = 8ull * h->D + 4ull * entries;
+    if (lds <= kCommitLds) {
+        // sums in LDS: one row per workgroup, at most kCommitRows of them
+        // (pools of up to 1,024 x 3,072 instances take 52 KiB)
+        if (h->commit_P != h->P || h->commit_D != h->D) {
+            dfree(h->cnt);
+            dfree(h->bytes);
+            h->commit_P = h->commit_D = 0;
+            HIPCHK(h, dalloc(h->cnt, kCommitRows * entries));
+            HIPCHK(h, dalloc(h->bytes, (uint64_t)kCommitRows * h->D));
+            h->commit_P = h->P;
+            h->commit_D = h->D;
+        }
+        const uint32_t nrow =
+            (uint32_t)std::min<uint64_t>(((uint64_t)req->n_req * kMatchLanes + kCommitThreads - 1) / kCommitThreads,
+                                         kCommitRows);
+        if (nrow) {
+            hipLaunchKernelGGL(commit_rows_kernel, dim3(nrow), dim3(kCommitThreads), (size_t)lds, s, make_snap(h),
+                               make_table(h), make_reqs(req), sel, h->cnt, h->bytes, h->errword);
+            HIPCHK(h, hipGetLastError());
+        }
+        hipLaunchKernelGGL(commit_sum_kernel, dim3((uint32_t)((entries + kWavesPerBlock - 1) / kWavesPerBlock)),
+                           dim3(kBlock), 0, s, h->P, h->D, cap, mu, nrow, (const uint32_t *)h->cnt,
+                           (const unsigned long long *)h->bytes, h->n_inflight, h->queue, h->free_mem, h->adm_prev);
+        HIPCHK(h, hipGetLastError());
+        return NETKV_OK;
+    }
     if (h->commit_P != h->P || h->commit_D != h->D) {
         dfree(h->cnt);
         dfree(h->adm);
@@ -4464,7 +4603,7 @@ netkv_status netkv_commit_batch(netkv_handle h, const netkv_requests_t *req, con
                            make_table(h), make_reqs(req), sel, h->cnt, h->adm, h->bytes, h->errword);
         HIPCHK(h, hipGetLastError());
     }
-    uint32_t n = std::max(4u * h->P, h->D);
+    const uint32_t n = 4u * h->P + h->D;
     hipLaunchKernelGGL(commit_apply_kernel, dim3((n + 255) / 256), dim3(256), 0, s, h->P, h->D, cap, mu,
                        (const uint32_t *)h->cnt, (const uint32_t *)h->adm, (const unsigned long long *)h->bytes,
                        h->n_inflight, h->queue, h->free_mem, h->adm_prev);
