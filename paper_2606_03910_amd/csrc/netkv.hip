@@ -2259,6 +2259,49 @@ __global__ __launch_bounds__(256) void smooth_kernel(float *__restrict__ util, c
     if (__ballot(bad) && (threadIdx.x % kWave) == 0) atomicOr(err, kErrObservation);
 }
 
+// A snapshot whose arrays all lie in this device's memory is copied and
+// checked in one pass (six copies, a clear and the check as launches of
+// their own took about 45 us).
+struct SnapIn {
+    const uint8_t *tier;
+    const float *util;
+    const uint16_t *n_inflight;
+    const uint64_t *free_mem;
+    const uint32_t *queue, *batch;
+};
+
+__global__ __launch_bounds__(256) void load_snapshot_kernel(SnapIn in, uint64_t npd, uint32_t P, uint32_t D,
+                                                            uint32_t beta_max, uint8_t *__restrict__ tier,
+                                                            float *__restrict__ util,
+                                                            uint16_t *__restrict__ n_inflight,
+                                                            uint64_t *__restrict__ free_mem,
+                                                            uint64_t *__restrict__ adm_prev,
+                                                            uint32_t *__restrict__ queue,
+                                                            uint32_t *__restrict__ batch,
+                                                            uint32_t *__restrict__ bad) {
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    uint32_t f = 0;
+    for (uint64_t x = i; x < npd; x += stride) {
+        const uint8_t t = in.tier[x];
+        const float u = in.util[x];
+        if (t > 3) f |= 1u;
+        if (!(u >= 0.0f && u < 1.0f)) f |= 2u;
+        tier[x] = t;
+        util[x] = u;
+    }
+    for (uint64_t x = i; x < 4ull * P; x += stride) n_inflight[x] = in.n_inflight[x];
+    for (uint64_t x = i; x < D; x += stride) {
+        const uint32_t b = in.batch[x];
+        if (b > beta_max) f |= 4u;
+        batch[x] = b;
+        queue[x] = in.queue[x];
+        free_mem[x] = in.free_mem[x];
+        adm_prev[x] = 0;
+    }
+    if (f) atomicOr(bad, f);
+}
+
 __global__ void check_snapshot_kernel(const uint8_t *__restrict__ tier, const float *__restrict__ util,
                                       uint64_t npd, const uint32_t *__restrict__ batch, uint32_t D,
                                       uint32_t beta_max, uint32_t *__restrict__ bad) {
@@ -2943,6 +2986,17 @@ struct netkv_ctx {
     uint32_t *queue = nullptr;
     uint32_t *batch = nullptr;
     uint64_t *adm_prev = nullptr;
+    // the snapshot buffers of the load before, of the same shape: the next
+    // load is staged and checked there, then the two are exchanged (a load
+    // that allocated and freed its seven buffers spent about 150 us on it)
+    struct SnapBuf {
+        uint32_t P = 0, D = 0;   // shape; 0: no buffers
+        uint8_t *tier_map = nullptr;
+        float *util = nullptr;
+        uint16_t *n_inflight = nullptr;
+        uint64_t *free_mem = nullptr, *adm_prev = nullptr;
+        uint32_t *queue = nullptr, *batch = nullptr;
+    } spare;
     float2 *sl = nullptr;        // derived per call: [P*D]
     float *dbase = nullptr;      // [D]
     uint64_t *dxlim = nullptr;   // [D]
@@ -3746,6 +3800,23 @@ netkv_status carve_static(netkv_handle h, uint8_t *base, uint64_t R, uint32_t k,
     return NETKV_OK;
 }
 
+void free_spare(netkv_ctx::SnapBuf &b) {
+    dfree(b.tier_map); dfree(b.util); dfree(b.n_inflight); dfree(b.free_mem);
+    dfree(b.adm_prev); dfree(b.queue); dfree(b.batch);
+    b.P = b.D = 0;
+}
+
+// Whether p is memory of the handle's device (host memory, pinned or not,
+// managed memory and other devices' are copied by the runtime).
+bool on_device(netkv_handle h, const void *p) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();   // not an error of this call: ordinary host memory
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == h->device && !at.isManaged;
+}
+
 bool finite_nonneg(double x) { return std::isfinite(x) && x >= 0.0; }
 
 }  // namespace
@@ -3887,6 +3958,7 @@ void netkv_destroy(netkv_handle h) {
         dfree(h->queue);
         dfree(h->batch);
         dfree(h->adm_prev);
+        free_spare(h->spare);
         dfree(h->sl);
         dfree(h->dbase);
         dfree(h->dxlim);
@@ -3936,47 +4008,56 @@ netkv_status netkv_oracle_load(netkv_handle h, const netkv_oracle_t *o, void *st
     DeviceGuard g(h->device);
     hipStream_t st = (hipStream_t)stream;
     const uint64_t npd = (uint64_t)P * D;
-    // stage into fresh buffers, validate, then swap in
-    uint8_t *tm = nullptr;
-    float *ut = nullptr;
-    uint16_t *ni = nullptr;
-    uint64_t *fm = nullptr, *ap = nullptr;
-    uint32_t *qd = nullptr, *bs = nullptr;
-    auto cleanup = [&]() {
-        dfree(tm); dfree(ut); dfree(ni); dfree(fm); dfree(ap); dfree(qd); dfree(bs);
-    };
-    if (dalloc(tm, npd) != hipSuccess || dalloc(ut, npd) != hipSuccess || dalloc(ni, 4ull * P) != hipSuccess ||
-        dalloc(fm, D) != hipSuccess || dalloc(ap, D) != hipSuccess || dalloc(qd, D) != hipSuccess ||
-        dalloc(bs, D) != hipSuccess) {
-        cleanup();
-        return fail(h, NETKV_ENOMEM, "snapshot allocation failed");
+    // stage into the spare buffers, validate, then exchange.  The wait is
+    // for the whole device: selections on other streams may still read the
+    // buffers exchanged out here, which the next load overwrites.
+    netkv_ctx::SnapBuf &sp = h->spare;
+    if (sp.P != P || sp.D != D) {
+        free_spare(sp);
+        if (dalloc(sp.tier_map, npd) != hipSuccess || dalloc(sp.util, npd) != hipSuccess ||
+            dalloc(sp.n_inflight, 4ull * P) != hipSuccess || dalloc(sp.free_mem, D) != hipSuccess ||
+            dalloc(sp.adm_prev, D) != hipSuccess || dalloc(sp.queue, D) != hipSuccess ||
+            dalloc(sp.batch, D) != hipSuccess) {
+            free_spare(sp);
+            return fail(h, NETKV_ENOMEM, "snapshot allocation failed");
+        }
+        sp.P = P;
+        sp.D = D;
     }
     hipError_t e = hipSuccess;
-    if (e == hipSuccess) e = hipMemcpyAsync(tm, o->tier_map, npd, hipMemcpyDefault, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(ut, o->util, npd * 4, hipMemcpyDefault, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(ni, o->n_inflight, 8ull * P, hipMemcpyDefault, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(fm, o->free_mem, 8ull * D, hipMemcpyDefault, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(qd, o->queue_depth, 4ull * D, hipMemcpyDefault, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(bs, o->batch_size, 4ull * D, hipMemcpyDefault, st);
-    if (e == hipSuccess) e = hipMemsetAsync(ap, 0, 8ull * D, st);
-    if (e == hipSuccess) e = hipMemsetAsync(h->loadword, 0, 4, st);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(check_snapshot_kernel, dim3(grid_for(std::max<uint64_t>(npd, D), 256, 4096)), dim3(256),
-                           0, st, tm, ut, npd, bs, D, o->beta_max, h->loadword);
-        e = hipGetLastError();
-    }
     uint32_t bad = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&bad, h->loadword, 4, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) {
-        cleanup();
-        return fail(h, NETKV_EDEVICE, "snapshot upload failed: %s", hipGetErrorString(e));
+    if (on_device(h, o->tier_map) && on_device(h, o->util) && on_device(h, o->n_inflight) &&
+        on_device(h, o->free_mem) && on_device(h, o->queue_depth) && on_device(h, o->batch_size)) {
+        const SnapIn in{o->tier_map, o->util, o->n_inflight, o->free_mem, o->queue_depth, o->batch_size};
+        e = hipMemsetAsync(h->loadword, 0, 4, st);
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(load_snapshot_kernel,
+                               dim3(grid_for(std::max<uint64_t>(npd, std::max(4u * P, D)), 256, 4096)), dim3(256), 0, st,
+                               in, npd, P, D, o->beta_max, sp.tier_map, sp.util, sp.n_inflight, sp.free_mem,
+                               sp.adm_prev, sp.queue, sp.batch, h->loadword);
+            e = hipGetLastError();
+        }
+    } else {
+        e = hipMemcpyAsync(sp.tier_map, o->tier_map, npd, hipMemcpyDefault, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(sp.util, o->util, npd * 4, hipMemcpyDefault, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(sp.n_inflight, o->n_inflight, 8ull * P, hipMemcpyDefault, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(sp.free_mem, o->free_mem, 8ull * D, hipMemcpyDefault, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(sp.queue, o->queue_depth, 4ull * D, hipMemcpyDefault, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(sp.batch, o->batch_size, 4ull * D, hipMemcpyDefault, st);
+        if (e == hipSuccess) e = hipMemsetAsync(sp.adm_prev, 0, 8ull * D, st);
+        if (e == hipSuccess) e = hipMemsetAsync(h->loadword, 0, 4, st);
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(check_snapshot_kernel, dim3(grid_for(std::max<uint64_t>(npd, D), 256, 4096)), dim3(256),
+                               0, st, sp.tier_map, sp.util, npd, sp.batch, D, o->beta_max, h->loadword);
+            e = hipGetLastError();
+        }
     }
-    if (bad) {
-        cleanup();
+    if (e == hipSuccess) e = hipMemcpyAsync(&bad, h->loadword, 4, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e != hipSuccess) return fail(h, NETKV_EDEVICE, "snapshot upload failed: %s", hipGetErrorString(e));
+    if (bad)
         return fail(h, NETKV_EINVAL, "invalid snapshot:%s%s%s", (bad & 1) ? " tier_map value > 3" : "",
                     (bad & 2) ? " util outside [0,1) or NaN" : "", (bad & 4) ? " batch_size > beta_max" : "");
-    }
     if (!h->have_snap || h->P != P || h->D != D) {
         dfree(h->sl); dfree(h->dbase); dfree(h->dxlim);
         // route maps and rows of another shape no longer apply
@@ -3986,15 +4067,18 @@ netkv_status netkv_oracle_load(netkv_handle h, const netkv_oracle_t *o, void *st
         h->have_route = false;
         h->have_snap = false;
         if (dalloc(h->sl, (uint64_t)P * sl_pitch(D) + kRowPad) != hipSuccess || dalloc(h->dbase, D) != hipSuccess ||
-            dalloc(h->dxlim, D) != hipSuccess) {
-            cleanup();
+            dalloc(h->dxlim, D) != hipSuccess)
             return fail(h, NETKV_ENOMEM, "snapshot allocation failed");
-        }
     }
-    dfree(h->tier_map); dfree(h->util); dfree(h->n_inflight); dfree(h->free_mem);
-    dfree(h->adm_prev); dfree(h->queue); dfree(h->batch);
-    h->tier_map = tm; h->util = ut; h->n_inflight = ni; h->free_mem = fm;
-    h->adm_prev = ap; h->queue = qd; h->batch = bs;
+    std::swap(h->tier_map, sp.tier_map);
+    std::swap(h->util, sp.util);
+    std::swap(h->n_inflight, sp.n_inflight);
+    std::swap(h->free_mem, sp.free_mem);
+    std::swap(h->adm_prev, sp.adm_prev);
+    std::swap(h->queue, sp.queue);
+    std::swap(h->batch, sp.batch);
+    // the buffers exchanged out are the next load's if they have this shape
+    if (h->P != P || h->D != D) free_spare(sp);
     h->P = P;
     h->D = D;
     for (int i = 0; i < 4; ++i) {
