@@ -849,6 +849,17 @@ __global__ __launch_bounds__(256) void assemble_kernel(uint32_t n_req, uint32_t 
     if (hotr) hotr[c.r] = rec;
 }
 
+// The scoring records by batch index alone (the sequential form orders its
+// chains itself and scores nothing in prefill order).
+__global__ __launch_bounds__(256) void records_kernel(uint32_t n_req, uint32_t bt, uint32_t lstride, uint32_t zrow,
+                                                      const uint64_t *__restrict__ seg,
+                                                      const uint64_t *__restrict__ tpre,
+                                                      const Pre *__restrict__ hrec, const Cold *__restrict__ crec,
+                                                      Hot *__restrict__ hotr) {
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n_req) hotr[crec[i].r] = make_hot(hrec[i], scanned_at(seg, tpre, i), bt, lstride, zrow);
+}
+
 // ---------------------------------------------------------------- batch sorts
 //
 // Stable LSD radix sort for the batch orders (batches of kSortMinN + 1 to
@@ -2577,12 +2588,13 @@ __global__ void segment_kernel(const uint32_t *__restrict__ keys, uint32_t n, ui
     if (i + 1 == n || keys[i + 1] != k) end[k] = i + 1;
 }
 
-__global__ void prefill_key_kernel(Reqs rq, uint32_t P, const uint32_t *__restrict__ order_keys,
+// (an invalid request's record has length 0)
+__global__ void prefill_key_kernel(Reqs rq, uint32_t P, const Hot *__restrict__ hotr,
                                    uint32_t *__restrict__ keys, uint32_t *__restrict__ vals) {
     const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= rq.n_req) return;
-    keys[r] = order_keys[r] == kKeyInvalid ? P : rq.prefill[r];
-    vals[r] = r;
+    keys[r] = hotr[r].len == 0 ? P : rq.prefill[r];
+    if (vals) vals[r] = r;
 }
 
 // Non-cached tokens x (Eq. (2)) of request r on decodes d0 + stride * k,
@@ -3536,9 +3548,13 @@ Geometry geometry(netkv_handle h, uint32_t k) {
 // validate and key the requests, hash order (sort), common runs and
 // leaders, the segmented scan, prefill order (stable sort), scoring
 // records, leaders' prefix lengths, scoring, merge.  Launches kernels only.
+// Without score_pairs it ends with the leaders' prefix lengths and the
+// records by batch index (hotr): the sequential form scores its own pairs
+// (the scoring it skips took 100 of 574 us for 131,071 requests on 3,072
+// decodes).
 netkv_status run_select(netkv_handle h, Scratch &sc, const netkv_requests_t *req, uint32_t k, int32_t *idx,
                         float *score, const PairOut &po, bool pairs, uint32_t max_blocks, hipStream_t st,
-                        bool route2 = false, bool derive = true, Hot *hotr = nullptr) {
+                        bool route2 = false, bool derive = true, Hot *hotr = nullptr, bool score_pairs = true) {
     const uint64_t R = req->n_req;
     const Geometry geo = geometry(h, k);
     const uint32_t K = geo.K, C = geo.C, ngroup = geo.ngroup;
@@ -3622,7 +3638,12 @@ netkv_status run_select(netkv_handle h, Scratch &sc, const netkv_requests_t *req
     // prefill order (stable: the hash order within each prefill) and the
     // scoring records in it
     const uint32_t lstride = h->D * (uint32_t)sizeof(float);
-    if (own_prefill) {
+    if (!score_pairs) {
+        hipLaunchKernelGGL(records_kernel, dim3((uint32_t)((R + 255) / 256)), dim3(256), 0, st, (uint32_t)R,
+                           h->block_tokens, lstride, sc.lead_cap * lstride, (const uint64_t *)sc.seg,
+                           (const uint64_t *)sc.tpre, (const Pre *)sc.hrec, (const Cold *)sc.crec, hotr);
+        HIPCHK(h, hipGetLastError());
+    } else if (own_prefill) {
         // (the hash order's keys and permutation are no longer needed)
         HIPCHK(h, prefill_order(h, sc, (uint32_t)R, pbits, sc.keys_out, sc.perm, lstride, sc.lead_cap * lstride,
                                 hotr, st));
@@ -3640,6 +3661,7 @@ netkv_status run_select(netkv_handle h, Scratch &sc, const netkv_requests_t *req
         HIPCHK(h, hipEventRecord(h->ev_join, s2));
         HIPCHK(h, hipStreamWaitEvent(st, h->ev_join, 0));
     }
+    if (!score_pairs) return NETKV_OK;
     const uint32_t run_len = h->run_len_opt ? h->run_len_opt : auto_run_len(R, ngroup);
     const uint32_t n_runs = (uint32_t)((R + run_len - 1) / run_len);
     Order ord{sc.hot, sc.cold, sc.lead_lam, sc.hv, sc.n_valid, lcap};
@@ -3704,14 +3726,14 @@ netkv_status ensure_seq(netkv_handle h, uint64_t R, uint64_t P, bool seq, bool b
 // index in sc.hotr (grown to the batch).
 netkv_status select_owned(netkv_handle h, const netkv_requests_t *req, uint32_t k, int32_t *idx, float *score,
                           const PairOut &po, bool pairs, uint32_t max_blocks, hipStream_t st, bool route2 = false,
-                          bool want_hotr = false) {
+                          bool want_hotr = false, bool score_pairs = true) {
     const Geometry geo = geometry(h, k);
-    netkv_status e = ensure_scratch(h, h->sc, req->n_req, (uint64_t)req->n_req * geo.ngroup * geo.K,
-                                    req->n_hashes, st);
+    netkv_status e = ensure_scratch(h, h->sc, req->n_req,
+                                    score_pairs ? (uint64_t)req->n_req * geo.ngroup * geo.K : 0, req->n_hashes, st);
     if (e) return e;
     if (want_hotr && (e = ensure_hotr(h, req->n_req))) return e;
     return run_select(h, h->sc, req, k, idx, score, po, pairs, max_blocks, st, route2, true,
-                      want_hotr ? h->sc.hotr : nullptr);
+                      want_hotr ? h->sc.hotr : nullptr, score_pairs);
 }
 
 // ---- work buffers carved from the static scratch array (no allocation)
@@ -4793,25 +4815,31 @@ netkv_status netkv_select_sequential(netkv_handle h, const netkv_requests_t *req
     hipStream_t s = (hipStream_t)stream;
     const uint64_t R = req->n_req, P = h->P;
     if ((st = ensure_seq(h, R, P, true, false))) return st;
-    // validation, every request's scoring record by batch index and the
-    // leaders' prefix lengths, by the batch selection (its outputs are then
-    // overwritten by the chain; invalid requests keep -1 / NaN)
+    // validation (invalid requests get -1 / NaN), every request's scoring
+    // record by batch index and the leaders' prefix lengths, by the batch
+    // selection's ordering
     {
         TimingOff off(h);  // only the sequential kernel is timed
         const PairOut po{nullptr, nullptr, nullptr};
-        if ((st = select_owned(h, req, 1, out_idx, out_score, po, false, 0xFFFFFFFFu, s, false, true))) return st;
+        if ((st = select_owned(h, req, 1, out_idx, out_score, po, false, 0xFFFFFFFFu, s, false, true, false)))
+            return st;
     }
     // requests grouped by prefill instance, batch order kept inside a group
     const Reqs rq = make_reqs(req);
+    const uint32_t pbits = bits_for(P);
+    const bool own_sort = R > kSortMinN && R <= kSortMaxN && h->sc.sort_cnt;
     hipLaunchKernelGGL(prefill_key_kernel, dim3((uint32_t)((R + 255) / 256)), dim3(256), 0, s, rq, (uint32_t)P,
-                       (const uint32_t *)h->sc.keys_in, h->seq_keys, h->seq_vals);
+                       (const Hot *)h->sc.hotr, h->seq_keys, own_sort ? nullptr : h->seq_vals);
     size_t tb = h->sc.sort_tmp_bytes;
-    if (R > kSortMinN && R <= kSortMaxN && h->sc.sort_cnt)
-        HIPCHK(h, batch_sort_pairs(h, h->sc, h->seq_keys, h->seq_vals, h->seq_keys_out, h->seq_perm, (uint32_t)R,
-                                   bits_for(P), s));
+    if (own_sort && pbits <= kSortMaxBits)   // one pass
+        HIPCHK(h, sort_pass<false>(h, h->sc, h->seq_keys, nullptr, h->seq_keys_out, h->seq_perm, (uint32_t)R, 0, pbits,
+                                   nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, nullptr, nullptr, s));
+    else if (own_sort)
+        HIPCHK(h, batch_sort_pairs(h, h->sc, h->seq_keys, nullptr, h->seq_keys_out, h->seq_perm, (uint32_t)R, pbits,
+                                   s));
     else
         HIPCHK(h, rocprim::radix_sort_pairs<SortConfig>(h->sc.sort_tmp, tb, h->seq_keys, h->seq_keys_out,
-                                                        h->seq_vals, h->seq_perm, (uint32_t)R, 0, bits_for(P), s));
+                                                        h->seq_vals, h->seq_perm, (uint32_t)R, 0, pbits, s));
     hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(P, 256)), dim3(256), 0, s, h->seq_start, P, 0u);
     hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(P, 256)), dim3(256), 0, s, h->seq_end, P, 0u);
     hipLaunchKernelGGL(segment_kernel, dim3((uint32_t)((R + 255) / 256)), dim3(256), 0, s,
