@@ -1734,6 +1734,165 @@ __global__ __launch_bounds__(256) void reduce_kernel(uint32_t n_req, uint32_t nc
     }
 }
 
+// ---------------------------------------------------------------- direct selection
+//
+// Small batches in one launch, with no ordering: the ordering pipeline is 10
+// to 25 launches of 3-10 us each, while the matching it saves (one scan per
+// shared prefix instead of one per request) costs a small batch less than
+// that.  One wavefront per request (or `nw` of them, each a share of the
+// decodes): lanes look up the holder values of 64 blocks at a time, up to the
+// first block no decode holds; then, per chunk of C groups of 64 decodes, the
+// blocks' bitmap words are ANDed block by block (scalar), each decode lane
+// counting the blocks it still matches.  Costs, feasibility and the top-k
+// are those of the scoring kernel bit for bit: x < 2^24 is the same integer
+// in fp32 and in u32, and larger x are rounded to fp32 as there.  fly: the
+// cost factors are computed here from the snapshot instead of read from the
+// derived rows (saves derive_kernel's launch).  With hotr, each request's
+// record and its row of B_tok * j are written for the ranking sweep, every
+// request being its own leader (row r of lam).
+template <int K, int C>
+__global__ __launch_bounds__(kBlock) void direct_kernel(Snap s, Table t, Reqs rq, uint32_t nw, bool fly,
+                                                        uint32_t k_out, int32_t *__restrict__ out_idx,
+                                                        float *__restrict__ out_score, uint32_t *__restrict__ err,
+                                                        Hot *__restrict__ hotr, float *__restrict__ lam) {
+    __shared__ uint64_t wkeys[kWavesPerBlock][K];
+    const uint32_t lane = threadIdx.x % kWave, wv = wave_index();
+    const uint32_t r = blockIdx.x * (kWavesPerBlock / nw) + wv / nw, part = wv % nw;
+    if (r >= rq.n_req) return;   // only with one wavefront per request (no barrier then)
+    const uint32_t p = as_const(rq.prefill)[r], len = as_const(rq.len)[r];
+    const uint64_t a = as_const(rq.off)[r], b = as_const(rq.off)[r + 1];
+    const bool ok = p < s.P && len >= 1 && b >= a && b <= rq.n_hashes && b - a == (uint64_t)(len / s.block_tokens);
+    uint64_t best[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q) best[q] = kEmptyKey;
+    if (ok) {
+        const uint32_t n = (uint32_t)(b - a), bt = s.block_tokens;
+        // holder values of blocks k0 .. k0+63, one per lane; returns how many
+        // blocks from k0 on some decode holds
+        auto lookup = [&](uint32_t k0, uint32_t &v) {
+            const uint32_t k = k0 + lane;
+            v = k < n ? holder_lane(t, rq.hashes[a + k]) : kNoHolder;
+            const lmask none = ballot(v == kNoHolder);
+            return none ? (uint32_t)__builtin_ctzll(none) : (uint32_t)kWave;
+        };
+        uint32_t v0 = kNoHolder;
+        const uint32_t m0 = lookup(0, v0);   // n = 0 gives 0
+        for (uint32_t base = part * kWave * C; base < s.D; base += nw * kWave * C) {
+            // this lane's leading blocks on each column's decode
+            lmask alive[C];
+            uint32_t j[C];
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                alive[q] = ~0ull;
+                j[q] = 0;
+            }
+            uint32_t v = v0, m = m0;
+            for (uint32_t k0 = 0;;) {
+                constexpr uint32_t U = C > 4 ? 2 : 4;   // blocks whose words load together
+                lmask any = ~0ull;
+                for (uint32_t k = 0; k < m && any; k += U) {
+                    lmask w[U][C];
+#pragma unroll
+                    for (uint32_t u = 0; u < U; ++u) {
+                        const uint32_t vk = k + u < m ? (uint32_t)__builtin_amdgcn_readlane((int)v, (int)((k + u) % kWave))
+                                                      : kNoHolder;
+                        holder_masks<C>(t, vk, base, w[u]);
+                    }
+                    any = 0;
+#pragma unroll
+                    for (uint32_t u = 0; u < U; ++u) {
+#pragma unroll
+                        for (int q = 0; q < C; ++q) {
+                            alive[q] &= w[u][q];
+                            j[q] += in_mask(alive[q]) ? 1u : 0u;
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < C; ++q) any |= alive[q];
+                }
+                k0 += kWave;
+                if (m < (uint32_t)kWave || !any || k0 >= n) break;
+                m = lookup(k0, v);
+            }
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                const uint32_t d = base + q * kWave + lane;
+                if (d < s.D) {
+                    const uint32_t x = len - bt * j[q];
+                    float cost;
+                    bool feas;
+                    if (fly) {
+                        const uint64_t pd = (uint64_t)p * s.D + d;
+                        const uint32_t tau = s.tier_map[pd] & 3u;
+                        cost = fmaf((float)x, sec_per_token(s, tau, p, s.util[pd]),
+                                    __fadd_rn(tier_latency(s, tau), load_term(s, d)));
+                        // bpt x <= m_d - m_min, both below 2^64
+                        const uint64_t mem = s.free_mem[d];
+                        feas = mem >= s.m_min && (uint64_t)s.bpt * x <= mem - s.m_min;
+                    } else {
+                        const uint64_t o = (uint64_t)p * s.slp + d;
+                        const float2 r1 = s.sl[o];
+                        uint32_t cb = __float_as_uint(fmaf((float)x, r1.x, r1.y));
+                        if (s.sr) {
+                            const float2 r2 = s.sr[o];
+                            cb = min(cb, __float_as_uint(fmaf((float)x, r2.x, r2.y)));
+                        }
+                        cost = __uint_as_float(cb);
+                        feas = (uint64_t)x < s.dxlim[d];
+                    }
+                    if (hotr) lam[(uint64_t)r * s.D + d] = (float)(bt * j[q]);
+                    const uint64_t key = feas ? ((uint64_t)__float_as_uint(cost) << 32) | d : kEmptyKey;
+                    if (key < best[K - 1]) topk_insert<K>(best, key);
+                }
+            }
+        }
+    }
+    if (hotr && part == 0 && lane == 0) {
+        const bool own = len >= kExactTok;
+        hotr[r] = ok ? Hot{p * s.slp * (uint32_t)sizeof(float2), own ? 0u : r * s.D * (uint32_t)sizeof(float),
+                           __float_as_uint((float)len), __float_as_uint(own ? -1.0f : __builtin_inff())}
+                     : Hot{0, 0, 0, 0};
+    }
+    // the wavefront's K least keys, in lanes 0 .. K-1
+    uint64_t mine = kEmptyKey;
+    auto wave_best = [&](uint64_t head, uint64_t &mn) {
+        const uint32_t hi = wave_min_u32_dpp((uint32_t)(head >> 32));
+        const uint32_t lo = wave_min_u32_dpp((uint32_t)(head >> 32) == hi ? (uint32_t)head : 0xFFFFFFFFu);
+        mn = ((uint64_t)hi << 32) | lo;
+    };
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+        uint64_t mn;
+        wave_best(best[0], mn);
+        if (lane == (uint32_t)q) mine = mn;
+        if (q + 1 < K && best[0] == mn) {   // keys differ, so one lane pops (or all do when nothing is left)
+#pragma unroll
+            for (int u = 0; u + 1 < K; ++u) best[u] = best[u + 1];
+            best[K - 1] = kEmptyKey;
+        }
+    }
+    if (nw > 1) {   // one request per workgroup: every wavefront arrives here
+        if (lane < (uint32_t)K) wkeys[wv][lane] = mine;
+        __syncthreads();
+        if (part != 0) return;
+        uint64_t head = lane < nw * K ? wkeys[lane / K][lane % K] : kEmptyKey;
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            uint64_t mn;
+            wave_best(head, mn);
+            if (lane == (uint32_t)q) mine = mn;
+            if (head == mn) head = kEmptyKey;
+        }
+    }
+    if (lane < k_out) {
+        const uint64_t o = (uint64_t)r * k_out + lane;
+        out_idx[o] = !ok || mine == kEmptyKey ? -1 : (int32_t)(uint32_t)mine;
+        out_score[o] = !ok ? __builtin_nanf("") : mine == kEmptyKey ? __builtin_inff()
+                                                                    : __uint_as_float((uint32_t)(mine >> 32));
+    }
+    if (!ok && part == 0 && lane == 0) atomicOr(err, kErrRequest);
+}
+
 // ---------------------------------------------------------------- ranking sweep
 //
 // Re-ranking of a batch under congestion scenarios (Sec. V-D).  Prefix
@@ -3042,6 +3201,8 @@ struct netkv_ctx {
     uint32_t *loadword = nullptr;         // validation flags of the load calls
     float *spt_scen = nullptr;    // ranking sweep: seconds per token of every (scenario, p, d)
     uint64_t spt_cap = 0;
+    float *dlam = nullptr;        // [R][D] B_tok * j of a direct selection with records
+    uint64_t dlam_cap = 0;
     int32_t *base_idx = nullptr;
     float *base_score = nullptr;
     uint64_t base_n = 0;
@@ -3543,6 +3704,70 @@ Geometry geometry(netkv_handle h, uint32_t k) {
     return g;
 }
 
+// Batches of the direct selection (one launch, no ordering): at most
+// kDirectWork (request, group of 64 decodes) tasks, and at most kDirectBlocks
+// block hashes per request on average, so that no request's walk over its
+// blocks is long.  Options that shape the ordering or the scoring runs ask
+// for the ordering pipeline.
+constexpr uint64_t kDirectWork = 1ull << 18;
+constexpr uint64_t kDirectFly = 1ull << 15;     // tasks up to which the factors are computed in place
+constexpr uint64_t kDirectBlocks = 64;
+
+bool direct_batch(netkv_handle h, uint64_t R, uint64_t n_hashes) {
+    const uint64_t ng = ((uint64_t)h->D + kWave - 1) / kWave;
+    return R * ng <= kDirectWork && n_hashes <= R * kDirectBlocks + 4096 && h->reuse_opt && !h->run_len_opt &&
+           !h->cols_opt && !h->lead_cap_opt;
+}
+
+// The cost factors of a call on `s` (and of the staged routes with `two`).
+hipError_t launch_derive(netkv_handle h, const Snap &sn, bool two, hipStream_t s) {
+    const uint64_t nd = std::max<uint64_t>((uint64_t)h->P * h->D, h->D);
+    hipLaunchKernelGGL(derive_kernel, dim3((uint32_t)((nd + 255) / 256)), dim3(256), 0, s, sn, h->sl, h->dbase,
+                       h->dxlim);
+    if (two)
+        hipLaunchKernelGGL(derive_route_kernel, dim3((uint32_t)((nd + 255) / 256)), dim3(256), 0, s, sn,
+                           (const uint8_t *)h->rt1, (const float *)h->ru1, (const uint8_t *)h->rt2,
+                           (const float *)h->ru2, h->sr);
+    return hipGetLastError();
+}
+
+netkv_status run_direct(netkv_handle h, const netkv_requests_t *req, uint32_t k, int32_t *idx, float *score,
+                        hipStream_t st, bool route2, Hot *hotr = nullptr, float *lam = nullptr) {
+    const uint32_t R = req->n_req, ng = (h->D + kWave - 1) / kWave;
+    const bool two = route2 && h->have_route;
+    const bool fly = !two && !hotr && (uint64_t)R * ng <= kDirectFly;
+    Snap sn = make_snap(h);
+    if (!fly) HIPCHK(h, launch_derive(h, sn, two, st));
+    if (two) sn.sr = h->sr;
+    // four wavefronts share a request when one each leaves most of the chip idle
+    const uint32_t nw = ng > 4 && R <= 2048 ? 4 : 1;
+    const uint32_t C = ng == 1 ? 1 : ng <= 4 || (nw > 1 && ng <= 16) ? 4 : 12;
+    const uint32_t grid = (uint32_t)(((uint64_t)R * nw + kWavesPerBlock - 1) / kWavesPerBlock);
+    const Table t = make_table(h);
+    const Reqs rq = make_reqs(req);
+    HIPCHK(h, time_begin(h, st));
+#define NETKV_DIRECT(KK)                                                                                             \
+    do {                                                                                                             \
+        if (C == 1)                                                                                                  \
+            hipLaunchKernelGGL((direct_kernel<KK, 1>), dim3(grid), dim3(kBlock), 0, st, sn, t, rq, nw, fly, k, idx,   \
+                               score, h->errword, hotr, lam);                                                        \
+        else if (C == 4)                                                                                             \
+            hipLaunchKernelGGL((direct_kernel<KK, 4>), dim3(grid), dim3(kBlock), 0, st, sn, t, rq, nw, fly, k, idx,   \
+                               score, h->errword, hotr, lam);                                                        \
+        else                                                                                                         \
+            hipLaunchKernelGGL((direct_kernel<KK, 12>), dim3(grid), dim3(kBlock), 0, st, sn, t, rq, nw, fly, k, idx,  \
+                               score, h->errword, hotr, lam);                                                        \
+    } while (0)
+    if (k <= 1) NETKV_DIRECT(1);
+    else if (k <= 2) NETKV_DIRECT(2);
+    else if (k <= 4) NETKV_DIRECT(4);
+    else NETKV_DIRECT(8);
+#undef NETKV_DIRECT
+    HIPCHK(h, hipGetLastError());
+    HIPCHK(h, time_end(h, st));
+    return NETKV_OK;
+}
+
 // The whole selection of one batch on `st` with the work buffers of sc
 // (which must hold the batch: R <= order_cap, R * ngroup * K <= partial_cap):
 // validate and key the requests, hash order (sort), common runs and
@@ -3578,17 +3803,9 @@ netkv_status run_select(netkv_handle h, Scratch &sc, const netkv_requests_t *req
         HIPCHK(h, hipEventRecord(h->ev_fork0, st));
         HIPCHK(h, hipStreamWaitEvent(s2, h->ev_fork0, 0));
     }
-    const uint64_t nd = std::max<uint64_t>((uint64_t)h->P * h->D, h->D);
-    if (derive)
-        hipLaunchKernelGGL(derive_kernel, dim3((uint32_t)((nd + 255) / 256)), dim3(256), 0, s2, sn, h->sl, h->dbase,
-                           h->dxlim);
-    if (route2 && h->have_route) {
-        if (derive)
-            hipLaunchKernelGGL(derive_route_kernel, dim3((uint32_t)((nd + 255) / 256)), dim3(256), 0, s2, sn,
-                               (const uint8_t *)h->rt1, (const float *)h->ru1, (const uint8_t *)h->rt2,
-                               (const float *)h->ru2, h->sr);
-        sn.sr = h->sr;
-    }
+    const bool two = route2 && h->have_route;
+    if (derive) HIPCHK(h, launch_derive(h, sn, two, s2));
+    if (two) sn.sr = h->sr;
     // the own batch sort (its first pass takes positions as values) where
     // its buffers are there and the batch is in its range
     const bool own_sort = R > kSortMinN && R <= kSortMaxN && sc.sort_cnt != nullptr;
@@ -3687,6 +3904,16 @@ netkv_status ensure_hotr(netkv_handle h, uint64_t n) {
     h->sc.hotr_cap = 0;
     if (dalloc(h->sc.hotr, n) != hipSuccess) return fail(h, NETKV_ENOMEM, "record scratch allocation failed");
     h->sc.hotr_cap = n;
+    return NETKV_OK;
+}
+
+// Rows of the direct selection's records: every request its own leader.
+netkv_status ensure_dlam(netkv_handle h, uint64_t R) {
+    if (R * h->D <= h->dlam_cap) return NETKV_OK;
+    dfree(h->dlam);
+    h->dlam_cap = 0;
+    if (dalloc(h->dlam, R * h->D) != hipSuccess) return fail(h, NETKV_ENOMEM, "record scratch allocation failed");
+    h->dlam_cap = R * h->D;
     return NETKV_OK;
 }
 
@@ -3990,6 +4217,7 @@ void netkv_destroy(netkv_handle h) {
         dfree(h->errword);
         dfree(h->loadword);
         dfree(h->spt_scen);
+        dfree(h->dlam);
         dfree(h->base_idx);
         dfree(h->base_score);
         dfree(h->cnt);
@@ -4495,6 +4723,8 @@ netkv_status netkv_select_batch(netkv_handle h, const netkv_requests_t *req, uin
         po.score = pairs->score;
         want_pairs = po.j || po.feas || po.score;
     }
+    if (!want_pairs && direct_batch(h, req->n_req, req->n_hashes))
+        return run_direct(h, req, k, out_idx, out_score, s, true);
     return select_owned(h, req, k, out_idx, out_score, po, want_pairs, 0xFFFFFFFFu, s, true);
 }
 
@@ -4516,6 +4746,7 @@ netkv_status netkv_select_batch_noalloc(netkv_handle h, const netkv_requests_t *
     Scratch sc;
     uint64_t r_sub = 0;
     if ((st = carve_static(h, base, req->n_req, k, sc, r_sub))) return st;
+    if (direct_batch(h, req->n_req, req->n_hashes)) return run_direct(h, req, k, out_idx, out_score, s, true);
     const PairOut po{nullptr, nullptr, nullptr};
     for (uint64_t r0 = 0; r0 < req->n_req; r0 += r_sub) {
         netkv_requests_t sub = *req;
@@ -4545,6 +4776,7 @@ netkv_status netkv_reserve(netkv_handle h, uint32_t max_req, uint64_t max_hashes
     }
     netkv_status st = ensure_scratch(h, h->sc, max_req, elems, max_hashes, (hipStream_t)stream);
     if (!st) st = ensure_hotr(h, max_req);
+    if (!st) st = ensure_dlam(h, std::min<uint64_t>(max_req, std::max<uint64_t>(kDirectWork / ((h->D + kWave - 1) / kWave), 1)));
     if (!st) st = ensure_seq(h, max_req, h->P, true, true);
     return st;
 }
@@ -4616,11 +4848,19 @@ netkv_status netkv_rank_sweep(netkv_handle h, const netkv_requests_t *req, uint3
     }
     // the selection under the loaded congestion, keeping every request's
     // scoring record by batch index and the leaders' prefix lengths
+    const float *lead_lam = nullptr;
     {
         TimingOff off(h);  // only the sweep kernel is timed
         const PairOut po{nullptr, nullptr, nullptr};
-        if ((st = select_owned(h, req, 1, h->base_idx, h->base_score, po, false, 0xFFFFFFFFu, s, false, true)))
-            return st;
+        if (direct_batch(h, R, req->n_hashes)) {
+            if ((st = ensure_hotr(h, R)) || (st = ensure_dlam(h, R))) return st;
+            if ((st = run_direct(h, req, 1, h->base_idx, h->base_score, s, false, h->sc.hotr, h->dlam))) return st;
+            lead_lam = h->dlam;
+        } else {
+            if ((st = select_owned(h, req, 1, h->base_idx, h->base_score, po, false, 0xFFFFFFFFu, s, false, true)))
+                return st;
+            lead_lam = h->sc.lead_lam;
+        }
     }
     hipLaunchKernelGGL(derive_scen_kernel, dim3((uint32_t)((nspt + 255) / 256)), dim3(256), 0, s, sn, util_scen, nspt,
                        h->spt_scen);
@@ -4636,7 +4876,7 @@ netkv_status netkv_rank_sweep(netkv_handle h, const netkv_requests_t *req, uint3
     unsigned long long *fl = (unsigned long long *)out_flips;
     HIPCHK(h, time_begin(h, s));
 #define NETKV_SWEEP(KK)                                                                                            \
-    launch_sweep_k<KK>((uint32_t)D, lds, grid, lds_bytes, s, sn, t, rq, h->sc.hotr, h->sc.lead_lam, h->spt_scen,    \
+    launch_sweep_k<KK>((uint32_t)D, lds, grid, lds_bytes, s, sn, t, rq, h->sc.hotr, lead_lam, h->spt_scen,          \
                        n_scen, h->base_idx, h->base_score, k, out_idx, out_score, fl)
     if (k == 1) NETKV_SWEEP(1);
     else if (k == 2) NETKV_SWEEP(2);
@@ -4815,14 +5055,25 @@ netkv_status netkv_select_sequential(netkv_handle h, const netkv_requests_t *req
     hipStream_t s = (hipStream_t)stream;
     const uint64_t R = req->n_req, P = h->P;
     if ((st = ensure_seq(h, R, P, true, false))) return st;
+    const float *ll = nullptr;
     // validation (invalid requests get -1 / NaN), every request's scoring
     // record by batch index and the leaders' prefix lengths, by the batch
     // selection's ordering
     {
         TimingOff off(h);  // only the sequential kernel is timed
         const PairOut po{nullptr, nullptr, nullptr};
-        if ((st = select_owned(h, req, 1, out_idx, out_score, po, false, 0xFFFFFFFFu, s, false, true, false)))
-            return st;
+        if (direct_batch(h, R, req->n_hashes)) {
+            // (the chain orders its requests with the selection's sort buffers)
+            if ((st = ensure_scratch(h, h->sc, R, 0, req->n_hashes, s)) || (st = ensure_hotr(h, R)) ||
+                (st = ensure_dlam(h, R)))
+                return st;
+            if ((st = run_direct(h, req, 1, out_idx, out_score, s, false, h->sc.hotr, h->dlam))) return st;
+            ll = h->dlam;
+        } else {
+            if ((st = select_owned(h, req, 1, out_idx, out_score, po, false, 0xFFFFFFFFu, s, false, true, false)))
+                return st;
+            ll = h->sc.lead_lam;
+        }
     }
     // requests grouped by prefill instance, batch order kept inside a group
     const Reqs rq = make_reqs(req);
@@ -4849,7 +5100,6 @@ netkv_status netkv_select_sequential(netkv_handle h, const netkv_requests_t *req
     const Snap sn = make_snap(h);
     const Table t = make_table(h);
     const Hot *hr = h->sc.hotr;
-    const float *ll = h->sc.lead_lam;
     const uint32_t *ord = h->seq_perm, *b0 = h->seq_start, *b1 = h->seq_end;
     // one workgroup per prefill instance, all of them resident at once on
     // 256 CUs up to 1,024 prefills (256 threads: four workgroups per CU
