@@ -130,6 +130,9 @@ struct Snap {
 constexpr uint32_t kHeldOne = 0x80000000u;
 constexpr uint32_t kNoHolder = 0xFFFFFFFFu;
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+
 struct Table {
     const uint64_t *keys;   // [buckets][2] distinct resident hashes
     const uint32_t *vals;   // [buckets][2] holder values
@@ -191,6 +194,29 @@ __device__ inline uint32_t holder_lane(const Table &t, uint64_t h) {
     const uint64_t slot = k1.x == h ? 2 * (uint64_t)b1 : k1.y == h ? 2 * (uint64_t)b1 + 1
                         : k2.x == h ? 2 * (uint64_t)b2 : k2.y == h ? 2 * (uint64_t)b2 + 1 : ~0ull;
     return slot == ~0ull ? kNoHolder : t.vals[slot];
+}
+
+// The shared index: the hashes that two or more decodes hold, with their
+// bitmap rows.  One 16-byte slot holds a key and its row, and linear probing
+// at a load factor of a sixth to a third finds most keys, and most absences,
+// with one load (the whole index takes three, two of them dependent).
+struct Shared {
+    const u32x4 *b;       // [mask + 1] key (0 = empty), row, 0; null when there is none
+    uint32_t shift;       // 64 - log2(slots)
+    uint32_t mask;        // slots - 1
+};
+
+__device__ inline uint32_t shared_slot(const Shared &t, uint64_t h) { return (uint32_t)((h * kGolden) >> t.shift); }
+
+// The row of h, given the content x of slot i where its probes start.
+__device__ inline uint32_t shared_find(const Shared &t, uint64_t h, uint32_t i, u32x4 x) {
+    for (;;) {   // ends: there are more slots than keys
+        const uint64_t k = ((uint64_t)x.y << 32) | x.x;
+        if (k == h) return h == 0 ? kNoHolder : x.z;
+        if (k == 0) return kNoHolder;
+        i = (i + 1) & t.mask;
+        x = t.b[i];
+    }
 }
 
 // Is h resident on decode d?
@@ -694,7 +720,6 @@ __global__ __launch_bounds__(256) void order_kernel(Reqs rq, uint32_t P, uint32_
 // (one round up to 2^24 requests), each thread combining its consecutive
 // totals, the threads' results scanned by shuffles and then across the
 // wavefronts, with the running prefix of earlier rounds.
-typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 constexpr uint32_t kPrefixThreads = 1024;
 constexpr uint32_t kPrefixWaves = kPrefixThreads / kWave;
 constexpr uint32_t kPrefixPer = 16;
@@ -1893,6 +1918,419 @@ __global__ __launch_bounds__(kBlock) void direct_kernel(Snap s, Table t, Reqs rq
     if (!ok && part == 0 && lane == 0) atomicOr(err, kErrRequest);
 }
 
+// ---------------------------------------------------------------- bounded selection
+//
+// Batches beyond the direct selection, without ordering: most (request,
+// decode) pairs cannot win, and a bound per group of 64 decodes shows it.
+// With x >= xlo non-cached tokens on every decode of group g,
+//     cost >= fma(xlo, least spt of the group, least constant of the group),
+// in fp32 as well, since each operand is no larger and rounding is monotone.
+// xlo = l - B_tok * m, m = leading blocks that any decode holds.  A request
+// is scored on the group of least bound; every other group whose bound
+// exceeds the K-th best cost so far is ruled out, and the rest are scored
+// too, so the selection is the exact top-k with its ties.  Network tiers
+// differ by factors, so on fat trees 1.1 of 48 groups are scored on average
+// (2 to 4 for k = 3 under memory pressure).
+//   derive_bound_kernel -- the cost factors, and per (p, group) the bound's.
+//   match_kernel        -- per request the holder values of its leading held
+//                          blocks and their count m.
+//   bounded_kernel      -- bounds, scoring, top-k, outputs.
+// Where nothing can be ruled out every group is scored by one wavefront,
+// which costs more than the ordering pipeline's shared scans.
+
+// lanes per request of match_kernel, and blocks per lane and step (measured at
+// 1,048,576 requests of 25 blocks / 262,144 of 191 / 99,991 of 25, us: 16 x 2
+// 303 / 261 / 29, 8 x 2 250 / 266 / 30, 8 x 4 265 / 264 / 30, 4 x 4 236 / 279 /
+// 40, 4 x 8 301 / 278 / 38)
+constexpr uint32_t kStepLanes = 8, kStepBlocks = 2;
+constexpr uint32_t kBoundMaxGroups = kWave;   // one lane per group: pools of up to 4,096 decodes
+
+struct Bounds {
+    const float2 *lo;    // [P][ngroup] least spt and constant of the group
+    const float2 *lo2;   // the staged routes', or null
+    const float *xm;     // [ngroup * 64] largest feasible x of a decode, capped at 2^24; -1: none
+    const float *xg;     // [ngroup] the group's largest xm
+    uint32_t ngroup;
+};
+
+// Least value over the wavefront of four registers at once, in a .. d of
+// every lane (the scheme of wave_min3_u32 with the fourth value in the rows
+// it leaves unused).
+__device__ inline void wave_min4_u32(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t (&m)[4]) {
+    const auto s1 = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    const auto s2 = __builtin_amdgcn_permlane32_swap(c, d, false, false);
+    const uint32_t x = min((uint32_t)s1[0], (uint32_t)s1[1]), y = min((uint32_t)s2[0], (uint32_t)s2[1]);
+    const auto s16 = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    uint32_t z = min((uint32_t)s16[0], (uint32_t)s16[1]);
+    z = min(z, dpp_u32<0xB1>(z));
+    z = min(z, dpp_u32<0x4E>(z));
+    z = min(z, dpp_u32<0x124>(z));
+    z = min(z, dpp_u32<0x128>(z));
+    m[0] = (uint32_t)__builtin_amdgcn_readlane((int)z, 0);
+    m[1] = (uint32_t)__builtin_amdgcn_readlane((int)z, 32);
+    m[2] = (uint32_t)__builtin_amdgcn_readlane((int)z, 16);
+    m[3] = (uint32_t)__builtin_amdgcn_readlane((int)z, 48);
+}
+
+// One wavefront per (p, group of 64 decodes): the derived row entries and the
+// bound's factors; p = 0's wavefronts also write the per-decode values.
+__global__ __launch_bounds__(kBlock) void derive_bound_kernel(Snap s, const uint8_t *__restrict__ t1,
+                                                              const float *__restrict__ u1,
+                                                              const uint8_t *__restrict__ t2,
+                                                              const float *__restrict__ u2, uint32_t ngroup,
+                                                              float2 *__restrict__ sl, float2 *__restrict__ sr,
+                                                              float *__restrict__ dbase, uint64_t *__restrict__ dxlim,
+                                                              float2 *__restrict__ lo, float2 *__restrict__ lo2,
+                                                              float *__restrict__ xm, float *__restrict__ xg) {
+    const uint32_t lane = threadIdx.x % kWave;
+    const uint64_t task = (uint64_t)blockIdx.x * kWavesPerBlock + wave_index();
+    const uint32_t p = (uint32_t)(task / ngroup), g = (uint32_t)(task % ngroup), d = g * kWave + lane;
+    if (p >= s.P) return;
+    const bool in = d < s.D;
+    // least values as fp32 bits (non-negative); a staged route's likewise
+    float2 a = make_float2(__builtin_inff(), __builtin_inff()), b = a;
+    const float base = in ? load_term(s, d) : 0.0f;
+    if (in) {
+        const uint64_t i = (uint64_t)p * s.D + d;
+        const uint32_t tau = s.tier_map[i] & 3u;
+        a = make_float2(sec_per_token(s, tau, p, s.util[i]), __fadd_rn(tier_latency(s, tau), base));
+        sl[(uint64_t)p * s.slp + d] = a;
+        if (sr) {
+            const uint32_t x = t1[i] & 3u, y = t2[i] & 3u;
+            b = make_float2(sec_per_token(s, x, p, u1[i]) + sec_per_token_n(s, y, 0.0f, u2[i]),
+                            __fadd_rn(__fadd_rn(tier_latency(s, x), tier_latency(s, y)), base));
+            sr[(uint64_t)p * s.slp + d] = b;
+        }
+    }
+    uint32_t m[4];
+    wave_min4_u32(__float_as_uint(a.x), __float_as_uint(a.y), __float_as_uint(b.x), __float_as_uint(b.y), m);
+    // a finite factor, so that xlo = 0 gives the constant and not NaN
+    const uint32_t top = 0x7F7FFFFFu;
+    if (lane == 0) {
+        lo[task] = make_float2(__uint_as_float(min(m[0], top)), __uint_as_float(m[1]));
+        if (sr) lo2[task] = make_float2(__uint_as_float(min(m[2], top)), __uint_as_float(m[3]));
+    }
+    if (p == 0) {
+        const uint64_t lim = in ? feasible_limit(s, s.free_mem[d]) : 0;
+        // largest feasible x plus one, at most 2^24 + 1
+        const uint32_t x1 = (uint32_t)(lim <= kExactTok ? lim : (uint64_t)kExactTok + 1);
+        xm[d] = (float)((int32_t)x1 - 1);
+        if (in) {
+            dbase[d] = base;
+            dxlim[d] = lim;
+        }
+        const uint32_t most = kExactTok + 1u - wave_min_u32_dpp(kExactTok + 1u - x1);
+        if (lane == 0) xg[g] = (float)((int32_t)most - 1);
+    }
+}
+
+// Holder values of the leading held blocks of every request, L neighbouring
+// lanes per request, U blocks each per step with their loads issued together
+// (the kernel is bound by the number of dependent loads per wavefront), and
+// their count (kNoPre for an invalid request).  Steps go through the shared
+// index, which stays in cache, so the blocks looked up past the run's end
+// cost no memory access; the first block it does not have is looked up in
+// the whole index, two lines of it from memory, and only where that block
+// has one holder do the following steps go there.
+template <uint32_t L, uint32_t U>
+__global__ __launch_bounds__(kBlock) void match_kernel(Snap s, Table t, Shared sh, Reqs rq,
+                                                       uint32_t *__restrict__ hv, uint32_t *__restrict__ mm,
+                                                       uint32_t *__restrict__ err) {
+    const uint32_t sub = threadIdx.x % L, seg0 = (threadIdx.x % kWave) - sub;
+    const uint64_t r = (uint64_t)blockIdx.x * (kBlock / L) + threadIdx.x / L;
+    const bool in = r < rq.n_req;
+    uint32_t p, len, n = 0;
+    uint64_t a = 0;
+    const bool ok = in && request_ok(rq, s, (uint32_t)r, p, len, a, n);
+    if (!ok) n = 0;
+    uint32_t m = n;
+    bool act = n > 0;
+    // blocks from k on through an index, up to the first it does not have
+    // (past the run's end: a miss, so m is at most n)
+    auto steps = [&](auto lookup, uint32_t k) {
+        for (; __any(act); k += L * U) {
+            uint64_t h[U];
+            uint32_t v[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t kk = k + u * L + sub;
+                h[u] = act && kk < n ? rq.hashes[a + kk] : 0ull;   // hash 0 is held nowhere
+            }
+            lookup(h, v);
+            uint32_t first = L * U;
+#pragma unroll
+            for (int u = (int)U - 1; u >= 0; --u) {
+                const uint32_t miss = (uint32_t)(ballot(v[u] == kNoHolder) >> seg0) & (uint32_t)((1ull << L) - 1);
+                if (miss) first = (uint32_t)u * L + (uint32_t)__builtin_ctz(miss);
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u)
+                if (act && u * L + sub < first) hv[a + k + u * L + sub] = v[u];
+            if (act && first < L * U) {
+                m = k + first;
+                act = false;
+            }
+        }
+    };
+    uint32_t k = 0;
+    if (sh.b) {
+        steps(
+            [&](const uint64_t (&h)[U], uint32_t (&v)[U]) {
+                uint32_t i[U];
+                u32x4 x[U];
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u) {
+                    i[u] = shared_slot(sh, h[u]);
+                    x[u] = u32x4{0, 0, 0, 0};
+                    if (h[u]) x[u] = sh.b[i[u]];
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u) v[u] = shared_find(sh, h[u], i[u], x[u]);
+            },
+            0);
+        uint32_t v = kNoHolder;
+        if (sub == 0 && m < n) v = holder_lane(t, rq.hashes[a + m]);
+        if (v != kNoHolder) hv[a + m] = v;
+        act = ((ballot(v != kNoHolder) >> seg0) & 1ull) != 0;
+        if (act) {
+            k = m + 1;
+            m = n;
+        }
+    }
+    steps(
+        [&](const uint64_t (&h)[U], uint32_t (&v)[U]) {
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) v[u] = holder_lane(t, h[u]);
+        },
+        k);
+    if (in && sub == 0) mm[r] = ok ? m : kNoPre;
+    if (ballot(in && !ok) && threadIdx.x % kWave == 0) atomicOr(err, kErrRequest);
+}
+
+// Leading words of this wavefront's `word`s (lane k: block k's, zero past the
+// run) that hold each lane's bit, 0 .. 64 (few: fewer than 16 words are not
+// zero).  An inclusive AND over the lanes leaves the decodes that hold every
+// block up to k in lane k; a lane's count is found by a binary search over
+// the words in LDS, of which it reads the half with its bit.  20 vector
+// instructions for short runs, 33 for long ones, and no scalar ones (a loop
+// over the blocks with read-lanes took 3 vector and 8 scalar instructions a
+// block, and the scalar unit bound the kernel).
+__device__ inline uint32_t leading_words(uint64_t *wds, uint64_t word, uint32_t lane, bool few) {
+    uint32_t lo = (uint32_t)word, hi = (uint32_t)(word >> 32);
+    lo &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x111, 0xF, 0xF, false);   // row_shr 1
+    hi &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)hi, 0x111, 0xF, 0xF, false);
+    lo &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x112, 0xF, 0xF, false);
+    hi &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)hi, 0x112, 0xF, 0xF, false);
+    lo &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x114, 0xF, 0xF, false);
+    hi &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)hi, 0x114, 0xF, 0xF, false);
+    lo &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x118, 0xF, 0xF, false);
+    hi &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)hi, 0x118, 0xF, 0xF, false);
+    if (!few) {
+        lo &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x142, 0xA, 0xF, false);   // row_bcast 15
+        hi &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)hi, 0x142, 0xA, 0xF, false);
+        lo &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x143, 0xC, 0xF, false);   // row_bcast 31
+        hi &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)hi, 0x143, 0xC, 0xF, false);
+    }
+    __builtin_amdgcn_wave_barrier();
+    wds[lane] = ((uint64_t)hi << 32) | lo;
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t *half = (const uint32_t *)wds + (lane >> 5);
+    const uint32_t sh = lane & 31u;
+    uint32_t j = 0;
+    if (!few) {
+        j += ((half[2 * (j + 31)] >> sh) & 1u) << 5;
+        j += ((half[2 * (j + 15)] >> sh) & 1u) << 4;
+    }
+    j += ((half[2 * (j + 7)] >> sh) & 1u) << 3;
+    j += ((half[2 * (j + 3)] >> sh) & 1u) << 2;
+    j += ((half[2 * (j + 1)] >> sh) & 1u) << 1;
+    j += (half[2 * j] >> sh) & 1u;
+    if (!few) j += (half[2 * j] >> sh) & 1u;   // 63 found so far: the last word
+    return j;
+}
+
+// Each wavefront takes `per` (a multiple of 4, at most 64 / K) consecutive
+// requests, four at a time with their loads issued together; the results are
+// gathered one per lane and stored at the end.
+template <int K, bool TWO>
+__global__ __launch_bounds__(kBlock) void bounded_kernel(Snap s, Table t, Reqs rq, Bounds bd,
+                                                         const uint32_t *__restrict__ hv,
+                                                         const uint32_t *__restrict__ mm, uint32_t per, uint32_t k_out,
+                                                         int32_t *__restrict__ out_idx, float *__restrict__ out_score) {
+    constexpr int Q = 4;
+    __shared__ uint64_t lds[kWavesPerBlock][Q][kWave];
+    const uint32_t lane = threadIdx.x % kWave;
+    const uint32_t wv = wave_index();
+    const uint64_t first = ((uint64_t)blockIdx.x * kWavesPerBlock + wv) * per;
+    if (first >= rq.n_req) return;
+    const uint32_t r0 = (uint32_t)first;
+    const uint32_t cnt = rq.n_req - r0 < per ? rq.n_req - r0 : per;
+    const uint32_t bt = s.block_tokens, ng = bd.ngroup;
+    const float xgl = lane < ng ? bd.xg[lane] : -1.0f;
+    const uint32_t lg = lane < ng ? lane : 0u;
+    uint32_t res_b = 0xFFFFFFFFu, res_d = 0xFFFFFFFFu;   // K keys per request, request i's from lane i * K
+    for (uint32_t i0 = 0; i0 < cnt; i0 += Q) {
+        uint32_t p[Q], len[Q], m[Q], mq[Q];
+        uint64_t a[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint32_t r = r0 + (i0 + q < cnt ? i0 + q : i0);
+            m[q] = as_const(mm)[r];
+            p[q] = as_const(rq.prefill)[r];
+            len[q] = as_const(rq.len)[r];
+            a[q] = as_const(rq.off)[r];
+        }
+        // bounds of the groups (lane g: group g), and the leading holder
+        // values (lane k: block k); an invalid request is scored as one
+        // without blocks and its result dropped
+        float2 b1[Q], b2[Q];
+        uint32_t v[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            mq[q] = m[q] == kNoPre ? 0u : m[q];
+            if (m[q] == kNoPre) p[q] = 0;
+            b1[q] = (bd.lo + (uint64_t)p[q] * ng)[lg];
+            if (TWO) b2[q] = (bd.lo2 + (uint64_t)p[q] * ng)[lg];
+            v[q] = kNoHolder;
+            if (lane < mq[q]) v[q] = (hv + a[q])[lane];
+        }
+        uint32_t lb[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const float xlo = (float)(len[q] - bt * mq[q]);
+            uint32_t c = __float_as_uint(fmaf(xlo, b1[q].x, b1[q].y));
+            if (TWO) c = min(c, __float_as_uint(fmaf(xlo, b2[q].x, b2[q].y)));
+            // (requests of 2^24 tokens or more: the limits are capped there)
+            lb[q] = lane < ng && (xlo <= xgl || len[q] >= kExactTok) ? c : 0xFFFFFFFFu;
+        }
+        uint32_t least[Q];
+        wave_min4_u32(lb[0], lb[1], lb[2], lb[3], least);
+        // the group of least bound of each request: its rows, words and limits
+        auto words = [&](uint32_t g, uint32_t v_) -> uint64_t {
+            uint64_t wd = 0;
+            if (v_ < kHeldOne) wd = t.bits[(uint64_t)v_ * t.bpitch + g];
+            else if (v_ != kNoHolder && (v_ & ~kHeldOne) / kWave == g) wd = 1ull << ((v_ & ~kHeldOne) % kWave);
+            return wd;
+        };
+        uint32_t home[Q];
+        float2 row[Q], row2[Q];
+        float xm[Q];
+        uint64_t word[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            // (no group can take it: lane 0, where nothing is feasible)
+            home[q] = (uint32_t)__builtin_ctzll(ballot(lb[q] == least[q]));
+            const uint64_t o = (uint64_t)p[q] * s.slp + home[q] * kWave;   // (past D: padding or the next row)
+            row[q] = (s.sl + o)[lane];
+            if (TWO) row2[q] = (s.sr + o)[lane];
+            xm[q] = (bd.xm + home[q] * kWave)[lane];
+            word[q] = words(home[q], v[q]);
+        }
+        // the lane's cost bits of request q on its decode of group g
+        auto cost = [&](int q, uint32_t g, float2 x1, float2 x2, float lim, uint64_t wd) -> uint32_t {
+            uint32_t j = leading_words(lds[wv][q], wd, lane, mq[q] < 16);
+            for (uint32_t k0 = kWave; k0 < mq[q] && __any(j == k0); k0 += kWave) {   // runs of more than 64 held blocks
+                const uint32_t vk = k0 + lane < mq[q] ? (hv + a[q] + k0)[lane] : kNoHolder;
+                const uint32_t more = leading_words(lds[wv][q], words(g, vk), lane, mq[q] - k0 < 16);
+                j += j == k0 ? more : 0u;
+            }
+            const uint32_t x = len[q] - bt * j;
+            const float xf = (float)x;
+            bool feas = xf <= lim;
+            if (len[q] >= kExactTok) {
+                const uint32_t d = g * kWave + lane;
+                feas = d < s.D && (uint64_t)x < s.dxlim[d < s.D ? d : 0u];
+            }
+            const uint32_t c = route_cost<TWO>(xf, x1, x2);
+            return feas ? c : 0xFFFFFFFFu;
+        };
+        uint32_t cb[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) cb[q] = cost(q, home[q], row[q], row2[q], xm[q], word[q]);
+        uint32_t best[Q];
+        wave_min4_u32(cb[0], cb[1], cb[2], cb[3], best);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            // keys kept: lanes 0 .. K-1 of kb / kd, ascending (cost bits, decode)
+            uint32_t kb = 0xFFFFFFFFu, kd = 0xFFFFFFFFu;
+            uint32_t thr;   // k-th best cost bits
+            if (K == 1) {
+                thr = best[q];
+                kb = best[q];
+                if (best[q] != 0xFFFFFFFFu) kd = home[q] * kWave + (uint32_t)__builtin_ctzll(ballot(cb[q] == best[q]));
+            }
+            // merge the column of group g into the kept keys
+            auto merge = [&](uint32_t g, uint32_t c) {
+                uint32_t ob = kb, od = kd;   // the old keys, consumed as they are placed
+                uint32_t nb = 0xFFFFFFFFu, nd = 0xFFFFFFFFu;
+                const uint32_t dl = g * kWave + lane;
+#pragma unroll
+                for (int u = 0; u < K; ++u) {
+                    const uint32_t mn = wave_min_u32_dpp(min(c, ob));
+                    if (mn == 0xFFFFFFFFu) break;
+                    const uint32_t dm = wave_min_u32_dpp(min(c == mn ? dl : 0xFFFFFFFFu, ob == mn ? od : 0xFFFFFFFFu));
+                    if (c == mn && dl == dm) c = 0xFFFFFFFFu;
+                    if (ob == mn && od == dm) ob = 0xFFFFFFFFu;
+                    nb = write_lane(mn, (uint32_t)u, nb);
+                    nd = write_lane(dm, (uint32_t)u, nd);
+                }
+                kb = nb;
+                kd = nd;
+            };
+            if (K > 1) {
+                if (best[q] != 0xFFFFFFFFu) merge(home[q], cb[q]);
+                thr = (uint32_t)__builtin_amdgcn_readlane((int)kb, (int)k_out - 1);
+            }
+            lmask left = ballot(lb[q] <= thr && lb[q] != 0xFFFFFFFFu) & ~(1ull << home[q]);
+            while (left) {
+                const uint32_t g = (uint32_t)__builtin_ctzll(left);
+                const uint64_t o = (uint64_t)p[q] * s.slp + g * kWave;
+                const float2 x1 = (s.sl + o)[lane];
+                const float2 x2 = TWO ? (s.sr + o)[lane] : x1;
+                const uint32_t c = cost(q, g, x1, x2, (bd.xm + g * kWave)[lane], words(g, v[q]));
+                if (K == 1) {
+                    const uint32_t mn = wave_min_u32_dpp(c);
+                    if (mn <= thr && mn != 0xFFFFFFFFu) {
+                        const uint32_t dm = g * kWave + (uint32_t)__builtin_ctzll(ballot(c == mn));
+                        if (mn < thr || dm < kd) kd = dm;
+                        thr = mn;
+                        kb = mn;
+                    }
+                } else if (ballot(c <= thr && c != 0xFFFFFFFFu)) {
+                    merge(g, c);
+                    thr = (uint32_t)__builtin_amdgcn_readlane((int)kb, (int)k_out - 1);
+                }
+                left &= left - 1;
+                left &= ballot(lb[q] <= thr);
+            }
+            if (i0 + q < cnt) {
+                const uint32_t slot = (i0 + q) * K;
+                if (m[q] == kNoPre) {   // marks an invalid request: no cost has these bits with a decode
+                    res_b = write_lane(0xFFFFFFFEu, slot, res_b);
+                } else if (K == 1) {
+                    res_b = write_lane(kb, slot, res_b);
+                    res_d = write_lane(kd, slot, res_d);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < K; ++u) {
+                        res_b = write_lane((uint32_t)__builtin_amdgcn_readlane((int)kb, u), slot + u, res_b);
+                        res_d = write_lane((uint32_t)__builtin_amdgcn_readlane((int)kd, u), slot + u, res_d);
+                    }
+                }
+            }
+        }
+    }
+    // lane i * K + u: key u of request i
+    const uint32_t i = lane / K, u = lane % K;
+    const uint32_t headb = (uint32_t)__shfl((int)res_b, (int)(i * K), kWave);
+    if (i < cnt && u < k_out) {
+        const bool bad = headb == 0xFFFFFFFEu, none = res_b == 0xFFFFFFFFu;
+        const uint64_t o = (uint64_t)(r0 + i) * k_out + u;
+        out_idx[o] = bad || none ? -1 : (int32_t)res_d;
+        out_score[o] = bad ? __builtin_nanf("") : none ? __builtin_inff() : __uint_as_float(res_b);
+    }
+}
+
 // ---------------------------------------------------------------- ranking sweep
 //
 // Re-ranking of a batch under congestion scenarios (Sec. V-D).  Prefix
@@ -2285,6 +2723,10 @@ __global__ __launch_bounds__(256) void classify_kernel(const uint64_t *__restric
     }
 }
 
+// Shared hashes up to which the shared index is built: 48 to 96 bytes each, at
+// most 64 MiB, a quarter of the last-level cache.
+constexpr uint64_t kSharedMaxRows = 1ull << 20;
+
 // Cuckoo insertion of the distinct hashes.  A key goes to an empty slot of
 // either candidate bucket (compare-and-swap 0 -> key); when all four slots
 // are taken it displaces the key of a random slot by atomic exchange (a
@@ -2301,42 +2743,62 @@ __device__ inline bool try_place(unsigned long long *bk, uint64_t key) {
     return false;
 }
 
+// Place one key; false when the walk did not end.
+__device__ inline bool cuckoo_place(unsigned long long *tab, uint32_t shift, uint64_t key, uint32_t rnd) {
+    uint32_t from = 0xFFFFFFFFu;   // bucket the carried key was displaced from
+    for (uint32_t kick = 0; kick < kMaxKicks; ++kick) {
+        uint32_t b1, b2;
+        buckets_of(key, shift, b1, b2);
+        if (try_place(tab + 2 * (uint64_t)b1, key) || try_place(tab + 2 * (uint64_t)b2, key)) return true;
+        // displace from the bucket the key did not just leave; the walk's
+        // choices come from the full-period 32-bit LCG of Knuth and Lewis
+        // (multiplier 1664525, increment 1013904223; Press et al.,
+        // Numerical Recipes, "quick and dirty" generator)
+        rnd = rnd * 1664525u + 1013904223u;
+        const uint32_t b = (b1 == from) ? b2 : (b2 == from) ? b1 : ((rnd >> 31) ? b2 : b1);
+        const unsigned long long old = atomicExch(tab + 2 * (uint64_t)b + ((rnd >> 30) & 1u),
+                                                  (unsigned long long)key);
+        if (old == 0ull || old == key) return true;
+        key = old;
+        from = b;
+    }
+    return false;
+}
+
+__device__ inline uint64_t slot_of(const uint64_t *keys, uint32_t shift, uint64_t key) {
+    uint32_t b1, b2;
+    buckets_of(key, shift, b1, b2);
+    if (keys[2 * (uint64_t)b1] == key) return 2 * (uint64_t)b1;
+    if (keys[2 * (uint64_t)b1 + 1] == key) return 2 * (uint64_t)b1 + 1;
+    if (keys[2 * (uint64_t)b2] == key) return 2 * (uint64_t)b2;
+    if (keys[2 * (uint64_t)b2 + 1] == key) return 2 * (uint64_t)b2 + 1;
+    return ~0ull;
+}
+
 __global__ __launch_bounds__(256) void index_insert_kernel(uint64_t *__restrict__ keys, uint32_t shift,
                                                            const uint64_t *__restrict__ skey, uint64_t n,
                                                            uint32_t *__restrict__ err) {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    unsigned long long *tab = (unsigned long long *)keys;
     for (; i < n; i += stride) {
         if (!run_head(skey, i)) continue;
-        uint64_t key = skey[i];
-        uint32_t from = 0xFFFFFFFFu;   // bucket the carried key was displaced from
-        uint32_t rnd = (uint32_t)(key ^ (key >> 32)) ^ (uint32_t)i;   // walk state (a 32-bit LCG)
-        bool done = false;
-        for (uint32_t kick = 0; kick < kMaxKicks && !done; ++kick) {
-            uint32_t b1, b2;
-            buckets_of(key, shift, b1, b2);
-            if (try_place(tab + 2 * (uint64_t)b1, key) || try_place(tab + 2 * (uint64_t)b2, key)) {
-                done = true;
-                break;
-            }
-            // displace from the bucket the key did not just leave; the walk's
-            // choices come from the full-period 32-bit LCG of Knuth and Lewis
-            // (multiplier 1664525, increment 1013904223; Press et al.,
-            // Numerical Recipes, "quick and dirty" generator)
-            rnd = rnd * 1664525u + 1013904223u;
-            const uint32_t b = (b1 == from) ? b2 : (b2 == from) ? b1 : ((rnd >> 31) ? b2 : b1);
-            const unsigned long long old = atomicExch(tab + 2 * (uint64_t)b + ((rnd >> 30) & 1u),
-                                                      (unsigned long long)key);
-            if (old == 0ull || old == key) {
-                done = true;
-                break;
-            }
-            key = old;
-            from = b;
-        }
-        if (!done) atomicOr(err, kErrTableFull);
+        const uint64_t key = skey[i];
+        if (!cuckoo_place((unsigned long long *)keys, shift, key, (uint32_t)(key ^ (key >> 32)) ^ (uint32_t)i))
+            atomicOr(err, kErrTableFull);
     }
+}
+
+// Fills the shared index (row v of the bitmap pool is key row_key[v]'s,
+// v >= 1; the keys are distinct).
+__global__ __launch_bounds__(256) void shared_insert_kernel(u32x4 *__restrict__ tab, uint32_t shift, uint32_t mask,
+                                                            const uint64_t *__restrict__ row_key, uint32_t rows) {
+    const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x + 1;
+    if (v >= rows) return;
+    const uint64_t key = row_key[v];
+    uint32_t i = (uint32_t)((key * kGolden) >> shift);
+    // ends: there are more slots than keys
+    while (atomicCAS((unsigned long long *)(tab + i), 0ull, (unsigned long long)key) != 0ull) i = (i + 1) & mask;
+    ((uint32_t *)(tab + i))[2] = v;
 }
 
 // Holder values, once every key has its final slot.  Bitmap rows are
@@ -2347,6 +2809,7 @@ __global__ __launch_bounds__(256) void index_value_kernel(const uint64_t *__rest
                                                           uint32_t bpitch, const uint64_t *__restrict__ skey,
                                                           const uint32_t *__restrict__ dec, uint64_t n,
                                                           uint32_t *__restrict__ rows_used,
+                                                          uint64_t *__restrict__ row_key,
                                                           uint32_t *__restrict__ err) {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -2360,16 +2823,11 @@ __global__ __launch_bounds__(256) void index_value_kernel(const uint64_t *__rest
             v = kHeldOne | dmin;
         } else {
             v = atomicAdd(rows_used, 1u);
+            row_key[v] = key;
             uint64_t *row = bits + (uint64_t)v * bpitch;
             for (uint64_t x = i; x < e; ++x) row[dec[x] / 64u] |= 1ull << (dec[x] % 64u);
         }
-        uint32_t b1, b2;
-        buckets_of(key, shift, b1, b2);
-        uint64_t slot = ~0ull;
-        if (keys[2 * (uint64_t)b1] == key) slot = 2 * (uint64_t)b1;
-        else if (keys[2 * (uint64_t)b1 + 1] == key) slot = 2 * (uint64_t)b1 + 1;
-        else if (keys[2 * (uint64_t)b2] == key) slot = 2 * (uint64_t)b2;
-        else if (keys[2 * (uint64_t)b2 + 1] == key) slot = 2 * (uint64_t)b2 + 1;
+        const uint64_t slot = slot_of(keys, shift, key);
         if (slot == ~0ull) atomicOr(err, kErrTableFull);
         else vals[slot] = v;
     }
@@ -3196,11 +3654,20 @@ struct netkv_ctx {
     uint64_t *bits = nullptr;    // [rows][bpitch] holder bitmaps
     uint64_t table_bytes = 0, buckets = 0, rows = 0, distinct = 0;
     uint32_t log2b = 0, bpitch = 0;
+    // shared index: the hashes of two or more holders (null: none was built)
+    u32x4 *sh_tab = nullptr;
+    uint32_t sh_log2b = 0;
     // scratch
     uint32_t *errword = nullptr;          // request / selection errors (sticky)
     uint32_t *loadword = nullptr;         // validation flags of the load calls
     float *spt_scen = nullptr;    // ranking sweep: seconds per token of every (scenario, p, d)
     uint64_t spt_cap = 0;
+    // the bounded selection: bound factors per (p, group), limits, match counts
+    float2 *bnd_lo = nullptr, *bnd_lo2 = nullptr;
+    float *bnd_xm = nullptr, *bnd_xg = nullptr;
+    uint32_t bnd_P = 0, bnd_D = 0;
+    uint32_t *match_m = nullptr;
+    uint64_t match_cap = 0;
     float *dlam = nullptr;        // [R][D] B_tok * j of a direct selection with records
     uint64_t dlam_cap = 0;
     int32_t *base_idx = nullptr;
@@ -3426,6 +3893,16 @@ hipError_t sort_tmp_bytes_for(uint64_t R, size_t &bytes) {
     return err;
 }
 
+netkv_status ensure_hv(netkv_handle h, Scratch &sc, uint64_t n_hashes) {
+    if (n_hashes <= sc.hv_cap && sc.hv) return NETKV_OK;
+    dfree(sc.hv);
+    sc.hv_cap = 0;
+    if (dalloc(sc.hv, std::max<uint64_t>(n_hashes, 1)) != hipSuccess)
+        return fail(h, NETKV_ENOMEM, "holder value scratch allocation failed");
+    sc.hv_cap = std::max<uint64_t>(n_hashes, 1);
+    return NETKV_OK;
+}
+
 // The handle's work buffers for a batch of R requests with n_hashes block
 // hashes and partial_elems per-group keys: grown (never shrunk) when a batch
 // needs more than any earlier one or than netkv_reserve provided.
@@ -3474,13 +3951,7 @@ netkv_status ensure_scratch(netkv_handle h, Scratch &sc, uint64_t R, uint64_t pa
     // holder values of the leaders' blocks: at most one per block of the
     // batch (fewer if runs overlap in the hash array; leaders that do not
     // fit look their blocks up in the leader kernel)
-    if (n_hashes > sc.hv_cap || !sc.hv) {
-        dfree(sc.hv);
-        sc.hv_cap = 0;
-        if (dalloc(sc.hv, std::max<uint64_t>(n_hashes, 1)) != hipSuccess)
-            return fail(h, NETKV_ENOMEM, "holder value scratch allocation failed");
-        sc.hv_cap = std::max<uint64_t>(n_hashes, 1);
-    }
+    if (netkv_status e = ensure_hv(h, sc, n_hashes)) return e;
     const uint32_t lc = lead_capacity(R, h->D);
     if (lc > sc.lead_cap || sc.lead_D != h->D || !sc.lead) {
         dfree(sc.lead);
@@ -3704,19 +4175,23 @@ Geometry geometry(netkv_handle h, uint32_t k) {
     return g;
 }
 
-// Batches of the direct selection (one launch, no ordering): at most
-// kDirectWork (request, group of 64 decodes) tasks, and at most kDirectBlocks
-// block hashes per request on average, so that no request's walk over its
-// blocks is long.  Options that shape the ordering or the scoring runs ask
-// for the ordering pipeline.
-constexpr uint64_t kDirectWork = 1ull << 18;
-constexpr uint64_t kDirectFly = 1ull << 15;     // tasks up to which the factors are computed in place
-constexpr uint64_t kDirectBlocks = 64;
+// Batches of the direct selection: its work grows with the (request, group of
+// 64 decodes) tasks, and with the blocks where runs are longer than 32.
+// Measured against the bounded selection (us, tasks -> direct / bounded): 48
+// decodes 8,192 -> 21 / 22, 16,384 -> 34 / 29; 768 decodes 12,288 -> 21 / 27,
+// 49,152 -> 64 / 28; 3,072 decodes 24,576 -> 45 / 54; runs of 191 blocks on
+// 48 decodes 2,048 -> 22 / 28, 4,096 -> 30 / 31.  Where records are wanted
+// the ordering pipeline is the other choice: 192 decodes 49,152 -> 56 / 109,
+// 3,072 decodes 49,152 -> 63 / 103, 196,608 -> 247 / 123.  Options that shape
+// the ordering or the scoring runs ask for that pipeline.
+constexpr uint64_t kDirectTasks = 1ull << 14;
+constexpr uint64_t kDirectRecordTasks = 1ull << 16;
 
-bool direct_batch(netkv_handle h, uint64_t R, uint64_t n_hashes) {
+bool unordered(netkv_handle h) { return h->reuse_opt && !h->run_len_opt && !h->cols_opt && !h->lead_cap_opt; }
+
+bool direct_batch(netkv_handle h, uint64_t R, uint64_t n_hashes, uint64_t tasks) {
     const uint64_t ng = ((uint64_t)h->D + kWave - 1) / kWave;
-    return R * ng <= kDirectWork && n_hashes <= R * kDirectBlocks + 4096 && h->reuse_opt && !h->run_len_opt &&
-           !h->cols_opt && !h->lead_cap_opt;
+    return ng * std::max<uint64_t>(R, n_hashes / 32) <= tasks && unordered(h);
 }
 
 // The cost factors of a call on `s` (and of the staged routes with `two`).
@@ -3735,7 +4210,7 @@ netkv_status run_direct(netkv_handle h, const netkv_requests_t *req, uint32_t k,
                         hipStream_t st, bool route2, Hot *hotr = nullptr, float *lam = nullptr) {
     const uint32_t R = req->n_req, ng = (h->D + kWave - 1) / kWave;
     const bool two = route2 && h->have_route;
-    const bool fly = !two && !hotr && (uint64_t)R * ng <= kDirectFly;
+    const bool fly = !two && !hotr;
     Snap sn = make_snap(h);
     if (!fly) HIPCHK(h, launch_derive(h, sn, two, st));
     if (two) sn.sr = h->sr;
@@ -3894,6 +4369,79 @@ netkv_status run_select(netkv_handle h, Scratch &sc, const netkv_requests_t *req
     else
         HIPCHK(h, launch_score_reduce<8>(h, sc, sn, t, rq, ord, run_len, n_runs, ngroup, C, po, pairs, k, idx,
                                          score, st));
+    return NETKV_OK;
+}
+
+// The bounded selection: pools of up to 64 groups of 64 decodes.  It looks up
+// every block of every request, the ordering pipeline about one per request:
+// with runs of 191 blocks 65,536 requests take 115 us here and 200 us there,
+// 262,144 requests 448 us here and 398 us there.
+bool bounded_batch(netkv_handle h, uint64_t R, uint64_t n_hashes) {
+    return (h->D + kWave - 1) / kWave <= kBoundMaxGroups && unordered(h) &&
+           (R <= (1ull << 17) || n_hashes <= 64 * R);
+}
+
+netkv_status ensure_bounds(netkv_handle h, uint64_t R, uint64_t n_hashes) {
+    const uint32_t ng = (h->D + kWave - 1) / kWave;
+    if (h->bnd_P != h->P || h->bnd_D != h->D) {
+        dfree(h->bnd_lo); dfree(h->bnd_lo2); dfree(h->bnd_xm); dfree(h->bnd_xg);
+        h->bnd_P = h->bnd_D = 0;
+        if (dalloc(h->bnd_lo, (uint64_t)h->P * ng) != hipSuccess || dalloc(h->bnd_lo2, (uint64_t)h->P * ng) != hipSuccess ||
+            dalloc(h->bnd_xm, (uint64_t)ng * kWave) != hipSuccess || dalloc(h->bnd_xg, ng) != hipSuccess)
+            return fail(h, NETKV_ENOMEM, "bound table allocation failed");
+        h->bnd_P = h->P;
+        h->bnd_D = h->D;
+    }
+    if (R > h->match_cap) {
+        dfree(h->match_m);
+        h->match_cap = 0;
+        if (dalloc(h->match_m, R) != hipSuccess) return fail(h, NETKV_ENOMEM, "match scratch allocation failed");
+        h->match_cap = R;
+    }
+    return ensure_hv(h, h->sc, n_hashes);
+}
+
+netkv_status run_bounded(netkv_handle h, const netkv_requests_t *req, uint32_t k, int32_t *idx, float *score,
+                         hipStream_t st, bool route2) {
+    const uint64_t R = req->n_req;
+    const uint32_t ng = (h->D + kWave - 1) / kWave;
+    netkv_status e = ensure_bounds(h, R, req->n_hashes);
+    if (e) return e;
+    const bool two = route2 && h->have_route;
+    Snap sn = make_snap(h);
+    const Table t = make_table(h);
+    const Reqs rq = make_reqs(req);
+    const uint64_t tasks = (uint64_t)h->P * ng;
+    hipLaunchKernelGGL(derive_bound_kernel, dim3((uint32_t)((tasks + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock),
+                       0, st, sn, (const uint8_t *)h->rt1, (const float *)h->ru1, (const uint8_t *)h->rt2,
+                       (const float *)h->ru2, ng, h->sl, two ? h->sr : nullptr, h->dbase, h->dxlim, h->bnd_lo, h->bnd_lo2,
+                       h->bnd_xm, h->bnd_xg);
+    const Shared sh{h->sh_tab, 64 - h->sh_log2b, (1u << h->sh_log2b) - 1u};
+    hipLaunchKernelGGL((match_kernel<kStepLanes, kStepBlocks>), dim3((uint32_t)((R * kStepLanes + kBlock - 1) / kBlock)),
+                       dim3(kBlock), 0, st, sn, t, sh, rq, h->sc.hv, h->match_m, h->errword);
+    HIPCHK(h, hipGetLastError());
+    if (two) sn.sr = h->sr;
+    const Bounds bd{h->bnd_lo, h->bnd_lo2, h->bnd_xm, h->bnd_xg, ng};
+    const uint32_t K = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : 8;
+    uint32_t per = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(16, 64 / K), std::max<uint64_t>(4, R / 8192 / 4 * 4));
+    const uint32_t grid = (uint32_t)((R + (uint64_t)per * kWavesPerBlock - 1) / ((uint64_t)per * kWavesPerBlock));
+    HIPCHK(h, time_begin(h, st));
+#define NETKV_BOUNDED(KK)                                                                                             \
+    do {                                                                                                              \
+        if (two)                                                                                                      \
+            hipLaunchKernelGGL((bounded_kernel<KK, true>), dim3(grid), dim3(kBlock), 0, st, sn, t, rq, bd,             \
+                               (const uint32_t *)h->sc.hv, (const uint32_t *)h->match_m, per, k, idx, score);         \
+        else                                                                                                          \
+            hipLaunchKernelGGL((bounded_kernel<KK, false>), dim3(grid), dim3(kBlock), 0, st, sn, t, rq, bd,            \
+                               (const uint32_t *)h->sc.hv, (const uint32_t *)h->match_m, per, k, idx, score);         \
+    } while (0)
+    if (K == 1) NETKV_BOUNDED(1);
+    else if (K == 2) NETKV_BOUNDED(2);
+    else if (K == 4) NETKV_BOUNDED(4);
+    else NETKV_BOUNDED(8);
+#undef NETKV_BOUNDED
+    HIPCHK(h, hipGetLastError());
+    HIPCHK(h, time_end(h, st));
     return NETKV_OK;
 }
 
@@ -4214,10 +4762,12 @@ void netkv_destroy(netkv_handle h) {
         dfree(h->table);
         dfree(h->tvals);
         dfree(h->bits);
+        dfree(h->sh_tab);
         dfree(h->errword);
         dfree(h->loadword);
         dfree(h->spt_scen);
         dfree(h->dlam);
+        dfree(h->bnd_lo); dfree(h->bnd_lo2); dfree(h->bnd_xm); dfree(h->bnd_xg); dfree(h->match_m);
         dfree(h->base_idx);
         dfree(h->base_score);
         dfree(h->cnt);
@@ -4641,6 +5191,12 @@ netkv_status netkv_cache_load(netkv_handle h, uint32_t n_decode, const uint64_t 
         return fail(h, NETKV_ENOMEM, "holder bitmap allocation of %llu bytes failed",
                     (unsigned long long)(8 * rows * bpitch));
     }
+    uint64_t *row_key = nullptr;   // the key of each bitmap row
+    if (dalloc(row_key, rows) != hipSuccess) {
+        cleanup();
+        dfree(bm);
+        return fail(h, NETKV_ENOMEM, "staging allocation failed");
+    }
     e = hipMemsetAsync(bm, 0, 8 * rows * bpitch, st);
     // build at the planned size; should a build fail to place every key (a
     // random walk that did not end), rebuild with twice the buckets, twice
@@ -4649,7 +5205,7 @@ netkv_status netkv_cache_load(netkv_handle h, uint32_t n_decode, const uint64_t 
         nbk = 1ull << log2b;
         if (e == hipSuccess && (dalloc(tab, 2 * nbk) != hipSuccess || dalloc(tv, 2 * nbk) != hipSuccess)) {
             cleanup();
-            dfree(tab); dfree(tv); dfree(bm);
+            dfree(tab); dfree(tv); dfree(bm); dfree(row_key);
             return fail(h, NETKV_ENOMEM, "index allocation of %llu bytes failed", (unsigned long long)(24 * nbk));
         }
         if (e == hipSuccess) e = hipMemsetAsync(tab, 0, 16 * nbk, st);
@@ -4674,12 +5230,35 @@ netkv_status netkv_cache_load(netkv_handle h, uint32_t n_decode, const uint64_t 
         if (e == hipSuccess) {
             hipLaunchKernelGGL(index_value_kernel, dim3(grid_for(total, 256, 16384)), dim3(256), 0, st,
                                (const uint64_t *)tab, tv, 64u - log2b, bm, bpitch, (const uint64_t *)dkey,
-                               (const uint32_t *)dec, total, (uint32_t *)cnt, h->loadword);
+                               (const uint32_t *)dec, total, (uint32_t *)cnt, row_key, h->loadword);
             e = hipGetLastError();
         }
         if (e == hipSuccess) e = hipMemcpyAsync(&bad, h->loadword, 4, hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
     }
+    // the shared index; without it (too many shared hashes to stay in cache,
+    // no memory) lookups go to the whole index
+    dfree(h->sh_tab);
+    if (e == hipSuccess && !bad && rows > 1 && rows <= kSharedMaxRows) {
+        uint32_t lb = 3;
+        while ((1ull << lb) < 3 * rows) ++lb;
+        u32x4 *sk = nullptr;
+        if (dalloc(sk, 1ull << lb) == hipSuccess) {
+            e = hipMemsetAsync(sk, 0, 16ull << lb, st);
+            if (e == hipSuccess) {
+                hipLaunchKernelGGL(shared_insert_kernel, dim3((uint32_t)((rows + 255) / 256)), dim3(256), 0, st, sk,
+                                   64u - lb, (1u << lb) - 1u, (const uint64_t *)row_key, (uint32_t)rows);
+                e = hipGetLastError();
+            }
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            if (e != hipSuccess) dfree(sk);
+            h->sh_tab = sk;
+            h->sh_log2b = lb;
+        } else {
+            (void)hipGetLastError();
+        }
+    }
+    dfree(row_key);
     cleanup();
     if (e != hipSuccess || bad) {
         dfree(tab);
@@ -4723,8 +5302,9 @@ netkv_status netkv_select_batch(netkv_handle h, const netkv_requests_t *req, uin
         po.score = pairs->score;
         want_pairs = po.j || po.feas || po.score;
     }
-    if (!want_pairs && direct_batch(h, req->n_req, req->n_hashes))
+    if (!want_pairs && direct_batch(h, req->n_req, req->n_hashes, kDirectTasks))
         return run_direct(h, req, k, out_idx, out_score, s, true);
+    if (!want_pairs && bounded_batch(h, req->n_req, req->n_hashes)) return run_bounded(h, req, k, out_idx, out_score, s, true);
     return select_owned(h, req, k, out_idx, out_score, po, want_pairs, 0xFFFFFFFFu, s, true);
 }
 
@@ -4746,7 +5326,7 @@ netkv_status netkv_select_batch_noalloc(netkv_handle h, const netkv_requests_t *
     Scratch sc;
     uint64_t r_sub = 0;
     if ((st = carve_static(h, base, req->n_req, k, sc, r_sub))) return st;
-    if (direct_batch(h, req->n_req, req->n_hashes)) return run_direct(h, req, k, out_idx, out_score, s, true);
+    if (direct_batch(h, req->n_req, req->n_hashes, kDirectTasks)) return run_direct(h, req, k, out_idx, out_score, s, true);
     const PairOut po{nullptr, nullptr, nullptr};
     for (uint64_t r0 = 0; r0 < req->n_req; r0 += r_sub) {
         netkv_requests_t sub = *req;
@@ -4775,8 +5355,9 @@ netkv_status netkv_reserve(netkv_handle h, uint32_t max_req, uint64_t max_hashes
         elems = std::max<uint64_t>(elems, (uint64_t)max_req * geo.ngroup * geo.K);
     }
     netkv_status st = ensure_scratch(h, h->sc, max_req, elems, max_hashes, (hipStream_t)stream);
+    if (!st && bounded_batch(h, max_req, 0)) st = ensure_bounds(h, max_req, max_hashes);
     if (!st) st = ensure_hotr(h, max_req);
-    if (!st) st = ensure_dlam(h, std::min<uint64_t>(max_req, std::max<uint64_t>(kDirectWork / ((h->D + kWave - 1) / kWave), 1)));
+    if (!st) st = ensure_dlam(h, std::min<uint64_t>(max_req, kDirectRecordTasks / ((h->D + kWave - 1) / kWave)));
     if (!st) st = ensure_seq(h, max_req, h->P, true, true);
     return st;
 }
@@ -4852,7 +5433,7 @@ netkv_status netkv_rank_sweep(netkv_handle h, const netkv_requests_t *req, uint3
     {
         TimingOff off(h);  // only the sweep kernel is timed
         const PairOut po{nullptr, nullptr, nullptr};
-        if (direct_batch(h, R, req->n_hashes)) {
+        if (direct_batch(h, R, req->n_hashes, kDirectRecordTasks)) {
             if ((st = ensure_hotr(h, R)) || (st = ensure_dlam(h, R))) return st;
             if ((st = run_direct(h, req, 1, h->base_idx, h->base_score, s, false, h->sc.hotr, h->dlam))) return st;
             lead_lam = h->dlam;
@@ -5062,7 +5643,7 @@ netkv_status netkv_select_sequential(netkv_handle h, const netkv_requests_t *req
     {
         TimingOff off(h);  // only the sequential kernel is timed
         const PairOut po{nullptr, nullptr, nullptr};
-        if (direct_batch(h, R, req->n_hashes)) {
+        if (direct_batch(h, R, req->n_hashes, kDirectRecordTasks)) {
             // (the chain orders its requests with the selection's sort buffers)
             if ((st = ensure_scratch(h, h->sc, R, 0, req->n_hashes, s)) || (st = ensure_hotr(h, R)) ||
                 (st = ensure_dlam(h, R)))

@@ -1,8 +1,9 @@
-"""The direct selection (small batches, one launch) against the ordering
-pipeline on the same handle: every output bit for bit, over pool sizes around
-the 64-decode groups and the column chunks, one and four wavefronts per
-request, factors computed in place and read from the derived rows.  An
-explicit run length asks for the pipeline."""
+"""The selections without ordering -- direct (small batches, one launch) and
+bounded (the others) -- against the ordering pipeline on the same handle:
+every output bit for bit, over pool sizes around the 64-decode groups and the
+column chunks, one and four wavefronts per request, factors computed in place
+and read from the derived rows.  An explicit run length asks for the
+pipeline."""
 import numpy as np
 import pytest
 
@@ -65,6 +66,83 @@ def test_direct_equals_pipeline(D, R):
             netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_RUN_LEN, 0)
             print("[direct] D", D, "R", R, "bt", bt, "k", k, flush=True)
             assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+        sel.close()
+
+
+def _grown(rng, req, cache, P, bt):
+    """The batch with an invalid request, requests of 2^24 tokens and more, runs
+    that one decode alone holds (and a hash 0 in one), and a run longer than 64
+    blocks of a decode's private ones."""
+    runs = [req["hashes"][int(req["hash_off"][r]):int(req["hash_off"][r + 1])] for r in range(len(req["prefill"]))]
+    length, pre = list(req["len_tokens"]), list(req["prefill"])
+    off = cache["hash_off"].astype(np.int64)
+    for _ in range(24):
+        d = int(rng.integers(len(off) - 1))
+        own = cache["hashes"][off[d]:off[d + 1]]
+        a = int(rng.integers(max(1, len(own) - 200)))
+        run = own[a:a + int(rng.integers(1, 200))].copy()
+        if rng.random() < 0.3:
+            run[len(run) // 2] = 0
+        runs.append(run)
+        length.append(len(run) * bt + int(rng.integers(bt)))
+        pre.append(int(rng.integers(P)))
+    for x in (1 << 24, (1 << 24) - 1, (1 << 24) + 77):
+        n = x // bt
+        run = rng.integers(1, 1 << 63, n, dtype=np.uint64)
+        run[:7] = runs[0][:7] if len(runs[0]) >= 7 else run[:7]
+        runs.append(run)
+        length.append(x)
+        pre.append(int(rng.integers(P)))
+    pre[len(pre) // 2] = 1 << 20
+    n = np.array([len(r) for r in runs])
+    return dict(prefill=np.array(pre, np.uint32), len_tokens=np.array(length, np.uint32),
+                hash_off=np.concatenate([[0], np.cumsum(n)]).astype(np.uint64), hashes=np.concatenate(runs))
+
+
+@pytest.mark.parametrize("D", [1, 48, 64, 65, 130, 768, 1602, 3072, 4096])
+@pytest.mark.parametrize("mem,bt,routes", [((20, 200), 512, False), ((1, 30), 64, False), ((2, 200), 512, True)])
+def test_bounded_equals_pipeline(D, mem, bt, routes):
+    from paper_2606_03910_amd import netkv
+    R = (1 << 14) // (-(-D // 64)) + 41
+    snap, cache, req = _inputs(D, R, D, mem=mem, bt=bt)
+    P = snap["n_prefill"]
+    rng = np.random.default_rng(D)
+    req = _grown(rng, req, cache, P, bt)
+    sel = _handle(netkv, snap, cache)
+    if routes:
+        n = P * D
+        sel.load_routes(rng.integers(1, 4, n), rng.uniform(0, 0.9, n), rng.integers(0, 2, n), rng.uniform(0, 0.9, n))
+    rd = netkv.requests_to_device(req, sel.device)
+    for k, policy in ((1, 0), (1, 2), (2, 0), (3, 1), (8, 0)):
+        sel.set_policy(policy)
+        got = _bits(netkv, sel.select(rd, k=k))
+        netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_RUN_LEN, 64)
+        want = _bits(netkv, sel.select(rd, k=k))
+        netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_RUN_LEN, 0)
+        print("[bounded] D", D, "R", R, "mem", mem, "bt", bt, "routes", routes, "k", k, flush=True)
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    sel.close()
+
+
+def test_bounded_ties_and_rejects():
+    """Identical decodes (every group survives the bound, ties go to the lowest
+    index) and pools where nothing is feasible."""
+    from paper_2606_03910_amd import netkv
+    D, R = 1602, 700
+    snap, cache, req = _inputs(D, R, 11)
+    P = snap["n_prefill"]
+    snap.update(tier_map=np.full(P * D, 2, np.uint8), util=np.zeros(P * D, np.float32),
+                queue_depth=np.zeros(D, np.uint32), free_mem=np.full(D, 10 ** 12, np.uint64))
+    for m_min in (0, 1 << 62):
+        snap["m_min"] = m_min
+        sel = _handle(netkv, snap, dict(hash_off=np.zeros(D + 1, np.uint64), hashes=np.ones(1, np.uint64)))
+        rd = netkv.requests_to_device(req, sel.device)
+        for k in (1, 3, 8):
+            i, s = _bits(netkv, sel.select(rd, k=k))
+            if m_min:
+                assert np.all(i == -1) and np.all(s == np.float32(np.inf).view(np.uint32))
+            else:
+                assert np.array_equal(i.reshape(R, k), np.tile(np.arange(k), (R, 1)))
         sel.close()
 
 
