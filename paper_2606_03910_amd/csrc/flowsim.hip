@@ -10,9 +10,11 @@
 // rates rise together by the largest amount every link still allows; the
 // flows crossing a link that this fills stop there; repeat.
 //
-// One workgroup runs one instance (a flow set on its links) through all its
-// events; the instances of a call are independent (other congestion draws,
-// other batches).  Inside a workgroup, threads take links and flows in
+// One wavefront runs one instance (a flow set on its links) through all its
+// events with the link state in its registers (flow_bits_kernel), where the
+// instance fits that form; else, or from where it no longer does, one
+// workgroup does (flow_sim_kernel).  The instances of a call are independent (other
+// congestion draws, other batches).  Inside a workgroup, threads take links and flows in
 // strides, and workgroup reductions give the minimum raise, the next event
 // and the counts.  Before the simulation each instance's flows are sorted
 // by arrival time (rocPRIM's segmented radix sort, which only orders work),
@@ -48,6 +50,8 @@ constexpr uint8_t kWaiting = 0, kMoving = 1, kDone = 2;
 // freeze marks of a moving flow within one allocation
 constexpr uint8_t kFree = 0, kFrozen = 1, kJustFrozen = 2;
 
+struct SimSave;
+
 struct SimArgs {
     uint32_t n_links;
     const double *cap;          // [n_inst][n_links]
@@ -67,6 +71,7 @@ struct SimArgs {
     const uint64_t *skey;       // [n_flows] their arrival times as sort keys, in that order
     const uint32_t *bad_off;    // nonzero: flow_off is not a valid partition of the flows
     const uint32_t *order;      // [n_inst] the instance of each workgroup, heaviest first (or null)
+    SimSave *save;              // [n_inst] where flow_bits_kernel left each instance (null: it did not run)
     double *g_rem;
     uint32_t *g_cnt, *g_lk;
     uint8_t *g_sat;
@@ -153,6 +158,13 @@ struct SimCtl {
     uint32_t stall;        // an iteration bound was reached
 };
 constexpr uint32_t kRunWave = 0, kRunGroup = 1, kRunEnd = 2;
+
+// What flow_bits_kernel hands to flow_sim_kernel.
+struct SimSave {
+    SimCtl ctl;
+    uint32_t status;   // kTodo, kResume (from ctl) or kFinished
+};
+constexpr uint32_t kTodo = 0, kResume = 1, kFinished = 2;
 
 // The instance's passes while at most one wavefront of flows moves, run by
 // wavefront 0 alone.  Lane i keeps moving flow i (its offset, path and
@@ -401,6 +413,484 @@ __device__ void wave_run(const SimArgs &a, uint64_t f0, uint64_t nf, const uint3
     }
 }
 
+// Least value over the wavefront of non-negative doubles (infinity among
+// them, no NaN, no -0), whose bits order as unsigned integers: the least high
+// word, then the low word of its only holder, or the least of several.
+__device__ inline uint32_t wave_min_u32(uint32_t v) {
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0xB1, 0xF, 0xF, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x4E, 0xF, 0xF, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x124, 0xF, 0xF, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x128, 0xF, 0xF, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xA, 0xF, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xC, 0xF, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+__device__ inline double wave_min_pos(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t vh = (uint32_t)(b >> 32), vl = (uint32_t)b;
+    const uint32_t hi = wave_min_u32(vh);
+    const lmask at = ballot(vh == hi);
+    uint32_t lo;
+    if ((at & (at - 1)) == 0) lo = (uint32_t)__builtin_amdgcn_readlane((int)vl, (int)__builtin_ctzll(at));
+    else lo = wave_min_u32(vh == hi ? vl : 0xFFFFFFFFu);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+__device__ inline uint64_t read_lane_u64(uint64_t v, uint32_t l) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)l);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// a / c, correctly rounded, for an integer c of 1 .. 512, y = 1 / c correctly
+// rounded and a = 0 or a >= kTinyCap: two steps of Markstein's correction
+// (the first makes the quotient faithful, the second correctly rounded; the
+// residuals are exact while nothing underflows).  5 operations in a chain
+// where the general division takes about 12.
+constexpr double kTinyCap = 0x1p-900;
+
+__device__ inline double div_count(double a, double c, double y) {
+    double q = a * y;
+    double r = __builtin_fma(-c, q, a);
+    q = __builtin_fma(r, y, q);
+    r = __builtin_fma(-c, q, a);
+    return __builtin_fma(r, y, q);
+}
+
+// An instance run by one wavefront with its link state in registers.  Lane l
+// keeps links l, l + 64, ... of the links its flows use: capacity left, count
+// of flows still rising, and M words with a bit per flow crossing the link
+// (up to 64 M flows in progress, flow i in lane i % 64).  A filling round is
+// then a chain of register operations only: shares, their least, the filled
+// links (ballots), the flows that stop (the OR of their links' words, in
+// scalar registers) and each count less the bits it shares with them.  The
+// general passes below go through LDS instead: each round reads counts and
+// capacities, marks filled links, tests every flow's path and takes the
+// stopped flows off with atomics, with three barriers above 64 flows.  The
+// round is bound by the latency of that chain, so one wavefront without
+// barriers is the faster form, and the call by its heaviest instance.
+// Between events the words are kept in LDS, where an arrival or a completion
+// changes one bit on each of its links; arrivals are read 64 ahead.
+//
+// Every quantity goes through the operations of the general passes in the
+// same order, so the results are the same bit for bit.  256 instances of
+// 4,096 transfers: 93.5 -> 50.7 ms; of one instance alone, 79,277 rounds with
+// 113 flows on average, 97 -> 44 ms, and 33,886 rounds with 7, 49 -> 22 ms.
+// (Words and flow sets in scalar registers throughout, with 64-bit floating
+// minima, spilled 236 of them and took 1.2 us a round against 0.45.)
+//
+// Instances outside its form (a flow over more than kBitPath links or twice
+// over one, more than 64 K links in use, capacities below kTinyCap, invalid
+// input) are left to flow_sim_kernel, as is the rest of an instance once more
+// than 64 M flows are in progress.
+constexpr uint32_t kBitPath = 8;
+constexpr uint32_t kBitLinks = 5, kBitWords = 8;   // K and M
+
+constexpr uint32_t kBitRow = kBitWords + 2;   // words per link in LDS (rows of neighbouring links in different banks)
+
+// Progressive filling of the na flows in progress over NK x 64 links with NW
+// words each; rt takes the flows' rates, the result is the number of rounds.
+// Comparisons of non-negative doubles are made on their words (the 64-bit
+// minima and comparisons run at a fraction of the 32-bit ones' rate).
+template <int NK, int NW, int K, int M>
+__device__ inline uint32_t fill_rounds(const uint64_t *mk, const double *recip, const double (&cp)[K], double (&rt)[M],
+                                       uint32_t na, uint32_t lane, bool &stall) {
+#pragma clang fp contract(off)
+    uint64_t m[NK][NW];   // the flows still rising on each link
+    uint32_t c[NK];
+    double rem[NK], cd[NK], y[NK];
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        c[k] = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            m[k][w] = mk[(k * kWave + lane) * kBitRow + w];
+            c[k] += (uint32_t)__builtin_popcountll(m[k][w]);
+        }
+        rem[k] = cp[k];
+        cd[k] = (double)c[k];
+        y[k] = recip[c[k]];
+    }
+    auto high = [](double v) { return (uint32_t)((uint64_t)__double_as_longlong(v) >> 32); };
+    auto low = [](double v) { return (uint32_t)__double_as_longlong(v); };
+    constexpr uint32_t kInfHigh = 0x7FF00000u, kTinyHigh = 0x07B00000u;   // of kTinyCap
+    double level = 0.0;
+    uint32_t rising = na, rd = 0;
+    for (;;) {
+        // the largest equal raise every link still allows
+        uint32_t hi[NK], lo[NK], least = kInfHigh;
+        bool tiny = false;
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            const double q = div_count(rem[k], cd[k], y[k]);
+            hi[k] = c[k] ? high(q) : kInfHigh;
+            lo[k] = low(q);
+            tiny |= c[k] != 0 && high(rem[k]) < kTinyHigh;
+            least = min(least, hi[k]);
+        }
+        if (__any(tiny)) {   // what is left of a capacity may be too small for div_count's residuals
+            least = kInfHigh;
+#pragma unroll
+            for (int k = 0; k < NK; ++k) {
+                if (c[k]) {
+                    const double q = rem[k] / cd[k];
+                    hi[k] = high(q);
+                    lo[k] = low(q);
+                    least = min(least, hi[k]);
+                }
+            }
+        }
+        const uint32_t ih = wave_min_u32(least);
+        if (ih >= kInfHigh || rd > na) {   // (never: every rising flow crosses a link, and every round stops one)
+            stall = true;
+            break;
+        }
+        lmask full[NK];
+        uint32_t n_full = 0, il = 0xFFFFFFFFu;
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            full[k] = ballot(hi[k] == ih);
+            n_full += (uint32_t)__builtin_popcountll(full[k]);
+        }
+        if (n_full == 1) {
+#pragma unroll
+            for (int k = 0; k < NK; ++k)
+                if (full[k]) il = (uint32_t)__builtin_amdgcn_readlane((int)lo[k], (int)__builtin_ctzll(full[k]));
+        } else {
+            uint32_t l = 0xFFFFFFFFu;
+#pragma unroll
+            for (int k = 0; k < NK; ++k) l = hi[k] == ih ? min(l, lo[k]) : l;
+            il = wave_min_u32(l);
+#pragma unroll
+            for (int k = 0; k < NK; ++k) full[k] &= ballot(lo[k] == il);
+        }
+        const double inc = __longlong_as_double((long long)(((uint64_t)ih << 32) | il));
+        level = level + inc;
+        // the flows that cross a filled link stop here
+        lmask stop[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) stop[w] = 0;
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            lmask f = full[k];
+            while (f) {
+                const uint32_t ln = (uint32_t)__builtin_ctzll(f);
+#pragma unroll
+                for (int w = 0; w < NW; ++w) stop[w] |= read_lane_u64(m[k][w], ln);
+                f &= f - 1;
+            }
+        }
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            rt[w] = __builtin_amdgcn_inverse_ballot_w64(stop[w]) ? level : rt[w];
+            rising -= (uint32_t)__builtin_popcountll(stop[w]);
+        }
+        ++rd;
+        if (rising == 0) break;
+        // the capacity left, and the flows still rising, on each link
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            const double used = inc * cd[k];
+            const double lf = rem[k] - used;
+            rem[k] = (int32_t)high(lf) < 0 ? 0.0 : lf;
+            c[k] = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                m[k][w] &= ~stop[w];
+                c[k] += (uint32_t)__builtin_popcountll(m[k][w]);
+            }
+            cd[k] = (double)c[k];
+            y[k] = recip[c[k]];
+        }
+    }
+    return rd;
+}
+
+template <int K, int M>
+__global__ __launch_bounds__(kWave) void flow_bits_kernel(SimArgs a) {
+#pragma clang fp contract(off)
+    __shared__ __align__(16) uint64_t mk[K * kWave * kBitRow];   // the flows of each link
+    __shared__ uint32_t fpath[M * kWave][kBitPath / 2];   // links of the flow in each place, 16 bits each
+    __shared__ double recip[M * kWave + 1];
+    extern __shared__ uint16_t cid[];            // [L] a link's number among those in use
+    const uint32_t lane = threadIdx.x;
+    const uint32_t inst = a.order ? a.order[blockIdx.x] : blockIdx.x;
+    const uint32_t L = a.n_links;
+    const uint64_t f0 = a.flow_off[inst], f1 = a.flow_off[inst + 1];
+    const double *cap = a.cap + (uint64_t)inst * L;
+    SimSave &save = a.save[inst];
+    if (lane == 0) save.status = kTodo;
+    if (*a.bad_off != 0 || !(f0 < f1 && f1 <= a.n_flows)) return;
+    const uint64_t nf = f1 - f0;
+    bool bad = false;
+    for (uint32_t l = lane; l < L; l += kWave) {
+        const double c = cap[l];
+        if (!(c >= kTinyCap) || !isfinite(c)) bad = true;
+        cid[l] = 0;
+    }
+    wave_phase();
+    for (uint64_t f = f0 + lane; f < f1; f += kWave) {
+        const uint64_t p0 = a.path_off[f], p1 = a.path_off[f + 1];
+        const double b = a.bytes[f], s = a.start[f];
+        if (!(b >= 0.0) || !isfinite(b) || !isfinite(s)) bad = true;
+        if (!(p1 > p0) || p1 > a.n_path || p1 - p0 > kBitPath) {
+            bad = true;
+        } else {
+            const uint32_t n = (uint32_t)(p1 - p0);
+            uint32_t x[kBitPath];
+#pragma unroll
+            for (uint32_t u = 0; u < kBitPath; ++u) x[u] = u < n ? a.path[p0 + u] : 0xFFFFFFFFu - u;
+#pragma unroll
+            for (uint32_t u = 0; u < kBitPath; ++u) {
+#pragma unroll
+                for (uint32_t v = 0; v < u; ++v) bad |= x[u] == x[v];
+                if (u < n) {
+                    if (x[u] < L) cid[x[u]] = 1;
+                    else bad = true;
+                }
+            }
+        }
+        a.state[f] = kWaiting;
+    }
+    if (__any(bad)) return;
+    wave_phase();
+    // number the links in use; their capacities through mk
+    uint32_t nu = 0;
+    double *stage = (double *)mk;
+    for (uint32_t l0 = 0; l0 < L; l0 += kWave) {
+        const uint32_t l = l0 + lane;
+        const bool use = l < L && cid[l] != 0;
+        const lmask b = ballot(use);
+        const uint32_t id = nu + below(b);
+        if (use) {
+            cid[l] = (uint16_t)id;
+            if (id < K * kWave) stage[id] = cap[l];
+        }
+        nu += (uint32_t)__builtin_popcountll(b);
+    }
+    if (nu > K * kWave) return;
+    const uint32_t nk = (nu + kWave - 1) / kWave;
+    wave_phase();
+    double cp[K];
+#pragma unroll
+    for (uint32_t k = 0; k < K; ++k) cp[k] = k * kWave + lane < nu ? stage[k * kWave + lane] : 1.0;
+    wave_phase();
+    for (uint32_t i = lane; i < K * kWave * kBitRow; i += kWave) mk[i] = 0;
+    for (uint32_t i = lane; i <= M * kWave; i += kWave) recip[i] = i ? 1.0 / (double)i : 0.0;
+    wave_phase();
+
+    // the flows in progress: flow of lane i and word w in place 64 w + i
+    lmask occ[M];
+    uint32_t o[M];
+    double rm[M], rt[M];
+#pragma unroll
+    for (uint32_t w = 0; w < M; ++w) {
+        occ[w] = 0;
+        o[w] = 0;
+        rm[w] = 0.0;
+        rt[w] = 1.0;
+    }
+    uint32_t na = 0;
+    // arrivals wb .. wb + 63 in arrival order, one per lane
+    uint64_t wb = 0;
+    uint32_t ao = 0, apk[kBitPath / 2];
+    double at = INFINITY, ab = 0.0;
+    auto window = [&]() {
+        const uint64_t q = wb + lane;
+        at = INFINITY;
+        ao = 0;
+        ab = 0.0;
+#pragma unroll
+        for (uint32_t u = 0; u < kBitPath / 2; ++u) apk[u] = 0xFFFFFFFFu;
+        if (q < nf) {
+            at = key_time(a.skey[f0 + q]);
+            ao = a.arr[f0 + q];
+            const uint64_t f = f0 + ao;
+            ab = a.bytes[f] + 0.0;   // (-0 becomes 0: times are compared as integers)
+            const uint64_t p0 = a.path_off[f];
+            const uint32_t n = (uint32_t)(a.path_off[f + 1] - p0);
+            uint32_t x[kBitPath];
+#pragma unroll
+            for (uint32_t u = 0; u < kBitPath; ++u) x[u] = u < n ? (uint32_t)cid[a.path[p0 + u]] : 0xFFFFu;
+#pragma unroll
+            for (uint32_t u = 0; u < kBitPath / 2; ++u) apk[u] = x[2 * u] | (x[2 * u + 1] << 16);
+        }
+    };
+    window();
+    uint64_t ap = 0, left = nf, pass = 0, events = 0, rounds = 0, moving = 0;
+    double t = __longlong_as_double((long long)read_lane_u64((uint64_t)__double_as_longlong(at), 0)), nx = t;
+    bool over = false, stall = false;
+    for (;; ++pass) {
+        if (left == 0) break;
+        if (pass > 2 * nf + 4) {
+            stall = true;
+            break;
+        }
+        while (ap < nf && nx <= t) {
+            if (na == M * kWave) {
+                over = true;
+                break;
+            }
+            // arrival ap into the lowest free place, its bit onto its links
+            const uint32_t j = (uint32_t)(ap - wb);
+            const uint32_t jo = (uint32_t)__builtin_amdgcn_readlane((int)ao, (int)j);
+            const double jb = __longlong_as_double((long long)read_lane_u64((uint64_t)__double_as_longlong(ab), j));
+            uint32_t pk[kBitPath / 2];
+#pragma unroll
+            for (uint32_t u = 0; u < kBitPath / 2; ++u) pk[u] = (uint32_t)__builtin_amdgcn_readlane((int)apk[u], (int)j);
+            uint32_t pw = 0, pl = 0;
+            bool placed = false;
+#pragma unroll
+            for (uint32_t w = 0; w < M; ++w) {
+                if (!placed && ~occ[w]) {
+                    placed = true;
+                    pw = w;
+                    pl = (uint32_t)__builtin_ctzll(~occ[w]);
+                    occ[w] |= 1ull << pl;
+                    if (lane == pl) {
+                        o[w] = jo;
+                        rm[w] = jb;
+                    }
+                }
+            }
+            uint32_t mine = pk[0];
+#pragma unroll
+            for (uint32_t u = 1; u < kBitPath / 2; ++u) mine = lane / 2 == u ? pk[u] : mine;
+            if (lane < kBitPath) {
+                const uint32_t l = (mine >> (16 * (lane & 1u))) & 0xFFFFu;
+                if (l != 0xFFFFu) atomicOr((unsigned long long *)&mk[l * kBitRow + pw], 1ull << pl);
+                if ((lane & 1u) == 0) fpath[pw * kWave + pl][lane / 2] = mine;
+            }
+            ++na;
+            ++ap;
+            if (ap - wb == kWave) {
+                wb = ap;
+                window();
+            }
+            nx = __longlong_as_double((long long)read_lane_u64((uint64_t)__double_as_longlong(at), (uint32_t)(ap - wb)));
+        }
+        if (over) break;
+        if (na == 0) {
+            t = nx;
+            continue;
+        }
+        wave_phase();
+        uint32_t nw = 0;   // words in use
+#pragma unroll
+        for (uint32_t w = 0; w < M; ++w) nw = occ[w] ? w + 1 : nw;
+        uint32_t rd;
+        if (nk <= 2) {
+            rd = nw == 1 ? fill_rounds<2, 1>(mk, recip, cp, rt, na, lane, stall)
+               : nw == 2 ? fill_rounds<2, 2>(mk, recip, cp, rt, na, lane, stall)
+               : nw <= 4 ? fill_rounds<2, 4>(mk, recip, cp, rt, na, lane, stall)
+                         : fill_rounds<2, M>(mk, recip, cp, rt, na, lane, stall);
+        } else {
+            rd = nw <= 2 ? fill_rounds<K, 2>(mk, recip, cp, rt, na, lane, stall)
+               : nw <= 4 ? fill_rounds<K, 4>(mk, recip, cp, rt, na, lane, stall)
+                         : fill_rounds<K, M>(mk, recip, cp, rt, na, lane, stall);
+        }
+        rounds += rd;
+        if (stall) break;
+        // the next event: the earliest completion, or the next arrival
+        uint64_t q[M], first = 0x7FF0000000000000ull;   // bits of the times, which are not negative
+#pragma unroll
+        for (uint32_t w = 0; w < M; ++w) {
+            q[w] = ~0ull;
+            if (w < nw) {
+                if (__builtin_amdgcn_inverse_ballot_w64(occ[w])) q[w] = (uint64_t)__double_as_longlong(rm[w] / rt[w]);
+                first = q[w] < first ? q[w] : first;
+            }
+        }
+        ++events;
+        moving += na;
+        const double dtc = wave_min_pos(__longlong_as_double((long long)first));
+        const uint64_t dtb = (uint64_t)__double_as_longlong(dtc);
+        if (dtc <= nx - t) {
+            const double tf = t + dtc;
+#pragma unroll
+            for (uint32_t w = 0; w < M; ++w)
+                if (w < nw) {
+                    const bool has = __builtin_amdgcn_inverse_ballot_w64(occ[w]);
+                    const bool done = q[w] == dtb;
+                    if (done) {
+                        a.finish[f0 + o[w]] = tf;
+                        a.state[f0 + o[w]] = kDone;
+                    } else if (has) {
+                        const double moved = rt[w] * dtc;
+                        const double r = rm[w] - moved;
+                        rm[w] = r > 0.0 ? r : 0.0;
+                    }
+                    lmask gone = ballot(done);
+                    occ[w] &= ~gone;
+                    left -= (uint64_t)__builtin_popcountll(gone);
+                    na -= (uint32_t)__builtin_popcountll(gone);
+                    while (gone) {   // their bits off their links
+                        const uint32_t s = (uint32_t)__builtin_ctzll(gone);
+                        if (lane < kBitPath) {
+                            const uint32_t l = (fpath[w * kWave + s][lane / 2] >> (16 * (lane & 1u))) & 0xFFFFu;
+                            if (l != 0xFFFFu) atomicAnd((unsigned long long *)&mk[l * kBitRow + w], ~(1ull << s));
+                        }
+                        gone &= gone - 1;
+                    }
+                }
+            t = tf;
+        } else {
+            const double dt = nx - t;
+#pragma unroll
+            for (uint32_t w = 0; w < M; ++w)
+                if (w < nw) {
+                    const double moved = rt[w] * dt;
+                    const double r = rm[w] - moved;
+                    rm[w] = r > 0.0 ? r : 0.0;   // (places without a flow: not read)
+                }
+            t = nx;
+        }
+        wave_phase();
+    }
+    if (over) {   // the flows in progress into the device list
+        uint32_t n = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < M; ++w) {
+            if ((occ[w] >> lane) & 1ull) {
+                const uint32_t i = n + below(occ[w]);
+                a.mlist[f0 + i] = o[w];
+                a.remaining[f0 + o[w]] = rm[w];
+                a.state[f0 + o[w]] = kMoving;
+            }
+            n += (uint32_t)__builtin_popcountll(occ[w]);
+        }
+    }
+    // flows that have not arrived keep their size where the passes read it
+    if (over)
+        for (uint64_t i = ap + lane; i < nf; i += kWave) {
+            const uint64_t f = f0 + a.arr[f0 + i];
+            a.remaining[f] = a.bytes[f];
+        }
+    if (lane == 0) {
+        SimCtl &s = save.ctl;
+        s.t = t;
+        s.nx = nx;
+        s.ap = ap;
+        s.left = left;
+        s.pass = pass;
+        s.events = events;
+        s.rounds = rounds;
+        s.moving = moving;
+        s.na = na;
+        s.list = 0;
+        s.mode = over ? kRunGroup : kRunEnd;
+        s.resume = 0;
+        s.stall = stall ? 1u : 0u;
+        save.status = over || stall ? kResume : kFinished;
+        if (!over && !stall && a.stats) {
+            a.stats[3ull * inst + 0] = events;
+            a.stats[3ull * inst + 1] = rounds;
+            a.stats[3ull * inst + 2] = moving;
+        }
+    }
+}
+
 // Bytes of the link state an instance keeps in LDS: per link the capacity
 // left and the capacity (fp64), the flow count and the list entry (u32),
 // and the filled mark (u8).
@@ -417,6 +907,8 @@ __global__ __launch_bounds__(kSimThreads) void flow_sim_kernel(SimArgs a) {
     const uint32_t tid = threadIdx.x, lane = tid % 64, w = tid / 64;
     const uint32_t inst = a.order ? a.order[blockIdx.x] : blockIdx.x;
     const uint32_t L = a.n_links;
+    const uint32_t status = a.save ? a.save[inst].status : kTodo;
+    if (status == kFinished) return;
     const uint64_t f0 = a.flow_off[inst], f1 = a.flow_off[inst + 1];
     const double *cap = a.cap + (uint64_t)inst * L;
     double *rem = LDS ? (double *)dyn : a.g_rem + (uint64_t)inst * L;
@@ -452,11 +944,12 @@ __global__ __launch_bounds__(kSimThreads) void flow_sim_kernel(SimArgs a) {
     // not a partition of the flows invalidate every instance of the call)
     const bool range_ok = f0 <= f1 && f1 <= a.n_flows;
     uint32_t bad = range_ok && *a.bad_off == 0 ? 0u : 1u;
-    for (uint32_t l = tid; l < L; l += kSimThreads) {
+    const bool todo = status == kTodo;
+    for (uint32_t l = tid; todo && l < L; l += kSimThreads) {
         const double c = cap[l];
         if (!(c > 0.0) || !isfinite(c)) bad = 1;
     }
-    for (uint64_t f = f0 + tid; range_ok && f < f1; f += kSimThreads) {
+    for (uint64_t f = f0 + tid; todo && range_ok && f < f1; f += kSimThreads) {
         const uint64_t p0 = a.path_off[f], p1 = a.path_off[f + 1];
         if (!(p1 > p0) || p1 > a.n_path) {
             bad = 1;
@@ -483,7 +976,7 @@ __global__ __launch_bounds__(kSimThreads) void flow_sim_kernel(SimArgs a) {
         cnt[l] = 0;
         if (LDS) lcap[l] = cap[l];
     }
-    for (uint64_t f = f0 + tid; f < f1; f += kSimThreads) {
+    for (uint64_t f = f0 + tid; todo && f < f1; f += kSimThreads) {
         a.state[f] = kWaiting;
         a.frz[f] = kFree;
         a.remaining[f] = a.bytes[f];
@@ -503,6 +996,7 @@ __global__ __launch_bounds__(kSimThreads) void flow_sim_kernel(SimArgs a) {
         ctl.mode = nf ? kRunWave : kRunEnd;
         ctl.resume = 0;
         ctl.stall = 0;
+        if (!todo) ctl = a.save[inst].ctl;
     }
     __syncthreads();
     // the wavefront run while few flows move, the workgroup passes while
@@ -988,7 +1482,7 @@ extern "C" netkv_status netkv_flow_sim(netkv_handle h, uint32_t n_inst, uint32_t
         return netkv_internal_fail(h, NETKV_EDEVICE, "launch-order sort size query failed");
     }
     const uint64_t per_flow = align256(8 * n_flows) * 3 + align256(n_flows) * 2 + align256(4 * n_flows) * 3;
-    const uint64_t per_inst = 6 * align256(4ull * n_inst) + 256 + align256(sort_bytes) + align256(isort_bytes);
+    const uint64_t per_inst = 6 * align256(4ull * n_inst) + align256(sizeof(SimSave) * (uint64_t)n_inst) + 256 + align256(sort_bytes) + align256(isort_bytes);
     const uint64_t per_link = lds ? 0 : align256(8ull * n_inst * n_links) + 2 * align256(4ull * n_inst * n_links) +
                                             align256((uint64_t)n_inst * n_links);
     void *buf = nullptr;
@@ -1048,6 +1542,8 @@ extern "C" netkv_status netkv_flow_sim(netkv_handle h, uint32_t n_inst, uint32_t
         p += align256(4ull * n_inst);
         void *isort_tmp = p;
         p += align256(isort_bytes);
+        SimSave *save = (SimSave *)p;
+        p += align256(sizeof(SimSave) * (uint64_t)n_inst);
         if (!lds) {
             a.g_rem = (double *)p;
             p += align256(8ull * n_inst * n_links);
@@ -1073,6 +1569,11 @@ extern "C" netkv_status netkv_flow_sim(netkv_handle h, uint32_t n_inst, uint32_t
                                               order, n_inst, 0, 32, s);
                 a.order = order;
             }
+        }
+        if (e == hipSuccess && lds && n_flows) {
+            a.save = save;
+            hipLaunchKernelGGL((flow_bits_kernel<kBitLinks, kBitWords>), dim3(n_inst), dim3(kWave),
+                               (2 * n_links + 7) / 8 * 8, s, a);
         }
         if (e == hipSuccess && lds)
             hipLaunchKernelGGL(flow_sim_kernel<true>, dim3(n_inst), dim3(kSimThreads), lds_link_bytes(n_links), s, a);

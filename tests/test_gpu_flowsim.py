@@ -264,3 +264,49 @@ def test_bursts_cross_the_wavefront_and_workgroup_sizes(nk):
     assert (ev[:, 2] / ev[:, 0] > 64).all(), ev
     _check_against_oracle(insts, fin, ev, arr)
     sel.close()
+
+
+@pytest.mark.parametrize("form", ["places", "links", "paths", "scale"])
+def test_limits_of_the_register_form(nk, form):
+    """The edges of the form that keeps an instance's links in one
+    wavefront's registers, on both sides of each: 64 flows per word and 512
+    in all in progress (one more than that hands the instance over with 512
+    flows moving and arrivals still due), 320 links in use, paths of 8
+    links and no link twice, capacities down to 2^-900, and shares of widely
+    different sizes.  Finish times and counts against the oracle bit for
+    bit."""
+    _say("flow sim register form", form)
+    rng = np.random.default_rng(23)
+    L = 400
+
+    def inst(n, links, plen, start, scale=1.0, spread=1.0):
+        cap = scale * 10.0 ** rng.uniform(0.0, spread, L)
+        paths = [list(rng.choice(links, rng.integers(1, plen + 1), replace=False)) for _ in range(n)]
+        return _flows(cap, paths, scale * rng.uniform(0.1, 9.0, n), start(n))
+
+    burst = lambda n: np.zeros(n)
+    spread = lambda n: rng.uniform(0.0, 40.0, n)
+    few = np.arange(40)
+    if form == "places":
+        insts = [inst(n, few, 4, burst) for n in (1, 63, 64, 65, 511, 512, 513)]
+        # 500 at once, then more while most still move, some together
+        late = lambda n: np.concatenate([np.zeros(500), np.repeat(rng.uniform(0.0, 0.5, (n - 500) // 4), 4)])
+        insts += [inst(700, few, 4, late), inst(300, few, 4, spread)]
+    elif form == "links":
+        insts = []
+        for used in (1, 64, 65, 319, 320, 321, 400):
+            n = max(150, used)
+            ids = rng.permutation(np.resize(np.arange(used), n))   # every link in use at least once
+            paths = [[int(l)] if i % 2 else sorted({int(l), int(ids[i - 1])}) for i, l in enumerate(ids)]
+            insts.append(_flows(rng.uniform(1.0, 9.0, L), paths, rng.uniform(0.1, 9.0, n), spread(n)))
+    elif form == "paths":
+        twice = _flows(np.linspace(1.0, 3.0, L), [[0, 1, 0], [1, 2], [0]] * 5, rng.uniform(1.0, 4.0, 15), spread(15))
+        insts = [inst(90, few, 8, spread), inst(90, few, 9, spread), twice]
+    else:
+        insts = [inst(90, few, 4, spread, scale=s, spread=d) for s, d in
+                 ((1e12, 1.0), (1e-250, 1.0), (2.0 ** -900, 0.0), (1e-271, 1.0), (1.0, 60.0), (1e290, 1.0))]
+    sel = nk.Selector(0)
+    fin, ev, arr = _run(nk, sel, insts)
+    sel.sync_errors()
+    _check_against_oracle(insts, fin, ev, arr)
+    sel.close()
