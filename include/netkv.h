@@ -127,8 +127,8 @@ netkv_status netkv_congestion_get(netkv_handle h, float *out, void *stream);
  * for each hash its holders -- one decode, or a bitmap over the decodes
  * (8 * ceil(ceil(n_decode / 64) / 12) * 12 bytes per hash held by two or more) -- so
  * that one lookup answers a membership test on every decode at once.
- * Synchronous; needs about 28 bytes of temporary device memory per
- * resident hash while building.  EINVAL: bad CSR, hash 0, lf out of range,
+ * Synchronous; needs about 28 bytes of device memory per resident hash
+ * while building (up to 2 GiB of it stay with the handle for the next load).  EINVAL: bad CSR, hash 0, lf out of range,
  * D different from a loaded snapshot; ECAPACITY: 2^31 or more resident
  * hashes, a set of more than 2^31 slots, or one that could not be built
  * even at four times the planned buckets; ENOMEM: out of device memory. */

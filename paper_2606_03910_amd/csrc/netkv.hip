@@ -51,7 +51,7 @@
 //                         one workgroup per prefill instance, from the
 //                         leader rows.
 //   selection_bytes_kernel -- the selections' transfer sizes (Eq. (2)).
-//   owner / classify / index_insert / index_value -- build the holder index.
+//   pair / parts / dedupe / build kernels -- build the holder index.
 // The flow-level transfer simulation is in flowsim.hip.
 //   commit kernels     -- between-batch counter / queue / memory update.
 #include <hip/hip_runtime.h>
@@ -77,6 +77,7 @@ constexpr int kWavesPerBlock = 4;
 constexpr uint32_t kXcds = 8;   // accelerator complex dies of an MI355X, each with its own L2
 constexpr int kBlock = kWave * kWavesPerBlock;
 constexpr uint64_t kGolden = 0x9E3779B97F4A7C15ull;
+constexpr uint64_t kGoldenInv = 0xF1DE83E19937733Dull;   // kGolden * kGoldenInv = 1 mod 2^64
 constexpr uint64_t kMix64 = 0xBF58476D1CE4E5B9ull;
 constexpr uint64_t kEmptyKey = ~0ull; // empty top-k entry (sorts last)
 // bytes of the static scratch array of the no-allocation selection (per device)
@@ -156,15 +157,26 @@ struct PairOut {
     float *score;       // [R][D]
 };
 
+// The mixed value of a hash, a multiplicative (Fibonacci) hash of the whole key
+// whose top bits serve as an index, and its inverse; 0 stays 0.
+__host__ __device__ inline uint64_t mix_hash(uint64_t h) { return h * kGolden; }
+__host__ __device__ inline uint64_t unmix_hash(uint64_t x) { return x * kGoldenInv; }
+
 // The two candidate buckets of hash h in a set of 2^b buckets (shift =
-// 64 - b): the top b bits of two 64-bit multiplicative hashes of the whole
-// key (Fibonacci hashing, and the multiplier of splitmix64 after an
-// xor-shift), the second xored onto the first with its low bit set, so the
-// two buckets always differ.  Both use all 64 bits, so keys that agree in
-// part of their bits still get independent bucket pairs.
+// 64 - b): the top b bits of its mixed value, and a bucket of the same aligned
+// block of 2^11, never the same one, chosen by the top bits of a second
+// multiplicative hash (the multiplier of splitmix64 after an xor-shift).
+// Both use all 64 bits, so keys that agree in part of their bits still get
+// independent pairs.  A pair lies within 32 KiB, so that a workgroup can
+// build a block of the set in LDS.  (A chain of two multiplications, with its
+// temporaries, in the place of these two cost the kernels that look hashes up
+// beside other work more than the lookups: the sequential form's 239 -> 353
+// us, a batch of 4,096 16 -> 21 us.)
+constexpr uint32_t kBlockLog2 = 11;
 __host__ __device__ inline void buckets_of(uint64_t h, uint32_t shift, uint32_t &b1, uint32_t &b2) {
-    b1 = (uint32_t)((h * kGolden) >> shift);
-    b2 = b1 ^ ((uint32_t)(((h ^ (h >> 31)) * kMix64) >> shift) | 1u);
+    b1 = (uint32_t)(mix_hash(h) >> shift);
+    const uint32_t in_block = shift > 64 - kBlockLog2 ? shift : 64 - kBlockLog2;
+    b2 = b1 ^ ((uint32_t)(((h ^ (h >> 31)) * kMix64) >> in_block) | 1u);
 }
 
 // Row pitch (elements) of the per-(p, d) float2 rows: D rounded up to whole
@@ -2648,78 +2660,148 @@ __global__ __launch_bounds__(256) void tier_inv_kernel(Snap s, Bw64 bw, const fl
 
 // ------------------------------------------------------------------ table build
 
-// Sets *flag when the resident hashes hold the reserved value 0.
-__global__ void count_zero_kernel(const uint64_t *__restrict__ h, uint64_t n, uint32_t *__restrict__ flag) {
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    bool z = false;
-    for (; i < n; i += stride) z |= h[i] == 0;
-    if (__any(z) && (threadIdx.x % kWave) == 0) atomicOr(flag, 1u);
-}
-
 // ---- holder index build (once per cache load)
 //
-// The (hash, decode) pairs of all resident sets are sorted by hash (rocPRIM
-// radix sort), so the holders of one hash form a run.  The first element of
-// each run ("head") stands for the run: classify_kernel counts distinct
-// hashes and those with two or more holders, index_insert_kernel puts every
-// distinct hash into the cuckoo set, and index_value_kernel finds each one's
-// slot and writes its holder value (for several holders, a fresh bitmap row
-// with their bits set).
+// The (hash, decode) pairs of all resident sets are partitioned by the top
+// bits of the mixed hash (rocPRIM radix sort over those bits alone: one or two
+// passes), so that the hashes of a block of buckets lie together, and the rest
+// happens in LDS, one workgroup per part or block, with coalesced reads and
+// writes of memory:
+//   pair_kernel   -- mixed hash and decode of every resident hash;
+//   parts_kernel  -- where each part starts;
+//   dedupe_kernel -- a part's distinct hashes, each with one holder and whether
+//                    it has more, and their counts (which size the set);
+//   build_kernel  -- a block's cuckoo set, its values, the bitmap rows and the
+//                    shared index.
+// A whole load of 50.3 M pairs of 768 decodes takes 3.3 ms (build 1.24, dedupe
+// 0.77, the sort 0.55, pairs 0.17, parts 0.12 and the allocations that are
+// left), against 17.0 ms with a sort over all 64 bits, one thread per distinct
+// hash walking its run of up to 768 holders, compare-and-swaps on the set in
+// memory, and all buffers allocated anew.
 
-// Decode of every resident hash of the CSR (binary search of the offsets).
-__global__ void owner_kernel(const uint64_t *__restrict__ off, uint32_t D, uint64_t first, uint64_t n,
-                             uint32_t *__restrict__ owner) {
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) {
-        const uint64_t x = first + i;
-        uint32_t lo = 0, hi = D;   // largest d with off[d] <= x
-        while (hi - lo > 1) {
-            const uint32_t mid = lo + (hi - lo) / 2;
-            if (off[mid] <= x) lo = mid;
-            else hi = mid;
+// The largest d with off[d] <= x.
+__device__ inline uint32_t owner_of(const uint64_t *__restrict__ off, uint32_t D, uint64_t x) {
+    uint32_t lo = 0, hi = D;
+    while (hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (off[mid] <= x) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// The pairs' sort keys: mixed values with their top `bits` bits, the part,
+// rotated to the low end (the sort goes over the low bits).
+__device__ inline uint64_t part_key(uint64_t x, uint32_t bits) { return (x << bits) | (x >> 1 >> (63 - bits)); }
+__device__ inline uint64_t part_value(uint64_t y, uint32_t bits) { return (y >> bits) | (y << 1 << (63 - bits)); }
+
+// Key and decode of every resident hash (binary search of the offsets, once
+// per 512 hashes where those are one decode's); sets *flag when a hash is the
+// reserved 0.
+constexpr uint32_t kPairPer = 8;
+__global__ __launch_bounds__(kBlock) void pair_kernel(const uint64_t *__restrict__ off, uint32_t D, uint64_t first,
+                                                      uint64_t n, const uint64_t *hashes, uint32_t bits,
+                                                      uint64_t *key, uint32_t *__restrict__ dec,
+                                                      uint32_t *__restrict__ flag) {
+    const uint32_t lane = threadIdx.x % kWave;
+    const uint64_t i0 = ((uint64_t)blockIdx.x * kWavesPerBlock + wave_index()) * (kWave * kPairPer);
+    if (i0 >= n) return;
+    const uint64_t last = n - i0 < kWave * kPairPer ? n - 1 : i0 + kWave * kPairPer - 1;
+    const uint32_t d0 = owner_of(off, D, first + i0), d1 = owner_of(off, D, first + last);
+    bool zero = false;
+#pragma unroll
+    for (uint32_t u = 0; u < kPairPer; ++u) {
+        const uint64_t i = i0 + u * kWave + lane;
+        if (i < n) {
+            const uint64_t h = hashes[i];
+            zero |= h == 0;
+            key[i] = part_key(mix_hash(h), bits);   // (may be the same array)
+            dec[i] = d0 == d1 ? d0 : owner_of(off, D, first + i);
         }
-        owner[i] = lo;
     }
+    if (__any(zero) && lane == 0) atomicOr(flag, 1u);
 }
 
-__device__ inline bool run_head(const uint64_t *__restrict__ key, uint64_t i) {
-    return i == 0 || key[i] != key[i - 1];
+// start[q], q = 0 .. 2^bits: the first pair of part q or a later one.
+__global__ __launch_bounds__(256) void parts_kernel(const uint64_t *__restrict__ key, uint64_t n, uint32_t bits,
+                                                    uint32_t *__restrict__ start) {
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i > n) return;
+    auto part = [&](uint64_t x) { return (uint32_t)key[x] & ((1u << bits) - 1u); };
+    const uint32_t lo = i == 0 ? 0u : part(i - 1) + 1u, hi = i == n ? 1u << bits : part(i);
+    for (uint32_t q = lo; q <= hi; ++q) start[q] = (uint32_t)i;
 }
 
-// Smallest and largest holder of the run starting at head i; returns the
-// run's end.
-__device__ inline uint64_t run_span(const uint64_t *__restrict__ key, const uint32_t *__restrict__ dec, uint64_t n,
-                                    uint64_t i, uint32_t &dmin, uint32_t &dmax) {
-    dmin = dmax = dec[i];
-    uint64_t e = i + 1;
-    for (; e < n && key[e] == key[i]; ++e) {
-        dmin = min(dmin, dec[e]);
-        dmax = max(dmax, dec[e]);
-    }
-    return e;
-}
+constexpr uint32_t kBlockSlots = 2u << kBlockLog2;   // slots of a block of the set
+constexpr uint32_t kManyHolders = 0x80000000u;   // with the decode of one of them
+constexpr uint32_t kNobody = 0xFFFFFFFFu;
 
-// cnt[0] += distinct hashes, cnt[1] += hashes with two or more holders.
-__global__ __launch_bounds__(256) void classify_kernel(const uint64_t *__restrict__ key,
-                                                       const uint32_t *__restrict__ dec, uint64_t n,
-                                                       unsigned long long *__restrict__ cnt) {
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    uint32_t heads = 0, multi = 0;
-    for (; i < n; i += stride) {
-        if (!run_head(key, i)) continue;
-        uint32_t dmin, dmax;
-        run_span(key, dec, n, i, dmin, dmax);
-        ++heads;
-        multi += dmin != dmax ? 1u : 0u;
+// One workgroup per part: its distinct hashes to (okey, ohold) from the part's
+// start on, count[part] of them; sums of the counts, and of the hashes of
+// several holders, in cnt.  S slots hold the part's hashes at the load factor
+// of the set or less on average.
+template <uint32_t S>
+__global__ __launch_bounds__(1024) void dedupe_kernel(const uint64_t *__restrict__ key,
+                                                      const uint32_t *__restrict__ dec,
+                                                      const uint32_t *__restrict__ start, uint32_t bits,
+                                                      uint64_t *__restrict__ okey,
+                                                      uint32_t *__restrict__ ohold, uint32_t *__restrict__ count,
+                                                      unsigned long long *__restrict__ cnt,
+                                                      uint32_t *__restrict__ flag) {
+    __shared__ unsigned long long lk[S];
+    __shared__ uint32_t lh[S];
+    __shared__ uint32_t n_out, n_many;
+    const uint32_t a = start[blockIdx.x], b = start[blockIdx.x + 1], tid = threadIdx.x;
+    if (a == b) {
+        if (tid == 0) count[blockIdx.x] = 0;
+        return;
     }
-    heads = wave_sum_u32(heads);
-    multi = wave_sum_u32(multi);
-    if ((threadIdx.x % kWave) == 0) {
-        if (heads) atomicAdd(cnt, (unsigned long long)heads);
-        if (multi) atomicAdd(cnt + 1, (unsigned long long)multi);
+    for (uint32_t s = tid; s < S; s += blockDim.x) {
+        lk[s] = 0;
+        lh[s] = kNobody;
+    }
+    if (tid == 0) n_out = n_many = 0;
+    __syncthreads();
+    for (uint32_t i = a + tid; i < b; i += blockDim.x) {
+        const uint64_t y = key[i];
+        const unsigned long long k = part_value(y, bits);
+        const uint32_t d = dec[i];
+        uint32_t s = (uint32_t)(y >> 32) / (0xFFFFFFFFu / S + 1u), probe = 0;   // the top bits after the part's
+        for (; probe < S; ++probe, s = (s + 1) & (S - 1)) {
+            unsigned long long cur = *(volatile unsigned long long *)&lk[s];
+            if (cur == 0) cur = atomicCAS(&lk[s], 0ull, k);
+            if (cur == 0 || cur == k) break;
+        }
+        if (probe == S) {
+            atomicOr(flag, 2u);
+            continue;
+        }
+        uint32_t h = *(volatile uint32_t *)&lh[s];
+        if (h == kNobody) h = atomicCAS(&lh[s], kNobody, d);
+        if (h != kNobody && !(h & kManyHolders) && h != d) atomicOr(&lh[s], kManyHolders);
+    }
+    __syncthreads();
+    for (uint32_t s = tid; s < S; s += blockDim.x) {   // (S is a multiple of the workgroup)
+        const unsigned long long k = lk[s];
+        const lmask out = ballot(k != 0), many = ballot(k != 0 && (lh[s] & kManyHolders));
+        uint32_t base = 0;
+        if (threadIdx.x % kWave == 0) {
+            base = atomicAdd(&n_out, (uint32_t)__builtin_popcountll(out));
+            if (many) atomicAdd(&n_many, (uint32_t)__builtin_popcountll(many));
+        }
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        if (k != 0) {
+            const uint32_t o = a + base + __builtin_amdgcn_mbcnt_hi((uint32_t)(out >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)out, 0u));
+            okey[o] = k;
+            ohold[o] = lh[s];
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        count[blockIdx.x] = n_out;
+        atomicAdd(cnt, (unsigned long long)n_out);
+        if (n_many) atomicAdd(cnt + 1, (unsigned long long)n_many);
     }
 }
 
@@ -2727,110 +2809,153 @@ __global__ __launch_bounds__(256) void classify_kernel(const uint64_t *__restric
 // most 64 MiB, a quarter of the last-level cache.
 constexpr uint64_t kSharedMaxRows = 1ull << 20;
 
-// Cuckoo insertion of the distinct hashes.  A key goes to an empty slot of
-// either candidate bucket (compare-and-swap 0 -> key); when all four slots
-// are taken it displaces the key of a random slot by atomic exchange (a
-// random walk: a fresh key picks either bucket, a displaced key its other
-// bucket) and carries the displaced key on.  A key is always either in the
-// set or carried by exactly one thread, so none is lost.
+// Cuckoo insertion of distinct hashes into a block of the set in LDS.  A key
+// goes to an empty slot of either candidate bucket (compare-and-swap 0 ->
+// key); when all four slots are taken it displaces the key of a random slot by
+// atomic exchange (a random walk: a fresh key picks either bucket, a displaced
+// key its other bucket) and carries the displaced key on.  A key is always
+// either in the set or carried by exactly one thread, so none is lost.
 constexpr uint32_t kMaxKicks = 2048;
 
-__device__ inline bool try_place(unsigned long long *bk, uint64_t key) {
-    for (int slot = 0; slot < 2; ++slot) {
-        const unsigned long long prev = atomicCAS(bk + slot, 0ull, (unsigned long long)key);
-        if (prev == 0ull || prev == key) return true;
-    }
+__device__ inline bool try_place(unsigned long long *bk, unsigned long long key) {
+    for (int slot = 0; slot < 2; ++slot)
+        if (atomicCAS(bk + slot, 0ull, key) == 0ull) return true;
     return false;
 }
 
-// Place one key; false when the walk did not end.
-__device__ inline bool cuckoo_place(unsigned long long *tab, uint32_t shift, uint64_t key, uint32_t rnd) {
+// Place the key of mixed value x in the block of 2^lg buckets `tab`; false
+// when the walk did not end.
+__device__ inline bool cuckoo_place(unsigned long long *tab, uint32_t lg, uint32_t shift, unsigned long long x) {
+    const uint32_t mask = (1u << lg) - 1u;
     uint32_t from = 0xFFFFFFFFu;   // bucket the carried key was displaced from
+    uint32_t rnd = (uint32_t)(x >> 20);
     for (uint32_t kick = 0; kick < kMaxKicks; ++kick) {
         uint32_t b1, b2;
-        buckets_of(key, shift, b1, b2);
-        if (try_place(tab + 2 * (uint64_t)b1, key) || try_place(tab + 2 * (uint64_t)b2, key)) return true;
+        buckets_of(unmix_hash(x), shift, b1, b2);
+        b1 &= mask;
+        b2 &= mask;
+        if (try_place(tab + 2 * b1, x) || try_place(tab + 2 * b2, x)) return true;
         // displace from the bucket the key did not just leave; the walk's
         // choices come from the full-period 32-bit LCG of Knuth and Lewis
         // (multiplier 1664525, increment 1013904223; Press et al.,
         // Numerical Recipes, "quick and dirty" generator)
         rnd = rnd * 1664525u + 1013904223u;
         const uint32_t b = (b1 == from) ? b2 : (b2 == from) ? b1 : ((rnd >> 31) ? b2 : b1);
-        const unsigned long long old = atomicExch(tab + 2 * (uint64_t)b + ((rnd >> 30) & 1u),
-                                                  (unsigned long long)key);
-        if (old == 0ull || old == key) return true;
-        key = old;
+        const unsigned long long old = atomicExch(tab + 2 * b + ((rnd >> 30) & 1u), x);
+        if (old == 0ull) return true;
+        x = old;
         from = b;
     }
     return false;
 }
 
-__device__ inline uint64_t slot_of(const uint64_t *keys, uint32_t shift, uint64_t key) {
+// The slot of mixed value x in the block, or ~0.
+__device__ inline uint32_t slot_of(const unsigned long long *tab, uint32_t lg, uint32_t shift, unsigned long long x) {
+    const uint32_t mask = (1u << lg) - 1u;
     uint32_t b1, b2;
-    buckets_of(key, shift, b1, b2);
-    if (keys[2 * (uint64_t)b1] == key) return 2 * (uint64_t)b1;
-    if (keys[2 * (uint64_t)b1 + 1] == key) return 2 * (uint64_t)b1 + 1;
-    if (keys[2 * (uint64_t)b2] == key) return 2 * (uint64_t)b2;
-    if (keys[2 * (uint64_t)b2 + 1] == key) return 2 * (uint64_t)b2 + 1;
-    return ~0ull;
+    buckets_of(unmix_hash(x), shift, b1, b2);
+    b1 &= mask;
+    b2 &= mask;
+    return tab[2 * b1] == x ? 2 * b1 : tab[2 * b1 + 1] == x ? 2 * b1 + 1
+         : tab[2 * b2] == x ? 2 * b2 : tab[2 * b2 + 1] == x ? 2 * b2 + 1 : 0xFFFFFFFFu;
 }
 
-__global__ __launch_bounds__(256) void index_insert_kernel(uint64_t *__restrict__ keys, uint32_t shift,
-                                                           const uint64_t *__restrict__ skey, uint64_t n,
-                                                           uint32_t *__restrict__ err) {
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) {
-        if (!run_head(skey, i)) continue;
-        const uint64_t key = skey[i];
-        if (!cuckoo_place((unsigned long long *)keys, shift, key, (uint32_t)(key ^ (key >> 32)) ^ (uint32_t)i))
-            atomicOr(err, kErrTableFull);
-    }
-}
+struct Build {
+    const uint64_t *key;      // the pairs, by part (part_key)
+    const uint32_t *dec;
+    const uint64_t *dkey;     // the distinct hashes of each part
+    const uint32_t *dhold;
+    const uint32_t *start, *count;
+    uint32_t bits;            // 2^bits parts
+    uint32_t lg;              // 2^lg buckets per block, at most S / 2
+    uint32_t log2b;           // 2^log2b buckets
+    uint64_t *keys;           // the set
+    uint32_t *vals;
+    uint64_t *rows;           // bitmap rows, cleared; handed out from 1
+    uint32_t bpitch;
+    u32x4 *shared;            // shared index, cleared, or null
+    uint32_t sh_shift, sh_mask;
+    uint32_t *rows_used;
+    uint32_t *flag;
+};
 
-// Fills the shared index (row v of the bitmap pool is key row_key[v]'s,
-// v >= 1; the keys are distinct).
-__global__ __launch_bounds__(256) void shared_insert_kernel(u32x4 *__restrict__ tab, uint32_t shift, uint32_t mask,
-                                                            const uint64_t *__restrict__ row_key, uint32_t rows) {
-    const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x + 1;
-    if (v >= rows) return;
-    const uint64_t key = row_key[v];
-    uint32_t i = (uint32_t)((key * kGolden) >> shift);
-    // ends: there are more slots than keys
-    while (atomicCAS((unsigned long long *)(tab + i), 0ull, (unsigned long long)key) != 0ull) i = (i + 1) & mask;
-    ((uint32_t *)(tab + i))[2] = v;
-}
-
-// Holder values, once every key has its final slot.  Bitmap rows are
-// handed out by rows_used (row 0 stays zero: the scan reads it when a value
-// is not a row); each row is written by the one thread of its run.
-__global__ __launch_bounds__(256) void index_value_kernel(const uint64_t *__restrict__ keys, uint32_t *__restrict__ vals,
-                                                          uint32_t shift, uint64_t *__restrict__ bits,
-                                                          uint32_t bpitch, const uint64_t *__restrict__ skey,
-                                                          const uint32_t *__restrict__ dec, uint64_t n,
-                                                          uint32_t *__restrict__ rows_used,
-                                                          uint64_t *__restrict__ row_key,
-                                                          uint32_t *__restrict__ err) {
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) {
-        if (!run_head(skey, i)) continue;
-        const uint64_t key = skey[i];
-        uint32_t dmin, dmax;
-        const uint64_t e = run_span(skey, dec, n, i, dmin, dmax);
-        uint32_t v;
-        if (dmin == dmax) {
-            v = kHeldOne | dmin;
-        } else {
-            v = atomicAdd(rows_used, 1u);
-            row_key[v] = key;
-            uint64_t *row = bits + (uint64_t)v * bpitch;
-            for (uint64_t x = i; x < e; ++x) row[dec[x] / 64u] |= 1ull << (dec[x] % 64u);
+// One workgroup per block of the set.  The block's hashes are those of one
+// part, a piece of one, or of several.
+template <uint32_t S>
+__global__ __launch_bounds__(1024) void build_kernel(Build u) {
+    __shared__ unsigned long long lk[S];
+    __shared__ uint32_t lv[S];
+    __shared__ uint32_t n_many, n_used, base;
+    const uint32_t tid = threadIdx.x, shift = 64 - u.log2b, n_slot = 2u << u.lg;
+    const uint64_t b0 = (uint64_t)blockIdx.x << u.lg;   // the block's first bucket
+    const uint32_t p0 = u.log2b >= u.bits ? (uint32_t)(b0 >> (u.log2b - u.bits)) : (uint32_t)(b0 << (u.bits - u.log2b));
+    const uint64_t b1 = b0 + (1ull << u.lg);
+    const uint32_t p1 = u.log2b >= u.bits ? (uint32_t)((b1 - 1) >> (u.log2b - u.bits)) + 1
+                                          : (uint32_t)(b1 << (u.bits - u.log2b));
+    // f(position) over the pairs or the distinct hashes of the block's parts:
+    // a wavefront per part where there are many, else all threads on each
+    const uint32_t wv = wave_index(), nwv = blockDim.x / kWave, lane = tid % kWave;
+    const bool spread = p1 - p0 < nwv;
+    auto each = [&](bool pairs, auto f) {
+        for (uint32_t p = spread ? p0 : p0 + wv; p < p1; p += spread ? 1 : nwv) {
+            const uint32_t a = u.start[p], e = pairs ? u.start[p + 1] : a + u.count[p];
+            for (uint32_t i = a + (spread ? tid : lane); i < e; i += spread ? blockDim.x : kWave) f(i);
         }
-        const uint64_t slot = slot_of(keys, shift, key);
-        if (slot == ~0ull) atomicOr(err, kErrTableFull);
-        else vals[slot] = v;
+    };
+    auto mine = [&](unsigned long long x) { return x >> shift >> u.lg == blockIdx.x; };
+    for (uint32_t s = tid; s < n_slot; s += blockDim.x) {
+        lk[s] = 0;
+        lv[s] = 0;
     }
+    if (tid == 0) n_many = n_used = 0;
+    __syncthreads();
+    each(false, [&](uint32_t i) {
+        const unsigned long long x = u.dkey[i];
+        if (!mine(x)) return;
+        if (!cuckoo_place(lk, u.lg, shift, x)) atomicOr(u.flag, kErrTableFull);
+        if (u.dhold[i] & kManyHolders) atomicAdd(&n_many, 1u);
+    });
+    __syncthreads();
+    if (tid == 0) base = n_many ? atomicAdd(u.rows_used, n_many) : 0u;
+    __syncthreads();
+    each(false, [&](uint32_t i) {
+        const unsigned long long x = u.dkey[i];
+        if (!mine(x)) return;
+        const uint32_t hold = u.dhold[i];
+        uint32_t v = kHeldOne | hold;
+        if (hold & kManyHolders) {
+            v = base + atomicAdd(&n_used, 1u);
+            if (u.shared) {
+                // ends: there are more slots than keys
+                const uint64_t h = unmix_hash(x);
+                uint32_t j = (uint32_t)((h * kGolden) >> u.sh_shift);
+                while (atomicCAS((unsigned long long *)(u.shared + j), 0ull, (unsigned long long)h) != 0ull)
+                    j = (j + 1) & u.sh_mask;
+                ((uint32_t *)(u.shared + j))[2] = v;
+            }
+        }
+        const uint32_t s = slot_of(lk, u.lg, shift, x);
+        if (s != 0xFFFFFFFFu) lv[s] = v;   // (else the walk failed, which was flagged)
+    });
+    __syncthreads();
+    for (uint32_t s = tid; s < n_slot; s += blockDim.x) {
+        u.keys[2 * b0 + s] = unmix_hash(lk[s]);
+        u.vals[2 * b0 + s] = lv[s];
+    }
+    // the bitmaps: this workgroup alone writes its rows, so the atomics stay
+    // in this die's cache
+    if (n_many == 0) return;
+    each(true, [&](uint32_t i) {
+        const unsigned long long x = part_value(u.key[i], u.bits);
+        if (!mine(x)) return;
+        const uint32_t s = slot_of(lk, u.lg, shift, x);
+        const uint32_t v = s != 0xFFFFFFFFu ? lv[s] : kHeldOne;
+        if (v < kHeldOne) {
+            const uint32_t d = u.dec[i];
+            __hip_atomic_fetch_or(u.rows + (uint64_t)v * u.bpitch + d / 64u, 1ull << (d % 64u), __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    });
 }
 
 __global__ void fill_u64_kernel(uint64_t *__restrict__ p, uint64_t n, uint64_t v) {
@@ -3363,7 +3488,7 @@ struct SeqBuf {
 };
 
 template <int T, int MAXC>
-__global__ __launch_bounds__(T) void sequential_cached_kernel(Snap s, Table t, Reqs rq, uint32_t cap,
+__global__ __launch_bounds__(T, MAXC <= 12 ? 4 : 1) void sequential_cached_kernel(Snap s, Table t, Reqs rq, uint32_t cap,
                                                               const Hot *__restrict__ hotr,
                                                               const float *__restrict__ lead_lam,
                                                               const uint32_t *__restrict__ order,
@@ -3600,6 +3725,8 @@ struct Scratch {
 
 // ====================================================================== host side
 
+// bytes of a cache load's work buffer that a handle keeps (89 M resident hashes)
+constexpr uint64_t kLoadKeep = 2ull << 30;
 constexpr uint32_t kTimeSlots = 256;   // timed launches kept for netkv_kernel_ms
 
 struct netkv_ctx {
@@ -3654,6 +3781,10 @@ struct netkv_ctx {
     uint64_t *bits = nullptr;    // [rows][bpitch] holder bitmaps
     uint64_t table_bytes = 0, buckets = 0, rows = 0, distinct = 0;
     uint32_t log2b = 0, bpitch = 0;
+    uint64_t bits_cap = 0;       // words allocated
+    // the cache load's work buffer, kept from load to load
+    uint8_t *load_buf = nullptr;
+    uint64_t load_bytes = 0;
     // shared index: the hashes of two or more holders (null: none was built)
     u32x4 *sh_tab = nullptr;
     uint32_t sh_log2b = 0;
@@ -4763,6 +4894,7 @@ void netkv_destroy(netkv_handle h) {
         dfree(h->tvals);
         dfree(h->bits);
         dfree(h->sh_tab);
+        dfree(h->load_buf);
         dfree(h->errword);
         dfree(h->loadword);
         dfree(h->spt_scen);
@@ -5096,182 +5228,187 @@ netkv_status netkv_cache_load(netkv_handle h, uint32_t n_decode, const uint64_t 
     // reads its groups' C words inside the row, at 8 * C-byte alignment
     const uint64_t bwords = ((uint64_t)n_decode + 63) / 64;
     const uint32_t bpitch = (uint32_t)((bwords + 11) / 12 * 12);
-    uint64_t *dh = nullptr, *dkey = nullptr, *doff = nullptr;
-    uint32_t *dec_in = nullptr, *dec = nullptr;
-    unsigned long long *cnt = nullptr;
-    uint8_t *stmp = nullptr;
-    auto cleanup = [&]() { dfree(dh); dfree(dkey); dfree(doff); dfree(dec_in); dfree(dec); dfree(cnt); dfree(stmp); };
-    // the device copy keeps the caller's absolute offsets valid: copy from `first`
-    if (dalloc(dh, off[n_decode]) != hipSuccess || dalloc(doff, (uint64_t)n_decode + 1) != hipSuccess ||
-        dalloc(dkey, total) != hipSuccess || dalloc(dec_in, total) != hipSuccess ||
-        dalloc(dec, total) != hipSuccess || dalloc(cnt, 2) != hipSuccess) {
-        cleanup();
-        return fail(h, NETKV_ENOMEM, "staging allocation failed");
-    }
-    hipError_t e = hipSuccess;
-    if (total) e = hipMemcpyAsync(dh + first, hashes + first, 8ull * total, hipMemcpyDefault, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(doff, off.data(), 8ull * (n_decode + 1), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMemsetAsync(h->loadword, 0, 4, st);
-    uint32_t bad = 0;
-    if (e == hipSuccess && total) {
-        hipLaunchKernelGGL(count_zero_kernel, dim3(grid_for(total, 256, 8192)), dim3(256), 0, st, dh + first, total,
-                           h->loadword);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipMemcpyAsync(&bad, h->loadword, 4, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) {
-        cleanup();
-        return fail(h, NETKV_EDEVICE, "cache upload failed: %s", hipGetErrorString(e));
-    }
-    if (bad) {
-        cleanup();
-        return fail(h, NETKV_EINVAL, "cache contains the reserved hash value 0");
-    }
-    // (hash, decode) pairs sorted by hash; per distinct hash: one holder or several
-    unsigned long long counts[2] = {0, 0};
-    if (total) {
-        hipLaunchKernelGGL(owner_kernel, dim3(grid_for(total, 256, 16384)), dim3(256), 0, st, (const uint64_t *)doff,
-                           n_decode, first, total, dec_in);
-        e = hipGetLastError();
-        size_t tb = 0;
-        if (e == hipSuccess)
-            e = rocprim::radix_sort_pairs(nullptr, tb, (const uint64_t *)(dh + first), dkey, (const uint32_t *)dec_in,
-                                          dec, (uint32_t)total, 0, 64, st);
-        if (e == hipSuccess && dalloc(stmp, std::max<size_t>(tb, 16)) != hipSuccess) {
-            cleanup();
-            return fail(h, NETKV_ENOMEM, "sort scratch allocation failed");
-        }
-        if (e == hipSuccess)
-            e = rocprim::radix_sort_pairs(stmp, tb, (const uint64_t *)(dh + first), dkey, (const uint32_t *)dec_in,
-                                          dec, (uint32_t)total, 0, 64, st);
-        if (e == hipSuccess) e = hipMemsetAsync(cnt, 0, 16, st);
-        if (e == hipSuccess) {
-            hipLaunchKernelGGL(classify_kernel, dim3(grid_for(total, 256, 16384)), dim3(256), 0, st,
-                               (const uint64_t *)dkey, (const uint32_t *)dec, total, cnt);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = hipMemcpyAsync(counts, cnt, 16, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-    }
-    dfree(dh);
-    dfree(doff);
-    dfree(dec_in);
-    dfree(stmp);
-    if (e != hipSuccess) {
-        cleanup();
-        return fail(h, NETKV_EDEVICE, "holder sort failed: %s", hipGetErrorString(e));
-    }
-    const uint64_t distinct = counts[0], rows = counts[1] + 1;   // row 0: all zero
-    if (rows >= (uint64_t)kHeldOne) {
-        cleanup();
-        return fail(h, NETKV_ECAPACITY, "more than 2^31 - 2 hashes held by several decodes");
-    }
-    // release the old index first: the new one may be large
-    dfree(h->table);
-    dfree(h->tvals);
-    dfree(h->bits);
-    h->have_cache = false;
     // two slots per bucket; two-choice cuckoo sets of 2-slot buckets stay
     // buildable well above load factor 0.5, and are capped at 0.85
     const double lf = std::min(0.85, (double)max_load_factor);
-    const uint64_t need = (uint64_t)std::ceil((double)distinct / (2.0 * lf));
-    uint32_t log2b = 3;
-    while ((1ull << log2b) < need) {
-        ++log2b;
-        if (log2b > 30) {
-            cleanup();
-            return fail(h, NETKV_ECAPACITY, "the index would need more than 2^31 slots");
+    auto log2_buckets = [&](uint64_t n, double f) {
+        const double need = std::ceil((double)n / (2.0 * f));
+        uint32_t b = 3;
+        while (b < 40 && (double)(1ull << b) < need) ++b;
+        return b;
+    };
+    // parts that would fill 2^11 buckets each if every hash were distinct, or
+    // 2^12 where those would be more than two sort passes of 8 bits can tell
+    // apart (with 160 KiB of LDS per CU, 3 or 1 workgroups work on a CU)
+    const uint32_t most = log2_buckets(total, std::max(lf, 0.5));
+    const bool big = most > 16 + kBlockLog2;
+    const uint32_t part_lg = kBlockLog2 + (big ? 1 : 0);
+    const uint32_t bits = most > part_lg ? most - part_lg : 0u;   // at most 19: total < 2^31
+    const uint32_t n_part = 1u << bits;
+    size_t tb = 0;
+    if (total && bits)
+        HIPCHK(h, rocprim::radix_sort_pairs(nullptr, tb, (const uint64_t *)nullptr, (uint64_t *)nullptr,
+                                            (const uint32_t *)nullptr, (uint32_t *)nullptr, (uint32_t)total,
+                                            0, bits, st));
+    // work buffer: the pairs twice (the sort's input, which then takes the
+    // distinct hashes, and its output), offsets, parts, counters
+    uint64_t at = 0;
+    auto take = [&](uint64_t bytes) {
+        const uint64_t o = at;
+        at += (bytes + 255) / 256 * 256;
+        return o;
+    };
+    const uint64_t o_key = take(8 * total), o_key2 = take(8 * total), o_dec = take(4 * total), o_dec2 = take(4 * total);
+    const uint64_t o_off = take(8ull * (n_decode + 1)), o_start = take(4ull * (n_part + 1)), o_count = take(4ull * n_part);
+    const uint64_t o_cnt = take(24), o_tmp = take(std::max<size_t>(tb, 16));
+    uint8_t *buf = h->load_buf;
+    if (at > h->load_bytes) {
+        dfree(h->load_buf);
+        h->load_bytes = 0;
+        if (dalloc(h->load_buf, at) != hipSuccess) return fail(h, NETKV_ENOMEM, "staging allocation failed");
+        buf = h->load_buf;
+        h->load_bytes = at;
+    }
+    // a work buffer of up to kLoadKeep bytes stays for the next load
+    struct Drop {
+        netkv_handle h;
+        ~Drop() {
+            if (h->load_bytes > kLoadKeep) {
+                dfree(h->load_buf);
+                h->load_bytes = 0;
+            }
         }
+    } drop{h};
+    uint64_t *key = (uint64_t *)(buf + o_key), *key2 = (uint64_t *)(buf + o_key2), *doff = (uint64_t *)(buf + o_off);
+    uint32_t *dec = (uint32_t *)(buf + o_dec), *dec2 = (uint32_t *)(buf + o_dec2);
+    uint32_t *start = (uint32_t *)(buf + o_start), *count = (uint32_t *)(buf + o_count);
+    struct Counters {
+        unsigned long long n[2];   // distinct hashes, those of several holders
+        uint32_t rows, flag;       // next bitmap row; errors
+    } c{};
+    Counters *dc = (Counters *)(buf + o_cnt);
+    c.rows = 1;   // row 0: all zero
+    hipError_t e = hipMemcpyAsync(doff, off.data(), 8ull * (n_decode + 1), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(dc, &c, sizeof c, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess && total) {
+        const uint64_t *src = hashes + first;
+        if (!on_device(h, hashes)) {
+            e = hipMemcpyAsync(key, src, 8ull * total, hipMemcpyDefault, st);
+            src = key;
+        }
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(pair_kernel, dim3((uint32_t)((total + kBlock * kPairPer - 1) / (kBlock * kPairPer))),
+                               dim3(kBlock), 0, st, (const uint64_t *)doff, n_decode, first, total, src, bits, key,
+                               dec, &dc->flag);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess && bits)
+            e = rocprim::radix_sort_pairs(buf + o_tmp, tb, (const uint64_t *)key, key2, (const uint32_t *)dec, dec2,
+                                          (uint32_t)total, 0, bits, st);
+        if (e == hipSuccess && !bits) {   // one part: the pairs as they are
+            std::swap(key, key2);
+            std::swap(dec, dec2);
+        }
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(parts_kernel, dim3((uint32_t)(total / 256 + 1)), dim3(256), 0, st,
+                               (const uint64_t *)key2, total, bits, start);
+            if (big)
+                hipLaunchKernelGGL((dedupe_kernel<2 * kBlockSlots>), dim3(n_part), dim3(1024), 0, st,
+                                   (const uint64_t *)key2, (const uint32_t *)dec2, (const uint32_t *)start, bits, key, dec,
+                                   count, dc->n, &dc->flag);
+            else
+                hipLaunchKernelGGL((dedupe_kernel<kBlockSlots>), dim3(n_part), dim3(512), 0, st,
+                                   (const uint64_t *)key2, (const uint32_t *)dec2, (const uint32_t *)start, bits, key, dec,
+                                   count, dc->n, &dc->flag);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) e = hipMemcpyAsync(&c, dc, sizeof c, hipMemcpyDeviceToHost, st);
     }
-    uint64_t *tab = nullptr, *bm = nullptr;
-    uint32_t *tv = nullptr;
-    if (dalloc(bm, rows * bpitch) != hipSuccess) {
-        cleanup();
-        return fail(h, NETKV_ENOMEM, "holder bitmap allocation of %llu bytes failed",
-                    (unsigned long long)(8 * rows * bpitch));
+    {
+        const hipError_t e2 = hipStreamSynchronize(st);   // (also after an error: the host's copies end here)
+        if (e == hipSuccess) e = e2;
     }
-    uint64_t *row_key = nullptr;   // the key of each bitmap row
-    if (dalloc(row_key, rows) != hipSuccess) {
-        cleanup();
-        dfree(bm);
-        return fail(h, NETKV_ENOMEM, "staging allocation failed");
+    if (e != hipSuccess) return fail(h, NETKV_EDEVICE, "index build failed: %s", hipGetErrorString(e));
+    if (c.flag & 1u) return fail(h, NETKV_EINVAL, "cache contains the reserved hash value 0");
+    if (c.flag) return fail(h, NETKV_ECAPACITY, "index build could not place every hash");
+    const uint64_t distinct = c.n[0], rows = c.n[1] + 1;   // row 0: all zero
+    if (rows >= (uint64_t)kHeldOne)
+        return fail(h, NETKV_ECAPACITY, "more than 2^31 - 2 hashes held by several decodes");
+    uint32_t log2b = log2_buckets(distinct, lf);
+    if (log2b > 30) return fail(h, NETKV_ECAPACITY, "the index would need more than 2^31 slots");
+    // the old index is given up here; its buffers serve the new one where they
+    // have its size (else they are released first: the new one may be large)
+    h->have_cache = false;
+    const uint64_t row_words = rows * bpitch;
+    if (row_words > h->bits_cap || row_words < h->bits_cap / 2) {
+        dfree(h->bits);
+        h->bits_cap = 0;
     }
-    e = hipMemsetAsync(bm, 0, 8 * rows * bpitch, st);
+    if (h->log2b != log2b) {
+        dfree(h->table);
+        dfree(h->tvals);
+        h->log2b = 0;
+    }
+    const bool shared = rows > 1 && rows <= kSharedMaxRows;
+    uint32_t lb = 3;
+    while ((1ull << lb) < 3 * rows) ++lb;
+    if (h->sh_log2b != lb || !shared) dfree(h->sh_tab);
+    if (!h->bits) {
+        if (dalloc(h->bits, row_words) != hipSuccess)
+            return fail(h, NETKV_ENOMEM, "holder bitmap allocation of %llu bytes failed",
+                        (unsigned long long)(8 * row_words));
+        h->bits_cap = row_words;
+    }
     // build at the planned size; should a build fail to place every key (a
     // random walk that did not end), rebuild with twice the buckets, twice
     uint64_t nbk = 0;
     for (int attempt = 0;; ++attempt) {
         nbk = 1ull << log2b;
-        if (e == hipSuccess && (dalloc(tab, 2 * nbk) != hipSuccess || dalloc(tv, 2 * nbk) != hipSuccess)) {
-            cleanup();
-            dfree(tab); dfree(tv); dfree(bm); dfree(row_key);
-            return fail(h, NETKV_ENOMEM, "index allocation of %llu bytes failed", (unsigned long long)(24 * nbk));
+        if (!h->table || !h->tvals) {
+            if (dalloc(h->table, 2 * nbk) != hipSuccess || dalloc(h->tvals, 2 * nbk) != hipSuccess) {
+                dfree(h->table);
+                dfree(h->tvals);
+                h->log2b = 0;
+                return fail(h, NETKV_ENOMEM, "index allocation of %llu bytes failed", (unsigned long long)(24 * nbk));
+            }
+            h->log2b = log2b;
         }
-        if (e == hipSuccess) e = hipMemsetAsync(tab, 0, 16 * nbk, st);
-        if (e == hipSuccess) e = hipMemsetAsync(h->loadword, 0, 4, st);
+        // the shared index; without it (too many shared hashes to stay in
+        // cache, no memory) lookups go to the whole index
+        if (shared && !h->sh_tab) {
+            if (dalloc(h->sh_tab, 1ull << lb) != hipSuccess) (void)hipGetLastError();
+            h->sh_log2b = lb;
+        }
+        c.rows = 1;
+        c.flag = 0;
+        e = hipMemsetAsync(h->bits, 0, 8 * row_words, st);
+        if (e == hipSuccess && h->sh_tab) e = hipMemsetAsync(h->sh_tab, 0, 16ull << lb, st);
+        if (e == hipSuccess && !total) e = hipMemsetAsync(h->table, 0, 16 * nbk, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(dc, &c, sizeof c, hipMemcpyHostToDevice, st);
         if (e == hipSuccess && total) {
-            hipLaunchKernelGGL(index_insert_kernel, dim3(grid_for(total, 256, 16384)), dim3(256), 0, st, tab,
-                               64u - log2b, (const uint64_t *)dkey, total, h->loadword);
+            const uint32_t lg = std::min(log2b, std::max(kBlockLog2, std::min(part_lg, log2b > bits ? log2b - bits : 0u)));
+            const Build u{key2, dec2, key, dec, start, count, bits, lg, log2b, h->table, h->tvals, h->bits, bpitch,
+                          h->sh_tab, 64u - lb, (1u << lb) - 1u, &dc->rows, &dc->flag};
+            const uint32_t grid = 1u << (log2b - lg);
+            if (lg > kBlockLog2)
+                hipLaunchKernelGGL((build_kernel<2 * kBlockSlots>), dim3(grid), dim3(1024), 0, st, u);
+            else
+                hipLaunchKernelGGL((build_kernel<kBlockSlots>), dim3(grid), dim3(512), 0, st, u);
             e = hipGetLastError();
         }
-        bad = 0;
-        if (e == hipSuccess) e = hipMemcpyAsync(&bad, h->loadword, 4, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess || !bad || attempt == 2 || log2b >= 30) break;
-        dfree(tab);
-        dfree(tv);
+        if (e == hipSuccess) e = hipMemcpyAsync(&c, dc, sizeof c, hipMemcpyDeviceToHost, st);
+        const hipError_t e2 = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = e2;
+        if (e != hipSuccess || !c.flag || attempt == 2 || log2b >= 30) break;
+        dfree(h->table);
+        dfree(h->tvals);
+        h->log2b = 0;
         ++log2b;
     }
-    if (e == hipSuccess && !bad && total) {
-        // rows are handed out from 1 (cnt[0] doubles as the counter)
-        const uint32_t one = 1;
-        e = hipMemcpyAsync(cnt, &one, 4, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) {
-            hipLaunchKernelGGL(index_value_kernel, dim3(grid_for(total, 256, 16384)), dim3(256), 0, st,
-                               (const uint64_t *)tab, tv, 64u - log2b, bm, bpitch, (const uint64_t *)dkey,
-                               (const uint32_t *)dec, total, (uint32_t *)cnt, row_key, h->loadword);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = hipMemcpyAsync(&bad, h->loadword, 4, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-    }
-    // the shared index; without it (too many shared hashes to stay in cache,
-    // no memory) lookups go to the whole index
-    dfree(h->sh_tab);
-    if (e == hipSuccess && !bad && rows > 1 && rows <= kSharedMaxRows) {
-        uint32_t lb = 3;
-        while ((1ull << lb) < 3 * rows) ++lb;
-        u32x4 *sk = nullptr;
-        if (dalloc(sk, 1ull << lb) == hipSuccess) {
-            e = hipMemsetAsync(sk, 0, 16ull << lb, st);
-            if (e == hipSuccess) {
-                hipLaunchKernelGGL(shared_insert_kernel, dim3((uint32_t)((rows + 255) / 256)), dim3(256), 0, st, sk,
-                                   64u - lb, (1u << lb) - 1u, (const uint64_t *)row_key, (uint32_t)rows);
-                e = hipGetLastError();
-            }
-            if (e == hipSuccess) e = hipStreamSynchronize(st);
-            if (e != hipSuccess) dfree(sk);
-            h->sh_tab = sk;
-            h->sh_log2b = lb;
-        } else {
-            (void)hipGetLastError();
-        }
-    }
-    dfree(row_key);
-    cleanup();
-    if (e != hipSuccess || bad) {
-        dfree(tab);
-        dfree(tv);
-        dfree(bm);
+    if (e != hipSuccess || c.flag)
         return e != hipSuccess ? fail(h, NETKV_EDEVICE, "index build failed: %s", hipGetErrorString(e))
                                : fail(h, NETKV_ECAPACITY, "index build could not place every hash");
-    }
-    h->table = tab;
-    h->tvals = tv;
-    h->bits = bm;
     h->buckets = nbk;
-    h->log2b = log2b;
     h->bpitch = bpitch;
     h->rows = rows;
     h->distinct = distinct;

@@ -1,0 +1,119 @@
+"""The holder index's build (netkv_cache_load): membership of every decode
+against numpy, over the forms the resident sets take.  Needs an MI355X and
+the built library."""
+import numpy as np
+import pytest
+
+from paper_2606_03910_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+D = 48   # decodes of the 64-GPU cluster
+
+
+@pytest.fixture(scope="module")
+def nk():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2606_03910_amd import netkv
+    netkv.load_library()
+    return netkv
+
+
+def _u64(rng, n):
+    return rng.integers(1, 1 << 63, n, dtype=np.uint64) * np.uint64(2) + rng.integers(0, 2, n, dtype=np.uint64)
+
+
+def _sets(form, rng):
+    """Per decode the resident hashes, and the load factor."""
+    if form == "empty":
+        return [np.zeros(0, np.uint64)] * D, 0.5
+    if form == "one":
+        return [np.array([7], np.uint64)] + [np.zeros(0, np.uint64)] * (D - 1), 0.5
+    if form == "part":        # all in one part, with repeats in a set
+        x = _u64(rng, 300)
+        return [np.concatenate([x[d:d + 40], x[d:d + 7]]) for d in range(D)], 0.5
+    if form == "same":        # every decode holds the same set: many parts per block
+        x = _u64(rng, 5000)
+        return [rng.permutation(x) for _ in range(D)], 0.5
+    if form == "sequential":  # hashes that differ in their low bits only
+        return [np.arange(1 + 3000 * d, 1 + 3000 * d + 4000, dtype=np.uint64) for d in range(D)], 0.5
+    if form == "sparse":      # several blocks per part
+        return [_u64(rng, 700) for _ in range(D)], 0.02
+    if form == "dense":
+        return [_u64(rng, 9100) for _ in range(D)], 0.85
+    if form == "large":       # parts of 2^12 buckets: three sort digits otherwise
+        x = _u64(rng, 200000)
+        return [np.concatenate([_u64(rng, 1600000), rng.choice(x, 50000)]) for _ in range(D)], 0.5
+    raise AssertionError(form)
+
+
+FORMS = ["empty", "one", "part", "same", "sequential", "sparse", "dense", "large"]
+
+
+def _check(nk, sel, snap, sets, lf, rng, host):
+    off = np.zeros(D + 1, np.uint64)
+    off[1:] = np.cumsum([len(x) for x in sets])
+    lead = 3   # the first set need not start at 0
+    hs = np.concatenate([np.full(lead, 5, np.uint64)] + list(sets))
+    off += np.uint64(lead)
+    if host:   # (the C call takes host arrays too)
+        assert nk.load_library().netkv_cache_load(sel.h, D, off.ctypes.data, hs.ctypes.data, len(hs), lf, None) == 0
+    else:
+        nk.netkv_cache_load(sel.h, D, nk.to_device(off, sel.device), nk.to_device(hs, sel.device), lf, sel.device)
+    allh = hs[lead:]
+    owner = np.repeat(np.arange(D), [len(x) for x in sets])
+    uniq, inv = np.unique(allh, return_inverse=True)
+    holds = np.zeros((len(uniq) + 1, D), bool)
+    holds[inv, owner] = True
+    ci = nk.netkv_cache_info(sel.h)
+    assert ci["distinct_hashes"] == len(uniq)
+    assert ci["shared_hashes"] == int((holds.sum(1) >= 2).sum())
+    buckets = 8
+    while 2 * buckets * lf < len(uniq):
+        buckets *= 2
+    assert ci["index_slots"] in (2 * buckets, 4 * buckets, 8 * buckets)
+    # one-block requests: resident hashes of every kind, and others
+    q = np.concatenate([rng.choice(uniq, 1200) if len(uniq) else uniq, _u64(rng, 300), np.zeros(1, np.uint64)])
+    bt = int(snap["block_tokens"])
+    req = dict(prefill=np.zeros(len(q), np.uint32), len_tokens=np.full(len(q), bt, np.uint32),
+               hash_off=np.arange(len(q) + 1, dtype=np.uint64), hashes=q)
+    out = sel.select(nk.requests_to_device(req, sel.device), k=1, pairs=True)
+    sel.sync_errors()
+    got = nk.to_numpy(out["pairs"]["prefix_blocks"]).reshape(len(q), D)
+    pos = np.minimum(np.searchsorted(uniq, q), max(0, len(uniq) - 1))
+    hit = uniq[pos] == q if len(uniq) else np.zeros(len(q), bool)
+    want = holds[np.where(hit, pos, len(uniq))]
+    assert np.array_equal(got, want.astype(got.dtype))
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_membership(nk, form):
+    """Resident hashes are found on exactly their decodes and nothing else
+    is found, from host and from device arrays, on a handle of their own;
+    then again on a handle whose buffers an index of another size, and one of
+    the same size, left behind."""
+    print("[gpu-case] index", form, flush=True)
+    rng = np.random.default_rng(91)
+    cfg = W.scaled(W.CONFIGS["c0"], n_requests=8, cache_per_decode=64)
+    snap = W.make_snapshot(cfg, 3)
+    sets, lf = _sets(form, rng)
+    sel = nk.Selector(0)
+    sel.load_snapshot(snap)
+    _check(nk, sel, snap, sets, lf, rng, host=True)
+    _check(nk, sel, snap, sets, lf, rng, host=False)
+    other, lf2 = _sets("same" if form != "same" else "part", rng)
+    _check(nk, sel, snap, other, lf2, rng, host=False)
+    _check(nk, sel, snap, sets, lf, rng, host=False)
+    # the reserved value is refused and the index stays
+    bad = [x.copy() for x in sets]
+    bad[-1] = np.concatenate([bad[-1], np.zeros(1, np.uint64)])
+    before = nk.netkv_cache_info(sel.h)
+    off = np.zeros(D + 1, np.uint64)
+    off[1:] = np.cumsum([len(x) for x in bad])
+    with pytest.raises(nk.NetKVError):
+        nk.netkv_cache_load(sel.h, D, nk.to_device(off, sel.device), nk.to_device(np.concatenate(bad), sel.device), lf,
+                            sel.device)
+    assert nk.netkv_cache_info(sel.h) == before
+    sel.close()
