@@ -5325,7 +5325,10 @@ netkv_status netkv_cache_load(netkv_handle h, uint32_t n_decode, const uint64_t 
         if (e == hipSuccess) e = hipMemcpyAsync(&c, dc, sizeof c, hipMemcpyDeviceToHost, st);
     }
     {
-        const hipError_t e2 = hipStreamSynchronize(st);   // (also after an error: the host's copies end here)
+        // (also after an error: the host's copies end here; the device, since
+        // selections on other streams may still read the index whose buffers
+        // are reused below)
+        const hipError_t e2 = hipDeviceSynchronize();
         if (e == hipSuccess) e = e2;
     }
     if (e != hipSuccess) return fail(h, NETKV_EDEVICE, "index build failed: %s", hipGetErrorString(e));

@@ -117,3 +117,34 @@ def test_membership(nk, form):
                             sel.device)
     assert nk.netkv_cache_info(sel.h) == before
     sel.close()
+
+
+def test_load_waits_for_selections_on_other_streams(nk):
+    """A selection in flight on one stream keeps the index it was called
+    with while another stream loads one of the same size (whose buffers it
+    takes over)."""
+    print("[gpu-case] index load beside a selection", flush=True)
+    rng = np.random.default_rng(5)
+    cfg = W.scaled(W.CONFIGS["c0"], n_requests=200000, cache_per_decode=4096)
+    snap = W.make_snapshot(cfg, 3)
+    ch = W.prefix_chains(cfg, 3)
+    req, cache = W.make_requests(cfg, 3, chains=ch), W.make_caches(cfg, 3, chains=ch)
+    sel = nk.Selector(0)
+    sel.load_snapshot(snap)
+    sel.load_cache(cache, 0.5)
+    rd = nk.requests_to_device(req, sel.device)
+    want = sel.select(rd, k=1)
+    want = [nk.to_numpy(want["idx"]), nk.to_numpy(want["score"])]
+    off = nk.to_device(cache["hash_off"].astype(np.uint64), sel.device)
+    other = nk.to_device(_u64(rng, len(cache["hashes"])), sel.device)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(a):
+        outs = [sel.select(rd, k=1) for _ in range(20)]
+    with torch.cuda.stream(b):
+        nk.netkv_cache_load(sel.h, D, off, other, 0.5, sel.device)
+    torch.cuda.synchronize()
+    for o in outs:
+        assert np.array_equal(nk.to_numpy(o["idx"]), want[0])
+        assert np.array_equal(nk.to_numpy(o["score"]).view(np.uint32), want[1].view(np.uint32))
+    sel.close()
