@@ -208,6 +208,22 @@ __device__ inline uint32_t holder_lane(const Table &t, uint64_t h) {
     return slot == ~0ull ? kNoHolder : t.vals[slot];
 }
 
+// The same with the second bucket read only where the first is full and does
+// not hold h: a hash lies in its second bucket only if its first was full when
+// it was placed, and no slot of the set empties again.
+__device__ inline uint32_t holder_lane_lean(const Table &t, uint64_t h) {
+    if (h == 0) return kNoHolder;
+    uint32_t b1, b2;
+    buckets_of(h, t.shift, b1, b2);
+    uint64_t slot = 2 * (uint64_t)b1;
+    ulonglong2 k = *(const ulonglong2 *)(t.keys + slot);
+    if (k.x != h && k.y != h && k.x != 0 && k.y != 0) {
+        slot = 2 * (uint64_t)b2;
+        k = *(const ulonglong2 *)(t.keys + slot);
+    }
+    return k.x == h ? t.vals[slot] : k.y == h ? t.vals[slot + 1] : kNoHolder;
+}
+
 // The shared index: the hashes that two or more decodes hold, with their
 // bitmap rows.  One 16-byte slot holds a key and its row, and linear probing
 // at a load factor of a sixth to a third finds most keys, and most absences,
@@ -2101,7 +2117,7 @@ __global__ __launch_bounds__(kBlock) void match_kernel(Snap s, Table t, Shared s
             },
             0);
         uint32_t v = kNoHolder;
-        if (sub == 0 && m < n) v = holder_lane(t, rq.hashes[a + m]);
+        if (sub == 0 && m < n) v = holder_lane_lean(t, rq.hashes[a + m]);
         if (v != kNoHolder) hv[a + m] = v;
         act = ((ballot(v != kNoHolder) >> seg0) & 1ull) != 0;
         if (act) {
@@ -4506,10 +4522,19 @@ netkv_status run_select(netkv_handle h, Scratch &sc, const netkv_requests_t *req
 // The bounded selection: pools of up to 64 groups of 64 decodes.  It looks up
 // every block of every request, the ordering pipeline about one per request:
 // with runs of 191 blocks 65,536 requests take 115 us here and 200 us there,
-// 262,144 requests 448 us here and 398 us there.
-bool bounded_batch(netkv_handle h, uint64_t R, uint64_t n_hashes) {
-    return (h->D + kWave - 1) / kWave <= kBoundMaxGroups && unordered(h) &&
-           (R <= (1ull << 17) || n_hashes <= 64 * R);
+// 262,144 requests 448 us here and 398 us there.  With staged routes (`two`)
+// the bounds leave many groups, more of them for k = 8 and for long runs, and
+// it wins only while the (request, group) tasks are few (us, requests x
+// groups, here / there): k = 1 60,000 x 48 185 / 246, 400,000 x 12 297 / 340,
+// 200,000 x 48 373 / 373, 800,000 x 48 1047 / 853; k = 3 60,000 x 48 306 / 331,
+// 200,000 x 48 685 / 571; k = 8 60,000 x 12 290 / 282, 60,000 x 48 725 / 453;
+// runs of 191 blocks, k = 1, 60,000 x 12 144-189 / 166, 60,000 x 48 341 / 230.
+constexpr uint64_t kBoundRouteTasks = 5ull << 20;
+bool bounded_batch(netkv_handle h, uint64_t R, uint64_t n_hashes, uint32_t k, bool two) {
+    const uint64_t ng = (h->D + kWave - 1) / kWave;
+    const bool hard = k > 4 || n_hashes > 64 * R;
+    return ng <= kBoundMaxGroups && unordered(h) && (R <= (1ull << 17) || n_hashes <= 64 * R) &&
+           (!two || R * ng * (hard ? 8 : 1) <= kBoundRouteTasks);
 }
 
 netkv_status ensure_bounds(netkv_handle h, uint64_t R, uint64_t n_hashes) {
@@ -5444,7 +5469,8 @@ netkv_status netkv_select_batch(netkv_handle h, const netkv_requests_t *req, uin
     }
     if (!want_pairs && direct_batch(h, req->n_req, req->n_hashes, kDirectTasks))
         return run_direct(h, req, k, out_idx, out_score, s, true);
-    if (!want_pairs && bounded_batch(h, req->n_req, req->n_hashes)) return run_bounded(h, req, k, out_idx, out_score, s, true);
+    if (!want_pairs && bounded_batch(h, req->n_req, req->n_hashes, k, h->have_route))
+        return run_bounded(h, req, k, out_idx, out_score, s, true);
     return select_owned(h, req, k, out_idx, out_score, po, want_pairs, 0xFFFFFFFFu, s, true);
 }
 
@@ -5495,7 +5521,7 @@ netkv_status netkv_reserve(netkv_handle h, uint32_t max_req, uint64_t max_hashes
         elems = std::max<uint64_t>(elems, (uint64_t)max_req * geo.ngroup * geo.K);
     }
     netkv_status st = ensure_scratch(h, h->sc, max_req, elems, max_hashes, (hipStream_t)stream);
-    if (!st && bounded_batch(h, max_req, 0)) st = ensure_bounds(h, max_req, max_hashes);
+    if (!st && bounded_batch(h, max_req, 0, 1, false)) st = ensure_bounds(h, max_req, max_hashes);
     if (!st) st = ensure_hotr(h, max_req);
     if (!st) st = ensure_dlam(h, std::min<uint64_t>(max_req, kDirectRecordTasks / ((h->D + kWave - 1) / kWave)));
     if (!st) st = ensure_seq(h, max_req, h->P, true, true);
