@@ -4529,12 +4529,16 @@ netkv_status run_select(netkv_handle h, Scratch &sc, const netkv_requests_t *req
 // 200,000 x 48 373 / 373, 800,000 x 48 1047 / 853; k = 3 60,000 x 48 306 / 331,
 // 200,000 x 48 685 / 571; k = 8 60,000 x 12 290 / 282, 60,000 x 48 725 / 453;
 // runs of 191 blocks, k = 1, 60,000 x 12 144-189 / 166, 60,000 x 48 341 / 230.
-constexpr uint64_t kBoundRouteTasks = 5ull << 20;
+// Without staged routes, k = 8: 60,000 x 12 166 / 281, 60,000 x 48 341-365 / 410
+// (runs of 191 blocks 271-412 / 403-412), 800,000 x 48 2,376 / 2,410; the line
+// is drawn where it still wins clearly.
+constexpr uint64_t kBoundRouteTasks = 5ull << 20, kBoundManyTasks = 8ull << 20;
 bool bounded_batch(netkv_handle h, uint64_t R, uint64_t n_hashes, uint32_t k, bool two) {
     const uint64_t ng = (h->D + kWave - 1) / kWave;
-    const bool hard = k > 4 || n_hashes > 64 * R;
-    return ng <= kBoundMaxGroups && unordered(h) && (R <= (1ull << 17) || n_hashes <= 64 * R) &&
-           (!two || R * ng * (hard ? 8 : 1) <= kBoundRouteTasks);
+    const bool many = k > 4, long_runs = n_hashes > 64 * R;
+    const uint64_t tasks = R * ng * (many ? 8 : 1) * (two && long_runs ? 8 : 1);
+    return ng <= kBoundMaxGroups && unordered(h) && (R <= (1ull << 17) || !long_runs) &&
+           (two ? tasks <= kBoundRouteTasks : !many || tasks <= kBoundManyTasks);
 }
 
 netkv_status ensure_bounds(netkv_handle h, uint64_t R, uint64_t n_hashes) {
