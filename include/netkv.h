@@ -122,16 +122,22 @@ netkv_status netkv_congestion_get(netkv_handle h, float *out, void *stream);
  * Host or device pointers.  Value 0 is reserved (EINVAL); repeated hashes
  * of one decode are allowed and count once.  Builds the holder index: one
  * open-addressed set of every distinct resident hash, with at most
- * `max_load_factor` (0 < lf < 1) occupancy (capped at 0.85; a build that
- * cannot place every hash is retried with twice the buckets, twice), and
+ * `max_load_factor` (0 < lf < 1) occupancy (capped at 0.85), and
  * for each hash its holders -- one decode, or a bitmap over the decodes
  * (8 * ceil(ceil(n_decode / 64) / 12) * 12 bytes per hash held by two or more) -- so
  * that one lookup answers a membership test on every decode at once.
+ * The set is built in blocks of 2^11 or 2^12 buckets, each in one
+ * workgroup's LDS; one of several blocks that would be more than 0.80 full
+ * takes twice the buckets.  Where the blocks cannot hold the hashes (values
+ * that crowd in few blocks, no memory or more than 2^31 slots for twice the
+ * buckets) the set is built as a whole at the planned size, about five times
+ * slower, and retried with twice the buckets, twice.
  * Synchronous; needs about 28 bytes of device memory per resident hash
- * while building (up to 2 GiB of it stay with the handle for the next load).  EINVAL: bad CSR, hash 0, lf out of range,
- * D different from a loaded snapshot; ECAPACITY: 2^31 or more resident
- * hashes, a set of more than 2^31 slots, or one that could not be built
- * even at four times the planned buckets; ENOMEM: out of device memory. */
+ * while building (up to 2 GiB of it stay with the handle for the next
+ * load).  EINVAL: bad CSR, hash 0, lf out of range, D different from a
+ * loaded snapshot; ECAPACITY: 2^31 or more resident hashes, a set of more
+ * than 2^31 slots, or one that could not be built even at four times the
+ * planned buckets; ENOMEM: out of device memory. */
 netkv_status netkv_cache_load(netkv_handle h, uint32_t n_decode, const uint64_t *hash_off,
                               const uint64_t *hashes, uint64_t n_hashes, float max_load_factor,
                               void *stream);

@@ -139,6 +139,7 @@ struct Table {
     const uint32_t *vals;   // [buckets][2] holder values
     const uint64_t *bits;   // [rows][bpitch] holder bitmaps (at least one row, row 0 of zeros if unused)
     uint32_t shift;         // 64 - log2(buckets)
+    uint32_t in_block;      // shift of the second bucket's offset (see buckets_of)
     uint32_t bpitch;        // 64-bit words per bitmap row, a multiple of 12
 };
 
@@ -163,19 +164,24 @@ __host__ __device__ inline uint64_t mix_hash(uint64_t h) { return h * kGolden; }
 __host__ __device__ inline uint64_t unmix_hash(uint64_t x) { return x * kGoldenInv; }
 
 // The two candidate buckets of hash h in a set of 2^b buckets (shift =
-// 64 - b): the top b bits of its mixed value, and a bucket of the same aligned
-// block of 2^11, never the same one, chosen by the top bits of a second
-// multiplicative hash (the multiplier of splitmix64 after an xor-shift).
-// Both use all 64 bits, so keys that agree in part of their bits still get
-// independent pairs.  A pair lies within 32 KiB, so that a workgroup can
-// build a block of the set in LDS.  (A chain of two multiplications, with its
+// 64 - b): the top b bits of its mixed value, and another bucket, never the
+// same one, chosen by the top bits of a second multiplicative hash (the
+// multiplier of splitmix64 after an xor-shift).  Both use all 64 bits, so keys
+// that agree in part of their bits still get independent pairs.
+// In a blocked set (in_block = block_shift(shift)) the second bucket is of the
+// same aligned block of 2^11, within 32 KiB, so that a workgroup can build a
+// block of the set in LDS.  In a whole set (in_block = shift) it is anywhere:
+// the form of resident sets whose mixed values crowd in few blocks, which the
+// second bucket then spreads over all of them.  (A chain of two multiplications, with its
 // temporaries, in the place of these two cost the kernels that look hashes up
 // beside other work more than the lookups: the sequential form's 239 -> 353
 // us, a batch of 4,096 16 -> 21 us.)
 constexpr uint32_t kBlockLog2 = 11;
-__host__ __device__ inline void buckets_of(uint64_t h, uint32_t shift, uint32_t &b1, uint32_t &b2) {
+__host__ __device__ inline uint32_t block_shift(uint32_t shift) {
+    return shift > 64 - kBlockLog2 ? shift : 64 - kBlockLog2;
+}
+__host__ __device__ inline void buckets_of(uint64_t h, uint32_t shift, uint32_t in_block, uint32_t &b1, uint32_t &b2) {
     b1 = (uint32_t)(mix_hash(h) >> shift);
-    const uint32_t in_block = shift > 64 - kBlockLog2 ? shift : 64 - kBlockLog2;
     b2 = b1 ^ ((uint32_t)(((h ^ (h >> 31)) * kMix64) >> in_block) | 1u);
 }
 
@@ -200,7 +206,7 @@ constexpr uint32_t kRowPad = 64u * 6u;
 __device__ inline uint32_t holder_lane(const Table &t, uint64_t h) {
     if (h == 0) return kNoHolder;
     uint32_t b1, b2;
-    buckets_of(h, t.shift, b1, b2);
+    buckets_of(h, t.shift, t.in_block, b1, b2);
     const ulonglong2 k1 = *(const ulonglong2 *)(t.keys + 2 * (uint64_t)b1);
     const ulonglong2 k2 = *(const ulonglong2 *)(t.keys + 2 * (uint64_t)b2);
     const uint64_t slot = k1.x == h ? 2 * (uint64_t)b1 : k1.y == h ? 2 * (uint64_t)b1 + 1
@@ -214,7 +220,7 @@ __device__ inline uint32_t holder_lane(const Table &t, uint64_t h) {
 __device__ inline uint32_t holder_lane_lean(const Table &t, uint64_t h) {
     if (h == 0) return kNoHolder;
     uint32_t b1, b2;
-    buckets_of(h, t.shift, b1, b2);
+    buckets_of(h, t.shift, t.in_block, b1, b2);
     uint64_t slot = 2 * (uint64_t)b1;
     ulonglong2 k = *(const ulonglong2 *)(t.keys + slot);
     if (k.x != h && k.y != h && k.x != 0 && k.y != 0) {
@@ -1204,7 +1210,7 @@ __device__ inline uint32_t write_lane(uint32_t v, uint32_t l, uint32_t old) {
 // both candidate buckets' keys and values).
 __device__ inline uint32_t holder_uniform(const Table &t, uint64_t h) {
     uint32_t b1, b2;
-    buckets_of(h, t.shift, b1, b2);
+    buckets_of(h, t.shift, t.in_block, b1, b2);
     const cptr<uint64_t> k = as_const(t.keys);
     const cptr<uint32_t> v = as_const(t.vals);
     const uint64_t k10 = k[2 * (uint64_t)b1], k11 = k[2 * (uint64_t)b1 + 1];
@@ -2749,13 +2755,19 @@ __global__ __launch_bounds__(256) void parts_kernel(const uint64_t *__restrict__
 }
 
 constexpr uint32_t kBlockSlots = 2u << kBlockLog2;   // slots of a block of the set
+// Most occupancy of a blocked set of several blocks.  Each block holds a random
+// share of the keys, a standard deviation of 0.014 of its slots at 0.80, and
+// has to stay below the two-choice threshold by itself: at 0.85 some block of
+// 2^11 exceeds it in sets of 128 blocks and more, at 0.83 in sets of some
+// 10,000; at 0.80 the threshold is seven standard deviations away.
+constexpr double kBlockedMost = 0.80;
 constexpr uint32_t kManyHolders = 0x80000000u;   // with the decode of one of them
 constexpr uint32_t kNobody = 0xFFFFFFFFu;
 
 // One workgroup per part: its distinct hashes to (okey, ohold) from the part's
 // start on, count[part] of them; sums of the counts, and of the hashes of
 // several holders, in cnt.  S slots hold the part's hashes at the load factor
-// of the set or less on average.
+// of the set or less on average; *flag gets 2 where they do not.
 template <uint32_t S>
 __global__ __launch_bounds__(1024) void dedupe_kernel(const uint64_t *__restrict__ key,
                                                       const uint32_t *__restrict__ dec,
@@ -2766,7 +2778,7 @@ __global__ __launch_bounds__(1024) void dedupe_kernel(const uint64_t *__restrict
                                                       uint32_t *__restrict__ flag) {
     __shared__ unsigned long long lk[S];
     __shared__ uint32_t lh[S];
-    __shared__ uint32_t n_out, n_many;
+    __shared__ uint32_t n_out, n_many, full;
     const uint32_t a = start[blockIdx.x], b = start[blockIdx.x + 1], tid = threadIdx.x;
     if (a == b) {
         if (tid == 0) count[blockIdx.x] = 0;
@@ -2776,7 +2788,7 @@ __global__ __launch_bounds__(1024) void dedupe_kernel(const uint64_t *__restrict
         lk[s] = 0;
         lh[s] = kNobody;
     }
-    if (tid == 0) n_out = n_many = 0;
+    if (tid == 0) n_out = n_many = full = 0;
     __syncthreads();
     for (uint32_t i = a + tid; i < b; i += blockDim.x) {
         const uint64_t y = key[i];
@@ -2787,11 +2799,15 @@ __global__ __launch_bounds__(1024) void dedupe_kernel(const uint64_t *__restrict
             unsigned long long cur = *(volatile unsigned long long *)&lk[s];
             if (cur == 0) cur = atomicCAS(&lk[s], 0ull, k);
             if (cur == 0 || cur == k) break;
+            // more distinct hashes than slots: the set is built whole instead
+            // (long probes ask for it, so that the part ends soon)
+            if (probe >= 64 && *(volatile uint32_t *)&full) break;
         }
         if (probe == S) {
+            full = 1;
             atomicOr(flag, 2u);
-            continue;
         }
+        if (probe >= 64 && *(volatile uint32_t *)&full) break;
         uint32_t h = *(volatile uint32_t *)&lh[s];
         if (h == kNobody) h = atomicCAS(&lh[s], kNobody, d);
         if (h != kNobody && !(h & kManyHolders) && h != d) atomicOr(&lh[s], kManyHolders);
@@ -2825,7 +2841,7 @@ __global__ __launch_bounds__(1024) void dedupe_kernel(const uint64_t *__restrict
 // most 64 MiB, a quarter of the last-level cache.
 constexpr uint64_t kSharedMaxRows = 1ull << 20;
 
-// Cuckoo insertion of distinct hashes into a block of the set in LDS.  A key
+// Cuckoo insertion of distinct hashes into a block of the set (in LDS), or into the whole set.  A key
 // goes to an empty slot of either candidate bucket (compare-and-swap 0 ->
 // key); when all four slots are taken it displaces the key of a random slot by
 // atomic exchange (a random walk: a fresh key picks either bucket, a displaced
@@ -2841,13 +2857,14 @@ __device__ inline bool try_place(unsigned long long *bk, unsigned long long key)
 
 // Place the key of mixed value x in the block of 2^lg buckets `tab`; false
 // when the walk did not end.
-__device__ inline bool cuckoo_place(unsigned long long *tab, uint32_t lg, uint32_t shift, unsigned long long x) {
+__device__ inline bool cuckoo_place(unsigned long long *tab, uint32_t lg, uint32_t shift, uint32_t in_block,
+                                    unsigned long long x) {
     const uint32_t mask = (1u << lg) - 1u;
     uint32_t from = 0xFFFFFFFFu;   // bucket the carried key was displaced from
     uint32_t rnd = (uint32_t)(x >> 20);
     for (uint32_t kick = 0; kick < kMaxKicks; ++kick) {
         uint32_t b1, b2;
-        buckets_of(unmix_hash(x), shift, b1, b2);
+        buckets_of(unmix_hash(x), shift, in_block, b1, b2);
         b1 &= mask;
         b2 &= mask;
         if (try_place(tab + 2 * b1, x) || try_place(tab + 2 * b2, x)) return true;
@@ -2866,10 +2883,11 @@ __device__ inline bool cuckoo_place(unsigned long long *tab, uint32_t lg, uint32
 }
 
 // The slot of mixed value x in the block, or ~0.
-__device__ inline uint32_t slot_of(const unsigned long long *tab, uint32_t lg, uint32_t shift, unsigned long long x) {
+__device__ inline uint32_t slot_of(const unsigned long long *tab, uint32_t lg, uint32_t shift, uint32_t in_block,
+                                   unsigned long long x) {
     const uint32_t mask = (1u << lg) - 1u;
     uint32_t b1, b2;
-    buckets_of(unmix_hash(x), shift, b1, b2);
+    buckets_of(unmix_hash(x), shift, in_block, b1, b2);
     b1 &= mask;
     b2 &= mask;
     return tab[2 * b1] == x ? 2 * b1 : tab[2 * b1 + 1] == x ? 2 * b1 + 1
@@ -2902,7 +2920,7 @@ __global__ __launch_bounds__(1024) void build_kernel(Build u) {
     __shared__ unsigned long long lk[S];
     __shared__ uint32_t lv[S];
     __shared__ uint32_t n_many, n_used, base;
-    const uint32_t tid = threadIdx.x, shift = 64 - u.log2b, n_slot = 2u << u.lg;
+    const uint32_t tid = threadIdx.x, shift = 64 - u.log2b, in_block = block_shift(shift), n_slot = 2u << u.lg;
     const uint64_t b0 = (uint64_t)blockIdx.x << u.lg;   // the block's first bucket
     const uint32_t p0 = u.log2b >= u.bits ? (uint32_t)(b0 >> (u.log2b - u.bits)) : (uint32_t)(b0 << (u.bits - u.log2b));
     const uint64_t b1 = b0 + (1ull << u.lg);
@@ -2928,7 +2946,7 @@ __global__ __launch_bounds__(1024) void build_kernel(Build u) {
     each(false, [&](uint32_t i) {
         const unsigned long long x = u.dkey[i];
         if (!mine(x)) return;
-        if (!cuckoo_place(lk, u.lg, shift, x)) atomicOr(u.flag, kErrTableFull);
+        if (!cuckoo_place(lk, u.lg, shift, in_block, x)) atomicOr(u.flag, kErrTableFull);
         if (u.dhold[i] & kManyHolders) atomicAdd(&n_many, 1u);
     });
     __syncthreads();
@@ -2950,7 +2968,7 @@ __global__ __launch_bounds__(1024) void build_kernel(Build u) {
                 ((uint32_t *)(u.shared + j))[2] = v;
             }
         }
-        const uint32_t s = slot_of(lk, u.lg, shift, x);
+        const uint32_t s = slot_of(lk, u.lg, shift, in_block, x);
         if (s != 0xFFFFFFFFu) lv[s] = v;   // (else the walk failed, which was flagged)
     });
     __syncthreads();
@@ -2964,7 +2982,7 @@ __global__ __launch_bounds__(1024) void build_kernel(Build u) {
     each(true, [&](uint32_t i) {
         const unsigned long long x = part_value(u.key[i], u.bits);
         if (!mine(x)) return;
-        const uint32_t s = slot_of(lk, u.lg, shift, x);
+        const uint32_t s = slot_of(lk, u.lg, shift, in_block, x);
         const uint32_t v = s != 0xFFFFFFFFu ? lv[s] : kHeldOne;
         if (v < kHeldOne) {
             const uint32_t d = u.dec[i];
@@ -2972,6 +2990,87 @@ __global__ __launch_bounds__(1024) void build_kernel(Build u) {
                                   __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     });
+}
+
+// The whole set, built in memory from the pairs sorted by all bits of their
+// keys, so that the holders of one hash form a run whose first element
+// ("head") stands for it: the form of resident sets that the blocks cannot
+// hold (five times the blocked build's time for 50.3 M pairs).
+__device__ inline bool run_head(const uint64_t *__restrict__ key, uint64_t i) {
+    return i == 0 || key[i] != key[i - 1];
+}
+
+// Least and largest holder of the run that starts at i, and its end.
+__device__ inline uint64_t run_span(const uint64_t *__restrict__ key, const uint32_t *__restrict__ dec, uint64_t n,
+                                    uint64_t i, uint32_t &dmin, uint32_t &dmax) {
+    dmin = dmax = dec[i];
+    uint64_t e = i + 1;
+    for (; e < n && key[e] == key[i]; ++e) {
+        dmin = min(dmin, dec[e]);
+        dmax = max(dmax, dec[e]);
+    }
+    return e;
+}
+
+// cnt[0] += distinct hashes, cnt[1] += hashes with two or more holders.
+__global__ __launch_bounds__(256) void whole_count_kernel(const uint64_t *__restrict__ key,
+                                                          const uint32_t *__restrict__ dec, uint64_t n,
+                                                          unsigned long long *__restrict__ cnt) {
+    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    uint32_t heads = 0, many = 0;
+    for (; i < n; i += stride) {
+        if (!run_head(key, i)) continue;
+        uint32_t dmin, dmax;
+        run_span(key, dec, n, i, dmin, dmax);
+        ++heads;
+        many += dmin != dmax ? 1u : 0u;
+    }
+    heads = wave_sum_u32(heads);
+    many = wave_sum_u32(many);
+    if ((threadIdx.x % kWave) == 0) {
+        if (heads) atomicAdd(cnt, (unsigned long long)heads);
+        if (many) atomicAdd(cnt + 1, (unsigned long long)many);
+    }
+}
+
+__global__ __launch_bounds__(256) void whole_insert_kernel(Build u, uint64_t n) {
+    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint32_t shift = 64 - u.log2b;
+    for (; i < n; i += stride)
+        if (run_head(u.key, i) && !cuckoo_place((unsigned long long *)u.keys, u.log2b, shift, shift,
+                                                part_value(u.key[i], u.bits)))
+            atomicOr(u.flag, kErrTableFull);
+}
+
+// Holder values, once every key has its slot; each bitmap row is written by
+// the one thread of its run.
+__global__ __launch_bounds__(256) void whole_value_kernel(Build u, uint64_t n) {
+    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint32_t shift = 64 - u.log2b;
+    for (; i < n; i += stride) {
+        if (!run_head(u.key, i)) continue;
+        uint32_t dmin, dmax;
+        const uint64_t e = run_span(u.key, u.dec, n, i, dmin, dmax);
+        uint32_t v = kHeldOne | dmin;
+        if (dmin != dmax) {
+            v = atomicAdd(u.rows_used, 1u);
+            uint64_t *row = u.rows + (uint64_t)v * u.bpitch;
+            for (uint64_t x = i; x < e; ++x) row[u.dec[x] / 64u] |= 1ull << (u.dec[x] % 64u);
+        }
+        const uint32_t s = slot_of((const unsigned long long *)u.keys, u.log2b, shift, shift,
+                                   part_value(u.key[i], u.bits));
+        if (s != 0xFFFFFFFFu) u.vals[s] = v;   // (else the walk failed, which was flagged)
+    }
+}
+
+// The set's mixed values back to hashes, once nothing looks them up.
+__global__ __launch_bounds__(256) void whole_unmix_kernel(uint64_t *__restrict__ keys, uint64_t n) {
+    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (; i < n; i += stride) keys[i] = unmix_hash(keys[i]);
 }
 
 __global__ void fill_u64_kernel(uint64_t *__restrict__ p, uint64_t n, uint64_t v) {
@@ -3797,6 +3896,7 @@ struct netkv_ctx {
     uint64_t *bits = nullptr;    // [rows][bpitch] holder bitmaps
     uint64_t table_bytes = 0, buckets = 0, rows = 0, distinct = 0;
     uint32_t log2b = 0, bpitch = 0;
+    bool whole = false;          // a whole set, not a blocked one (see buckets_of)
     uint64_t bits_cap = 0;       // words allocated
     // the cache load's work buffer, kept from load to load
     uint8_t *load_buf = nullptr;
@@ -3960,6 +4060,7 @@ Table make_table(netkv_handle h) {
     t.vals = h->tvals;
     t.bits = h->bits;
     t.shift = 64 - h->log2b;
+    t.in_block = h->whole ? t.shift : block_shift(t.shift);
     t.bpitch = h->bpitch;
     return t;
 }
@@ -5257,8 +5358,8 @@ netkv_status netkv_cache_load(netkv_handle h, uint32_t n_decode, const uint64_t 
     // reads its groups' C words inside the row, at 8 * C-byte alignment
     const uint64_t bwords = ((uint64_t)n_decode + 63) / 64;
     const uint32_t bpitch = (uint32_t)((bwords + 11) / 12 * 12);
-    // two slots per bucket; two-choice cuckoo sets of 2-slot buckets stay
-    // buildable well above load factor 0.5, and are capped at 0.85
+    // two slots per bucket; two-choice cuckoo sets of 2-slot buckets can be
+    // built up to an occupancy of about 0.897, and are capped at 0.85
     const double lf = std::min(0.85, (double)max_load_factor);
     auto log2_buckets = [&](uint64_t n, double f) {
         const double need = std::ceil((double)n / (2.0 * f));
@@ -5362,12 +5463,50 @@ netkv_status netkv_cache_load(netkv_handle h, uint32_t n_decode, const uint64_t 
     }
     if (e != hipSuccess) return fail(h, NETKV_EDEVICE, "index build failed: %s", hipGetErrorString(e));
     if (c.flag & 1u) return fail(h, NETKV_EINVAL, "cache contains the reserved hash value 0");
-    if (c.flag) return fail(h, NETKV_ECAPACITY, "index build could not place every hash");
+    // the whole set's pairs: sorted by all bits, once; then key / dec hold them
+    bool whole = false;
+    auto sort_whole = [&]() -> netkv_status {
+        if (whole) return NETKV_OK;
+        whole = true;
+        size_t wb = 0;
+        HIPCHK(h, rocprim::radix_sort_pairs(nullptr, wb, (const uint64_t *)key2, key, (const uint32_t *)dec2, dec,
+                                            (uint32_t)total, 0, 64, st));
+        uint8_t *tmp = buf + o_tmp, *own = nullptr;
+        if (wb > std::max<size_t>(tb, 16)) {
+            if (dalloc(own, wb) != hipSuccess) return fail(h, NETKV_ENOMEM, "sort scratch allocation failed");
+            tmp = own;
+        }
+        hipError_t e = rocprim::radix_sort_pairs(tmp, wb, (const uint64_t *)key2, key, (const uint32_t *)dec2, dec,
+                                                 (uint32_t)total, 0, 64, st);
+        Counters z{};
+        z.rows = 1;
+        if (e == hipSuccess) e = hipMemcpyAsync(dc, &z, sizeof z, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(whole_count_kernel, dim3(grid_for(total, 256, 16384)), dim3(256), 0, st,
+                               (const uint64_t *)key, (const uint32_t *)dec, total, dc->n);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) e = hipMemcpyAsync(&c, dc, sizeof c, hipMemcpyDeviceToHost, st);
+        const hipError_t e2 = hipStreamSynchronize(st);   // (the buffer's uses end here)
+        if (e == hipSuccess) e = e2;
+        dfree(own);
+        if (e != hipSuccess) return fail(h, NETKV_EDEVICE, "index build failed: %s", hipGetErrorString(e));
+        return NETKV_OK;
+    };
+    netkv_status ns;
+    if (c.flag && (ns = sort_whole())) return ns;   // a part was too full
     const uint64_t distinct = c.n[0], rows = c.n[1] + 1;   // row 0: all zero
     if (rows >= (uint64_t)kHeldOne)
         return fail(h, NETKV_ECAPACITY, "more than 2^31 - 2 hashes held by several decodes");
-    uint32_t log2b = log2_buckets(distinct, lf);
-    if (log2b > 30) return fail(h, NETKV_ECAPACITY, "the index would need more than 2^31 slots");
+    const uint32_t planned = log2_buckets(distinct, lf);
+    if (planned > 30) return fail(h, NETKV_ECAPACITY, "the index would need more than 2^31 slots");
+    // a blocked set beyond kBlockedMost takes twice the buckets, or is a whole
+    // one where the set can have no more
+    uint32_t log2b = planned;
+    if (!whole && planned > kBlockLog2 && (double)distinct > kBlockedMost * 2.0 * (double)(1ull << planned)) {
+        if (planned < 30) ++log2b;
+        else if ((ns = sort_whole())) return ns;
+    }
     // the old index is given up here; its buffers serve the new one where they
     // have its size (else they are released first: the new one may be large)
     h->have_cache = false;
@@ -5376,70 +5515,98 @@ netkv_status netkv_cache_load(netkv_handle h, uint32_t n_decode, const uint64_t 
         dfree(h->bits);
         h->bits_cap = 0;
     }
-    if (h->log2b != log2b) {
-        dfree(h->table);
-        dfree(h->tvals);
-        h->log2b = 0;
-    }
     const bool shared = rows > 1 && rows <= kSharedMaxRows;
     uint32_t lb = 3;
     while ((1ull << lb) < 3 * rows) ++lb;
     if (h->sh_log2b != lb || !shared) dfree(h->sh_tab);
+    auto drop_table = [&]() {
+        dfree(h->table);
+        dfree(h->tvals);
+        h->log2b = 0;
+    };
+    auto take_table = [&]() {   // 2^log2b buckets
+        if (h->log2b != log2b) drop_table();
+        if (h->table && h->tvals) return true;
+        if (dalloc(h->table, 2ull << log2b) != hipSuccess || dalloc(h->tvals, 2ull << log2b) != hipSuccess) {
+            (void)hipGetLastError();
+            drop_table();
+            return false;
+        }
+        h->log2b = log2b;
+        return true;
+    };
+    if (h->log2b != log2b) drop_table();
     if (!h->bits) {
         if (dalloc(h->bits, row_words) != hipSuccess)
             return fail(h, NETKV_ENOMEM, "holder bitmap allocation of %llu bytes failed",
                         (unsigned long long)(8 * row_words));
         h->bits_cap = row_words;
     }
-    // build at the planned size; should a build fail to place every key (a
-    // random walk that did not end), rebuild with twice the buckets, twice
-    uint64_t nbk = 0;
-    for (int attempt = 0;; ++attempt) {
-        nbk = 1ull << log2b;
-        if (!h->table || !h->tvals) {
-            if (dalloc(h->table, 2 * nbk) != hipSuccess || dalloc(h->tvals, 2 * nbk) != hipSuccess) {
-                dfree(h->table);
-                dfree(h->tvals);
-                h->log2b = 0;
-                return fail(h, NETKV_ENOMEM, "index allocation of %llu bytes failed", (unsigned long long)(24 * nbk));
+    // should a blocked build fail to place every key (a random walk that did
+    // not end), or have no memory for twice the buckets, the set is built
+    // whole at the planned size, and where that fails with twice the buckets,
+    // twice
+    for (int attempt = 0;;) {
+        if (!take_table()) {
+            if (!whole && log2b > planned) {
+                if ((ns = sort_whole())) return ns;
+                log2b = planned;
+                continue;
             }
-            h->log2b = log2b;
+            return fail(h, NETKV_ENOMEM, "index allocation of %llu bytes failed", (unsigned long long)(24ull << log2b));
         }
         // the shared index; without it (too many shared hashes to stay in
-        // cache, no memory) lookups go to the whole index
-        if (shared && !h->sh_tab) {
+        // cache, a whole set, whose hashes may crowd in few slots, no memory)
+        // lookups go to the set
+        if (whole) dfree(h->sh_tab);
+        else if (shared && !h->sh_tab) {
             if (dalloc(h->sh_tab, 1ull << lb) != hipSuccess) (void)hipGetLastError();
             h->sh_log2b = lb;
         }
+        const uint64_t nbk = 1ull << log2b;
         c.rows = 1;
         c.flag = 0;
         e = hipMemsetAsync(h->bits, 0, 8 * row_words, st);
         if (e == hipSuccess && h->sh_tab) e = hipMemsetAsync(h->sh_tab, 0, 16ull << lb, st);
-        if (e == hipSuccess && !total) e = hipMemsetAsync(h->table, 0, 16 * nbk, st);
+        if (e == hipSuccess && (whole || !total)) e = hipMemsetAsync(h->table, 0, 16 * nbk, st);
         if (e == hipSuccess) e = hipMemcpyAsync(dc, &c, sizeof c, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess && total) {
-            const uint32_t lg = std::min(log2b, std::max(kBlockLog2, std::min(part_lg, log2b > bits ? log2b - bits : 0u)));
-            const Build u{key2, dec2, key, dec, start, count, bits, lg, log2b, h->table, h->tvals, h->bits, bpitch,
-                          h->sh_tab, 64u - lb, (1u << lb) - 1u, &dc->rows, &dc->flag};
+        const uint32_t lg = std::min(log2b, std::max(kBlockLog2, std::min(part_lg, log2b > bits ? log2b - bits : 0u)));
+        Build u{key2, dec2, key, dec, start, count, bits, lg, log2b, h->table, h->tvals, h->bits, bpitch,
+                h->sh_tab, 64u - lb, (1u << lb) - 1u, &dc->rows, &dc->flag};
+        if (e == hipSuccess && total && !whole) {
             const uint32_t grid = 1u << (log2b - lg);
             if (lg > kBlockLog2)
                 hipLaunchKernelGGL((build_kernel<2 * kBlockSlots>), dim3(grid), dim3(1024), 0, st, u);
             else
                 hipLaunchKernelGGL((build_kernel<kBlockSlots>), dim3(grid), dim3(512), 0, st, u);
             e = hipGetLastError();
+        } else if (e == hipSuccess && total) {
+            u.key = key;
+            u.dec = dec;
+            const dim3 grid(grid_for(total, 256, 16384));
+            hipLaunchKernelGGL(whole_insert_kernel, grid, dim3(256), 0, st, u, total);
+            hipLaunchKernelGGL(whole_value_kernel, grid, dim3(256), 0, st, u, total);
+            hipLaunchKernelGGL(whole_unmix_kernel, dim3(grid_for(2 * nbk, 256, 16384)), dim3(256), 0, st, h->table,
+                               2 * nbk);
+            e = hipGetLastError();
         }
         if (e == hipSuccess) e = hipMemcpyAsync(&c, dc, sizeof c, hipMemcpyDeviceToHost, st);
         const hipError_t e2 = hipStreamSynchronize(st);
         if (e == hipSuccess) e = e2;
-        if (e != hipSuccess || !c.flag || attempt == 2 || log2b >= 30) break;
-        dfree(h->table);
-        dfree(h->tvals);
-        h->log2b = 0;
-        ++log2b;
+        if (e != hipSuccess || !c.flag) break;
+        if (!whole) {
+            if ((ns = sort_whole())) return ns;
+            log2b = planned;
+        } else {
+            if (attempt++ == 2 || log2b >= 30) break;
+            ++log2b;
+        }
     }
     if (e != hipSuccess || c.flag)
         return e != hipSuccess ? fail(h, NETKV_EDEVICE, "index build failed: %s", hipGetErrorString(e))
                                : fail(h, NETKV_ECAPACITY, "index build could not place every hash");
+    const uint64_t nbk = 1ull << log2b;
+    h->whole = whole;
     h->buckets = nbk;
     h->bpitch = bpitch;
     h->rows = rows;

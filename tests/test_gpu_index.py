@@ -43,7 +43,7 @@ def _sets(form, rng):
         return [_u64(rng, 700) for _ in range(D)], 0.02
     if form == "dense":
         return [_u64(rng, 9100) for _ in range(D)], 0.85
-    if form == "large":       # parts of 2^12 buckets: three sort digits otherwise
+    if form == "large":       # parts told apart by two sort digits
         x = _u64(rng, 200000)
         return [np.concatenate([_u64(rng, 1600000), rng.choice(x, 50000)]) for _ in range(D)], 0.5
     raise AssertionError(form)
@@ -52,7 +52,7 @@ def _sets(form, rng):
 FORMS = ["empty", "one", "part", "same", "sequential", "sparse", "dense", "large"]
 
 
-def _check(nk, sel, snap, sets, lf, rng, host):
+def _check(nk, sel, snap, sets, lf, rng, host, also=()):
     off = np.zeros(D + 1, np.uint64)
     off[1:] = np.cumsum([len(x) for x in sets])
     lead = 3   # the first set need not start at 0
@@ -75,7 +75,8 @@ def _check(nk, sel, snap, sets, lf, rng, host):
         buckets *= 2
     assert ci["index_slots"] in (2 * buckets, 4 * buckets, 8 * buckets)
     # one-block requests: resident hashes of every kind, and others
-    q = np.concatenate([rng.choice(uniq, 1200) if len(uniq) else uniq, _u64(rng, 300), np.zeros(1, np.uint64)])
+    q = np.concatenate([rng.choice(uniq, 1200) if len(uniq) else uniq, _u64(rng, 300), np.zeros(1, np.uint64),
+                        np.asarray(also, np.uint64)])
     bt = int(snap["block_tokens"])
     req = dict(prefill=np.zeros(len(q), np.uint32), len_tokens=np.full(len(q), bt, np.uint32),
                hash_off=np.arange(len(q) + 1, dtype=np.uint64), hashes=q)
@@ -147,4 +148,103 @@ def test_load_waits_for_selections_on_other_streams(nk):
     for o in outs:
         assert np.array_equal(nk.to_numpy(o["idx"]), want[0])
         assert np.array_equal(nk.to_numpy(o["score"]).view(np.uint32), want[1].view(np.uint32))
+    sel.close()
+
+
+def _crowd(n, first=0):
+    """Hashes whose mixed values (the hash times the odd multiplier 0x9E37...15)
+    are neighbours: all of them fall in one part and one block of the set."""
+    inv = np.uint64(pow(0x9E3779B97F4A7C15, -1, 1 << 64))
+    with np.errstate(over="ignore"):
+        return (np.arange(1, n + 1, dtype=np.uint64) + (np.uint64(first) << np.uint64(40))) * inv
+
+
+@pytest.mark.parametrize("crowd", [3000, 5000, 20000])
+def test_crowded_sets(nk, crowd):
+    """Hashes that crowd in one block among ordinary ones: more of them than the
+    block's second buckets can take (3,000) and than the part has slots (5,000
+    and 20,000).  Such a set is built whole: membership, and the selections
+    that look hashes up in their own ways (direct, bounded, sequential) against
+    the ordering pipeline; then an ordinary set on the same handle."""
+    print("[gpu-case] crowded set", crowd, flush=True)
+    rng = np.random.default_rng(17)
+    cfg = W.scaled(W.CONFIGS["c0"], n_requests=8, cache_per_decode=64)
+    snap = W.make_snapshot(cfg, 3)
+    x = _crowd(crowd)
+    sets = [np.concatenate([_u64(rng, 22000), x[d * crowd // 64:d * crowd // 64 + crowd // 4]]) for d in range(D)]
+    sel = nk.Selector(0)
+    sel.load_snapshot(snap)
+    also = np.concatenate([rng.choice(x, 800), _crowd(300, 1)])
+    _check(nk, sel, snap, sets, 0.5, rng, True, also)
+    _check(nk, sel, snap, sets, 0.5, rng, False, also)
+    bt, n = int(snap["block_tokens"]), 20000
+    runs = [sets[rng.integers(D)][a:a + int(rng.integers(1, 40))] for a in rng.integers(21900, 22000 + crowd // 4 - 40, n)]
+    ln = np.array([len(r) for r in runs])
+    req = dict(prefill=rng.integers(0, cfg.n_prefill, n).astype(np.uint32), len_tokens=(ln * bt).astype(np.uint32),
+               hash_off=np.concatenate([[0], np.cumsum(ln)]).astype(np.uint64), hashes=np.concatenate(runs))
+    for m in (2000, n):
+        part = dict(req, prefill=req["prefill"][:m], len_tokens=req["len_tokens"][:m], hash_off=req["hash_off"][:m + 1],
+                    hashes=req["hashes"][:int(req["hash_off"][m])])
+        rd = nk.requests_to_device(part, sel.device)
+        got = []
+        for run_len in (0, 8):   # an explicit run length asks for the ordering pipeline
+            nk.netkv_set_option(sel.h, nk.NETKV_OPT_RUN_LEN, run_len)
+            o, q = sel.select(rd, k=3), sel.select_sequential(rd, 16)
+            got.append([nk.to_numpy(v[key]).view(np.uint32).copy() for v in (o, q) for key in ("idx", "score")])
+        nk.netkv_set_option(sel.h, nk.NETKV_OPT_RUN_LEN, 0)
+        sel.sync_errors()
+        assert all(np.array_equal(a, b) for a, b in zip(*got))
+    _check(nk, sel, snap, [rng.permutation(s[:9000]) for s in sets], 0.5, rng, False)
+    sel.close()
+
+
+def _windows(dev, width, stride):
+    """Per decode a window of `width` of a sequence of distinct hashes (the
+    finaliser of splitmix64 of the position, a bijection), `stride` apart."""
+    x = torch.arange(1, (D - 1) * stride + width + 1, device=dev)
+    for s, m in ((30, 0xBF58476D1CE4E5B9), (27, 0x94D049BB133111EB)):
+        x = (x ^ ((x >> s) & ((1 << (64 - s)) - 1))) * (m - (1 << 64))
+    x = x ^ ((x >> 31) & ((1 << 33) - 1))
+    return x, x.unfold(0, width, stride).reshape(-1)
+
+
+@pytest.mark.parametrize("form", ["0.79", "0.82", "0.849", "parts of 2^12 buckets"])
+def test_large_sets(nk, form):
+    """Sets of thousands of blocks near the largest occupancy: as planned up to
+    0.80, twice the buckets beyond; and one of more than 2^27 hashes, whose
+    parts and blocks are of 2^12 buckets."""
+    print("[gpu-case] large set", form, flush=True)
+    dev = torch.device("cuda", 0)
+    cfg = W.scaled(W.CONFIGS["c0"], n_requests=8, cache_per_decode=64)
+    snap = W.make_snapshot(cfg, 3)
+    if form.startswith("0."):
+        lf, occ = 0.85, float(form)
+        stride = int(occ * (1 << 23)) // D
+        width, slots = stride, (1 << 23) * (2 if occ > 0.8 else 1)
+    else:
+        lf, stride, width, slots = 0.5, 2850000, 2950000, 1 << 29
+    seq, hashes = _windows(dev, width, stride)
+    off = torch.arange(D + 1, device=dev) * width
+    sel = nk.Selector(0)
+    sel.load_snapshot(snap)
+    nk.netkv_cache_load(sel.h, D, off.view(torch.uint64), hashes.view(torch.uint64), lf, dev)
+    n = len(seq)
+    ci = nk.netkv_cache_info(sel.h)
+    assert ci["distinct_hashes"] == n and ci["index_slots"] == slots
+    assert ci["shared_hashes"] == (D - 1) * (width - stride)
+    g = torch.Generator(device=dev)
+    g.manual_seed(4)
+    at = torch.randint(0, n, (40000,), generator=g, device=dev)
+    q = torch.cat([seq[at], torch.randint(1, 1 << 62, (2000,), generator=g, device=dev)])
+    m = len(q)
+    req = dict(prefill=torch.zeros(m, dtype=torch.int32, device=dev).view(torch.uint32),
+               len_tokens=torch.full((m,), int(snap["block_tokens"]), dtype=torch.int32, device=dev).view(torch.uint32),
+               hash_off=torch.arange(m + 1, device=dev).view(torch.uint64), hashes=q.view(torch.uint64))
+    out = sel.select(req, k=1, pairs=True)
+    sel.sync_errors()
+    got = nk.to_numpy(out["pairs"]["prefix_blocks"]).reshape(m, D)
+    pos, d = at.cpu().numpy()[:, None], np.arange(D)[None, :]
+    want = np.zeros((m, D), got.dtype)
+    want[:len(pos)] = (pos >= d * stride) & (pos < d * stride + width)
+    assert np.array_equal(got, want)
     sel.close()
