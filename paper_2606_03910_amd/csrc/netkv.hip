@@ -2149,7 +2149,13 @@ __global__ __launch_bounds__(kBlock) void match_kernel(Snap s, Table t, Shared s
 // instructions for short runs, 33 for long ones, and no scalar ones (a loop
 // over the blocks with read-lanes took 3 vector and 8 scalar instructions a
 // block, and the scalar unit bound the kernel).
-__device__ inline uint32_t leading_words(uint64_t *wds, uint64_t word, uint32_t lane, bool few) {
+// The array holds 32-bit words, low and high halves in turn, as they are read:
+// stored as 64-bit ones, the compiler may take stores and reads as unrelated.
+// The fences order the lanes' accesses around the exchange (one wavefront's
+// LDS operations execute in order, so they cost no instruction).
+__device__ inline void lane_phase() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+__device__ inline uint32_t leading_words(uint32_t *wds, uint64_t word, uint32_t lane, bool few) {
     uint32_t lo = (uint32_t)word, hi = (uint32_t)(word >> 32);
     lo &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x111, 0xF, 0xF, false);   // row_shr 1
     hi &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)hi, 0x111, 0xF, 0xF, false);
@@ -2165,10 +2171,11 @@ __device__ inline uint32_t leading_words(uint64_t *wds, uint64_t word, uint32_t 
         lo &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x143, 0xC, 0xF, false);   // row_bcast 31
         hi &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)hi, 0x143, 0xC, 0xF, false);
     }
-    __builtin_amdgcn_wave_barrier();
-    wds[lane] = ((uint64_t)hi << 32) | lo;
-    __builtin_amdgcn_wave_barrier();
-    const uint32_t *half = (const uint32_t *)wds + (lane >> 5);
+    lane_phase();
+    wds[2 * lane] = lo;
+    wds[2 * lane + 1] = hi;
+    lane_phase();
+    const uint32_t *half = wds + (lane >> 5);
     const uint32_t sh = lane & 31u;
     uint32_t j = 0;
     if (!few) {
@@ -2192,7 +2199,7 @@ __global__ __launch_bounds__(kBlock) void bounded_kernel(Snap s, Table t, Reqs r
                                                          const uint32_t *__restrict__ mm, uint32_t per, uint32_t k_out,
                                                          int32_t *__restrict__ out_idx, float *__restrict__ out_score) {
     constexpr int Q = 4;
-    __shared__ uint64_t lds[kWavesPerBlock][Q][kWave];
+    __shared__ __align__(8) uint32_t lds[kWavesPerBlock][Q][2 * kWave];
     const uint32_t lane = threadIdx.x % kWave;
     const uint32_t wv = wave_index();
     const uint64_t first = ((uint64_t)blockIdx.x * kWavesPerBlock + wv) * per;
