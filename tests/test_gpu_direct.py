@@ -180,3 +180,48 @@ def test_direct_forms(D):
             print("[direct] forms D", D, "policy", policy, "routes", routes, flush=True)
             assert all(np.array_equal(a, b) for a, b in zip(got, want))
     sel.close()
+
+
+@pytest.mark.parametrize("D", [48, 5440, 5600])
+@pytest.mark.parametrize("R", [1, 64, 5000])
+def test_commit_forms(D, R):
+    """The between-batch update against the oracle on pools whose sums fit a
+    workgroup's LDS (12 D + 16 P bytes of 64 KiB: 5,440 decodes and 5 prefills
+    take 65,360) and on one beyond, with rejected requests; twice, so that the
+    admitted bytes come back; then an invalid request and an index past the
+    pool."""
+    import oracle
+    from paper_2606_03910_amd import netkv
+    snap, cache, req = _inputs(D, R, D + R, bt=64)
+    P = snap["n_prefill"]
+    assert P == 5
+    rng = np.random.default_rng(R)
+    sel = _handle(netkv, snap, cache)
+    oc = oracle.Cache(cache, n_threads=8)
+    state = dict(n_inflight=snap["n_inflight"].copy(), queue_depth=snap["queue_depth"].copy(),
+                 free_mem=snap["free_mem"].copy(), admitted_prev=np.zeros(D, np.uint64))
+    rd = netkv.requests_to_device(req, sel.device)
+    for step in range(2):
+        idx = rng.integers(-1, D, R).astype(np.int32)
+        idx[:R // 2] = rng.integers(0, 3, R // 2)   # many on few counters
+        print("[gpu-case] commit D", D, "R", R, "step", step, flush=True)
+        sel.commit(rd, netkv.to_device(idx, sel.device), 16, 7)
+        sel.sync_errors()
+        state = oracle.commit(dict(snap, **{k: state[k] for k in ("n_inflight", "queue_depth", "free_mem")}), oc, req, idx,
+                              16, 7, state)
+        got = sel.state()
+        for key in ("n_inflight", "queue_depth", "free_mem", "admitted_prev"):
+            np.testing.assert_array_equal(got[key], state[key], err_msg=key)
+    # what the update refuses changes nothing else
+    before = sel.state()
+    bad = dict(req, prefill=req["prefill"].copy())
+    bad["prefill"][0] = 1 << 20
+    idx = np.full(R, -1, np.int32)
+    idx[0], idx[-1] = 0, D if R > 1 else 0
+    sel.commit(netkv.requests_to_device(bad, sel.device), netkv.to_device(idx, sel.device), 16, 0)
+    with pytest.raises(netkv.NetKVError):
+        sel.sync_errors()
+    got = sel.state()
+    assert np.all(got["n_inflight"] == 0) and np.array_equal(got["queue_depth"], before["queue_depth"])
+    assert np.all(got["admitted_prev"] == 0)
+    sel.close()
