@@ -421,7 +421,10 @@ netkv_status netkv_selection_bytes(netkv_handle h, const netkv_requests_t *req, 
  * there.  fp64 throughout; results are bit-identical to a sequential
  * implementation of the same operations.
  *
- * n_inst independent instances, one workgroup each: instance i holds flows
+ * n_inst independent instances, one wavefront or workgroup each (instances of
+ * either kind run side by side, the latter on the handle's second stream,
+ * forked from `stream` and joined back to it by events within the call):
+ * instance i holds flows
  * flow_off[i] .. flow_off[i+1]-1 (n_flows = flow_off[n_inst] in all) on
  * links 0 .. n_links-1 with capacities cap[i * n_links + l] (bytes/s,
  * finite and > 0).  Flow f crosses the links path[path_off[f] ..
@@ -439,7 +442,7 @@ netkv_status netkv_selection_bytes(netkv_handle h, const netkv_requests_t *req, 
  * segmented radix sort), and the instances are started heaviest first (by
  * the sum over their flows of bytes over the least capacity on the path;
  * rocPRIM's radix sort), which only changes where each one runs.  Grows a
- * work buffer of the handle to 38 B per flow, 24 B per instance and the
+ * work buffer of the handle to 38 B per flow, 112 B per instance and the
  * two sorts' temporary storage, plus, for more
  * than 2,048 links (whose state then lives in device memory instead of
  * LDS), 17 B per link and instance.  EINVAL: NULL arrays, n_links = 0,

@@ -4965,6 +4965,12 @@ int netkv_internal_device(netkv_handle h) { return h->device; }
 
 uint32_t *netkv_internal_errword(netkv_handle h) { return h->errword; }
 
+void netkv_internal_side(netkv_handle h, hipStream_t *side, hipEvent_t *fork, hipEvent_t *join) {
+    *side = h->side;
+    *fork = h->ev_inv_fork;
+    *join = h->ev_inv_join;
+}
+
 hipError_t netkv_internal_flow_buffer(netkv_handle h, uint64_t bytes, void **out) {
     if (bytes > h->flow_buf_bytes) {
         if (h->flow_buf) (void)hipFree(h->flow_buf);

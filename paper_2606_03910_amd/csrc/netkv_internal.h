@@ -21,6 +21,9 @@ void netkv_internal_clear(netkv_handle h);
 int netkv_internal_device(netkv_handle h);
 // The handle's device error word (reported by netkv_sync_errors).
 uint32_t *netkv_internal_errword(netkv_handle h);
+// The handle's second stream, and two events to fork it from another stream
+// and join it back within a call.
+void netkv_internal_side(netkv_handle h, hipStream_t *side, hipEvent_t *fork, hipEvent_t *join);
 // A device buffer of the handle for the flow simulation, of at least
 // `bytes` (grown on demand, kept until the handle is destroyed).
 hipError_t netkv_internal_flow_buffer(netkv_handle h, uint64_t bytes, void **out);

@@ -310,3 +310,46 @@ def test_limits_of_the_register_form(nk, form):
     sel.sync_errors()
     _check_against_oracle(insts, fin, ev, arr)
     sel.close()
+
+
+def test_forms_in_one_call(nk):
+    """Instances of every form side by side: in the register form, outside it
+    (over 320 links, paths of 9, a burst that is sure to exceed 512 flows in
+    progress), handed over on the way, empty and invalid ones.  Finish times and
+    counts as in calls of one instance each, and against the oracle, bit for
+    bit; twice on one handle."""
+    _say("flow sim forms in one call")
+    rng = np.random.default_rng(31)
+    L = 400
+    few, many = np.arange(40), np.arange(400)
+
+    def inst(n, links, plen, start):
+        paths = [list(rng.choice(links, rng.integers(1, plen + 1), replace=False)) for _ in range(n)]
+        return _flows(10.0 ** rng.uniform(0.0, 1.0, L), paths, rng.uniform(0.1, 9.0, n), start)
+
+    late = np.concatenate([np.zeros(500), np.repeat(rng.uniform(0.0, 0.5, 50), 4)])
+    insts = [inst(300, few, 4, rng.uniform(0.0, 40.0, 300)), inst(500, many, 6, rng.uniform(0.0, 30.0, 500)),
+             inst(90, few, 9, rng.uniform(0.0, 20.0, 90)), inst(700, few, 3, np.zeros(700)), inst(700, few, 4, late),
+             inst(0, few, 4, np.zeros(0)), inst(64, few, 4, np.zeros(64))]
+    sel = nk.Selector(0)
+    alone = [_run(nk, sel, [i])[:2] for i in insts]
+    sel.sync_errors()
+    for rep in range(2):
+        fin, ev, arr = _run(nk, sel, insts)
+        sel.sync_errors()
+        at = 0
+        for i, (f, e) in enumerate(alone):
+            assert np.array_equal(fin[at:at + len(f)].view(np.uint64), f.view(np.uint64)), (rep, i)
+            assert np.array_equal(ev[i], e[0]), (rep, i)
+            at += len(f)
+    _check_against_oracle(insts, fin, ev, arr)
+    bad = dict(insts[0], bytes=insts[0]["bytes"].copy())
+    bad["bytes"][7] = np.nan
+    fin, ev, arr = _run(nk, sel, [insts[1], bad, insts[3]])
+    with pytest.raises(nk.NetKVError):
+        sel.sync_errors()
+    n = len(alone[1][0])
+    assert np.isnan(fin[n:n + 300]).all() and (ev[1] == 0).all()
+    assert np.array_equal(fin[:n].view(np.uint64), alone[1][0].view(np.uint64))
+    assert np.array_equal(fin[n + 300:].view(np.uint64), alone[3][0].view(np.uint64))
+    sel.close()
