@@ -1793,6 +1793,45 @@ __global__ __launch_bounds__(256) void reduce_kernel(uint32_t n_req, uint32_t nc
     }
 }
 
+// Orders one wavefront's LDS accesses around an exchange between its lanes
+// (its LDS operations execute in order, so it costs no instruction).
+__device__ inline void lane_phase() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// Leading 64-bit words of the 64 in LDS (each the AND of those before it, low
+// and high halves in turn) that have the lane's bit, 0 .. 64.
+__device__ inline uint32_t count_words(const uint32_t *wds, uint32_t lane) {
+    const uint32_t *half = wds + (lane >> 5);
+    const uint32_t sh = lane & 31u;
+    uint32_t j = 0;
+#pragma unroll
+    for (uint32_t b = 32; b; b >>= 1) j += (half[2 * (j + b - 1)] >> sh & 1u) * b;
+    return j + (half[2 * j] >> sh & 1u);   // 63 found so far: the last word
+}
+
+// Holder values of two hashes, the loads of both together (hash 0: none).
+__device__ inline void holder_lane2(const Table &t, const uint64_t (&h)[2], uint32_t (&v)[2]) {
+    uint64_t slot[2];
+    ulonglong2 k1[2], k2[2];
+    uint32_t b1[2], b2[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        buckets_of(h[u], t.shift, t.in_block, b1[u], b2[u]);
+        k1[u] = *(const ulonglong2 *)(t.keys + 2 * (uint64_t)b1[u]);
+        k2[u] = *(const ulonglong2 *)(t.keys + 2 * (uint64_t)b2[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const uint64_t x = h[u];
+        slot[u] = x == 0 ? ~0ull
+                : k1[u].x == x ? 2 * (uint64_t)b1[u] : k1[u].y == x ? 2 * (uint64_t)b1[u] + 1
+                : k2[u].x == x ? 2 * (uint64_t)b2[u] : k2[u].y == x ? 2 * (uint64_t)b2[u] + 1 : ~0ull;
+        v[u] = kNoHolder;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+        if (slot[u] != ~0ull) v[u] = t.vals[slot[u]];
+}
+
 // ---------------------------------------------------------------- direct selection
 //
 // Small batches in one launch, with no ordering: the ordering pipeline is 10
@@ -1802,7 +1841,11 @@ __global__ __launch_bounds__(256) void reduce_kernel(uint32_t n_req, uint32_t nc
 // decodes): lanes look up the holder values of 64 blocks at a time, up to the
 // first block no decode holds; then, per chunk of C groups of 64 decodes, the
 // blocks' bitmap words are ANDed block by block (scalar), each decode lane
-// counting the blocks it still matches.  Costs, feasibility and the top-k
+// counting the blocks it still matches.  Runs with more than 64 held blocks go
+// 128 at a time: a lane loads its blocks' words, the ANDs go over the lanes
+// and each decode lane finds its count by a binary search (a run of 4,096 held
+// blocks on 48 / 768 decodes 364 / 778 us block by block, 54 / 98 so;
+// the ordering pipeline 178 / 186).  Costs, feasibility and the top-k
 // are those of the scoring kernel bit for bit: x < 2^24 is the same integer
 // in fp32 and in u32, and larger x are rounded to fp32 as there.  fly: the
 // cost factors are computed here from the snapshot instead of read from the
@@ -1814,7 +1857,9 @@ __global__ __launch_bounds__(kBlock) void direct_kernel(Snap s, Table t, Reqs rq
                                                         uint32_t k_out, int32_t *__restrict__ out_idx,
                                                         float *__restrict__ out_score, uint32_t *__restrict__ err,
                                                         Hot *__restrict__ hotr, float *__restrict__ lam) {
+    constexpr int G = C < 4 ? C : 4;   // columns whose words are exchanged together
     __shared__ uint64_t wkeys[kWavesPerBlock][K];
+    __shared__ __align__(8) uint32_t wds[kWavesPerBlock][2][G][2 * kWave];
     const uint32_t lane = threadIdx.x % kWave, wv = wave_index();
     const uint32_t r = blockIdx.x * (kWavesPerBlock / nw) + wv / nw, part = wv % nw;
     if (r >= rq.n_req) return;   // only with one wavefront per request (no barrier then)
@@ -1845,16 +1890,15 @@ __global__ __launch_bounds__(kBlock) void direct_kernel(Snap s, Table t, Reqs rq
                 alive[q] = ~0ull;
                 j[q] = 0;
             }
-            uint32_t v = v0, m = m0;
-            for (uint32_t k0 = 0;;) {
+            if (m0 < (uint32_t)kWave || n <= (uint32_t)kWave) {
                 constexpr uint32_t U = C > 4 ? 2 : 4;   // blocks whose words load together
                 lmask any = ~0ull;
-                for (uint32_t k = 0; k < m && any; k += U) {
+                for (uint32_t k = 0; k < m0 && any; k += U) {
                     lmask w[U][C];
 #pragma unroll
                     for (uint32_t u = 0; u < U; ++u) {
-                        const uint32_t vk = k + u < m ? (uint32_t)__builtin_amdgcn_readlane((int)v, (int)((k + u) % kWave))
-                                                      : kNoHolder;
+                        const uint32_t vk = k + u < m0 ? (uint32_t)__builtin_amdgcn_readlane((int)v0, (int)((k + u) % kWave))
+                                                       : kNoHolder;
                         holder_masks<C>(t, vk, base, w[u]);
                     }
                     any = 0;
@@ -1869,9 +1913,57 @@ __global__ __launch_bounds__(kBlock) void direct_kernel(Snap s, Table t, Reqs rq
 #pragma unroll
                     for (int q = 0; q < C; ++q) any |= alive[q];
                 }
-                k0 += kWave;
-                if (m < (uint32_t)kWave || !any || k0 >= n) break;
-                m = lookup(k0, v);
+            } else {
+                for (uint32_t k0 = 0;; k0 += 2 * kWave) {
+                    uint64_t hs[2];
+                    uint32_t v[2];
+#pragma unroll
+                    for (uint32_t u = 0; u < 2; ++u) {
+                        const uint32_t k = k0 + u * kWave + lane;
+                        hs[u] = k < n ? rq.hashes[a + k] : 0ull;
+                    }
+                    holder_lane2(t, hs, v);
+                    const lmask none0 = ballot(v[0] == kNoHolder), none1 = ballot(v[1] == kNoHolder);
+                    lmask any = 0;
+#pragma unroll
+                    for (int q0 = 0; q0 < C; q0 += G) {
+                        lmask w[2][G];
+#pragma unroll
+                        for (uint32_t u = 0; u < 2; ++u) {
+                            const bool row = v[u] < kHeldOne;
+                            const uint64_t *src = t.bits + (uint64_t)(row ? v[u] : 0u) * t.bpitch + base / kWave + q0;
+#pragma unroll
+                            for (int q = 0; q < G; ++q) w[u][q] = src[q];
+                            const uint32_t d = v[u] & ~kHeldOne;
+#pragma unroll
+                            for (int q = 0; q < G; ++q) {
+                                const uint32_t o = d - (base + (uint32_t)(q0 + q) * kWave);
+                                if (!row) w[u][q] = v[u] != kNoHolder && o < (uint32_t)kWave ? 1ull << o : 0ull;
+                                w[u][q] = wave_and_prefix_u64(w[u][q] & alive[q0 + q]);
+                            }
+                        }
+                        lane_phase();
+#pragma unroll
+                        for (uint32_t u = 0; u < 2; ++u) {
+#pragma unroll
+                            for (int q = 0; q < G; ++q) {
+                                wds[wv][u][q][2 * lane] = (uint32_t)w[u][q];
+                                wds[wv][u][q][2 * lane + 1] = (uint32_t)(w[u][q] >> 32);
+                            }
+                        }
+                        lane_phase();
+#pragma unroll
+                        for (int q = 0; q < G; ++q) {
+                            const uint32_t c0 = count_words(wds[wv][0][q], lane), c1 = count_words(wds[wv][1][q], lane);
+                            j[q0 + q] += c0 + (c0 == (uint32_t)kWave ? c1 : 0u);
+                            alive[q0 + q] = ballot(c0 == (uint32_t)kWave && c1 == (uint32_t)kWave);
+                            any |= alive[q0 + q];
+                        }
+                        lane_phase();
+                    }
+                    // (a block that no decode holds, the run's end among them, leaves none)
+                    if (none0 || none1 || !any) break;
+                }
             }
 #pragma unroll
             for (int q = 0; q < C; ++q) {
@@ -2070,7 +2162,7 @@ template <uint32_t L, uint32_t U>
 __global__ __launch_bounds__(kBlock) void match_kernel(Snap s, Table t, Shared sh, Reqs rq,
                                                        uint32_t *__restrict__ hv, uint32_t *__restrict__ mm,
                                                        uint32_t *__restrict__ err) {
-    const uint32_t sub = threadIdx.x % L, seg0 = (threadIdx.x % kWave) - sub;
+    const uint32_t lane = threadIdx.x % kWave, sub = lane % L, seg0 = lane - sub;
     const uint64_t r = (uint64_t)blockIdx.x * (kBlock / L) + threadIdx.x / L;
     const bool in = r < rq.n_req;
     uint32_t p, len, n = 0;
@@ -2080,9 +2172,13 @@ __global__ __launch_bounds__(kBlock) void match_kernel(Snap s, Table t, Shared s
     uint32_t m = n;
     bool act = n > 0;
     // blocks from k on through an index, up to the first it does not have
-    // (past the run's end: a miss, so m is at most n)
+    // (past the run's end: a miss, so m is at most n); after kAlone blocks the
+    // whole wavefront takes one request after another, as many blocks per step
+    // in all (a wavefront with one run of 4,096 held blocks takes 30 steps
+    // more, and not 240)
+    constexpr uint32_t kAlone = 256;
     auto steps = [&](auto lookup, uint32_t k) {
-        for (; __any(act); k += L * U) {
+        for (uint32_t done = 0; __any(act) && done < kAlone; done += L * U, k += L * U) {
             uint64_t h[U];
             uint32_t v[U];
 #pragma unroll
@@ -2102,6 +2198,37 @@ __global__ __launch_bounds__(kBlock) void match_kernel(Snap s, Table t, Shared s
                 if (act && u * L + sub < first) hv[a + k + u * L + sub] = v[u];
             if (act && first < L * U) {
                 m = k + first;
+                act = false;
+            }
+        }
+        for (lmask left = ballot(act && sub == 0); left; left &= left - 1) {
+            const uint32_t l = (uint32_t)__builtin_ctzll(left);
+            const uint32_t nl = (uint32_t)__builtin_amdgcn_readlane((int)n, (int)l);
+            const uint64_t al = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(a >> 32), (int)l) << 32) |
+                                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)a, (int)l);
+            uint32_t kl = (uint32_t)__builtin_amdgcn_readlane((int)k, (int)l), first = kWave * U;
+            for (;; kl += kWave * U) {
+                uint64_t h[U];
+                uint32_t v[U];
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u) {
+                    const uint32_t kk = kl + u * kWave + lane;
+                    h[u] = kk < nl ? rq.hashes[al + kk] : 0ull;
+                }
+                lookup(h, v);
+                first = kWave * U;
+#pragma unroll
+                for (int u = (int)U - 1; u >= 0; --u) {
+                    const lmask miss = ballot(v[u] == kNoHolder);
+                    if (miss) first = (uint32_t)u * kWave + (uint32_t)__builtin_ctzll(miss);
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u)
+                    if (u * kWave + lane < first) hv[al + kl + u * kWave + lane] = v[u];
+                if (first < kWave * U) break;   // (at the run's end at the latest)
+            }
+            if (seg0 == l) {
+                m = kl + first;
                 act = false;
             }
         }
@@ -2151,10 +2278,6 @@ __global__ __launch_bounds__(kBlock) void match_kernel(Snap s, Table t, Shared s
 // block, and the scalar unit bound the kernel).
 // The array holds 32-bit words, low and high halves in turn, as they are read:
 // stored as 64-bit ones, the compiler may take stores and reads as unrelated.
-// The fences order the lanes' accesses around the exchange (one wavefront's
-// LDS operations execute in order, so they cost no instruction).
-__device__ inline void lane_phase() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
 __device__ inline uint32_t leading_words(uint32_t *wds, uint64_t word, uint32_t lane, bool few) {
     uint32_t lo = (uint32_t)word, hi = (uint32_t)(word >> 32);
     lo &= (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x111, 0xF, 0xF, false);   // row_shr 1
@@ -2270,9 +2393,15 @@ __global__ __launch_bounds__(kBlock) void bounded_kernel(Snap s, Table t, Reqs r
         // the lane's cost bits of request q on its decode of group g
         auto cost = [&](int q, uint32_t g, float2 x1, float2 x2, float lim, uint64_t wd) -> uint32_t {
             uint32_t j = leading_words(lds[wv][q], wd, lane, mq[q] < 16);
-            for (uint32_t k0 = kWave; k0 < mq[q] && __any(j == k0); k0 += kWave) {   // runs of more than 64 held blocks
-                const uint32_t vk = k0 + lane < mq[q] ? (hv + a[q] + k0)[lane] : kNoHolder;
-                const uint32_t more = leading_words(lds[wv][q], words(g, vk), lane, mq[q] - k0 < 16);
+            for (uint32_t k0 = kWave; k0 < mq[q] && __any(j == k0); k0 += 2 * kWave) {   // runs of more than 64 held blocks
+                const uint32_t v0 = k0 + lane < mq[q] ? (hv + a[q] + k0)[lane] : kNoHolder;
+                const uint32_t v1 = k0 + kWave + lane < mq[q] ? (hv + a[q] + k0 + kWave)[lane] : kNoHolder;
+                const uint64_t w0 = words(g, v0), w1 = words(g, v1);
+                uint32_t more = leading_words(lds[wv][q], w0, lane, mq[q] - k0 < 16);
+                if (mq[q] - k0 > (uint32_t)kWave) {
+                    const uint32_t next = leading_words(lds[wv][q], w1, lane, mq[q] - k0 - kWave < 16);
+                    more += more == (uint32_t)kWave ? next : 0u;
+                }
                 j += j == k0 ? more : 0u;
             }
             const uint32_t x = len[q] - bt * j;

@@ -225,3 +225,53 @@ def test_commit_forms(D, R):
     assert np.all(got["n_inflight"] == 0) and np.array_equal(got["queue_depth"], before["queue_depth"])
     assert np.all(got["admitted_prev"] == 0)
     sel.close()
+
+
+@pytest.mark.parametrize("D", [1, 48, 65, 768, 1602, 3072])
+def test_long_runs(D):
+    """Runs of up to 5,000 held blocks, cut at different blocks on different
+    decodes (about every multiple of 64 and 128), some with a tail that one
+    decode alone holds, in the middle or at the end of the batch: the direct
+    and the bounded selection, the records of the sequential form and the
+    ranking sweep against the ordering pipeline."""
+    from paper_2606_03910_amd import netkv
+    rng = np.random.default_rng(D)
+    bt = 64
+    snap, _, _ = _inputs(D, 4, D, bt=bt, mem=(20, 200))
+    P = snap["n_prefill"]
+    cuts = np.array([1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 255, 256, 257, 319, 320, 321, 511, 512, 513, 1000, 4999, 5000])
+    chains = [rng.integers(1, 1 << 63, 5000, dtype=np.uint64) for _ in range(3)]
+    sets = []
+    for d in range(D):
+        own = [c[:rng.choice(cuts)] for c in chains if rng.random() < 0.5]
+        if d == D // 2:
+            own.append(chains[0])
+        sets.append(np.concatenate(own + [rng.integers(1, 1 << 63, 5, dtype=np.uint64)]))
+    off = np.zeros(D + 1, np.uint64)
+    off[1:] = np.cumsum([len(x) for x in sets])
+    sel = _handle(netkv, snap, dict(hash_off=off, hashes=np.concatenate(sets)))
+
+    def batch(n):
+        runs = []
+        for _ in range(n):
+            c = chains[rng.integers(3)][:rng.choice(cuts)] if rng.random() < min(1.0, 300 / n) else chains[0][:rng.integers(1, 30)]
+            runs.append(np.concatenate([c, rng.integers(1, 1 << 63, int(rng.integers(0, 200)) if len(c) > 60 else 0, dtype=np.uint64)]))
+        ln = np.array([len(r) for r in runs])
+        return dict(prefill=rng.integers(0, P, n).astype(np.uint32), len_tokens=(ln * bt + rng.integers(0, bt, n)).astype(np.uint32),
+                    hash_off=np.concatenate([[0], np.cumsum(ln)]).astype(np.uint64), hashes=np.concatenate(runs))
+    util = torch.from_numpy(rng.uniform(0, 0.9, (3, P * D)).astype(np.float32)).to(sel.device).reshape(-1)
+    for n in (1, 7, 150, 20000 // (-(-D // 64)) + 50):
+        rd = netkv.requests_to_device(batch(n), sel.device)
+        for k in (1, 3, 8):
+            both = []
+            for run_len in (0, 8):
+                netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_RUN_LEN, run_len)
+                out = sel.select(rd, k=k)
+                both.append([*_bits(netkv, out)])
+                if k == 1:
+                    both[-1] += [*_bits(netkv, sel.select_sequential(rd, 16)), *_bits(netkv, sel.rank_sweep(rd, util, 2))]
+            netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_RUN_LEN, 0)
+            print("[direct] long runs D", D, "R", n, "k", k, flush=True)
+            assert all(np.array_equal(a, b) for a, b in zip(*both))
+    sel.sync_errors()
+    sel.close()
