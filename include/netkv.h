@@ -175,15 +175,17 @@ typedef struct {
  * rejects a request with no feasible decode).  out_idx, out_score:
  * [n_req * k] DEVICE arrays.  `pairs` may be NULL.  Asynchronous on
  * `stream`: inputs must stay valid and outputs are defined once the stream
- * completes.  A batch of 2^16 requests or more also runs work on a second
+ * completes.  A batch of 2^16 requests or more may also run work on a second
  * stream of the handle, forked from `stream` and joined back to it by
  * events within the call, so ordering on `stream` (and a graph capture of
  * it) covers all of it.  Allocates only when a batch is
- * larger than the handle's work buffers hold -- every earlier batch's, or
- * what netkv_reserve sized them for -- and then grows them (about
- * 100 + 8*K*ceil(D/(64*C)) bytes per request, K the next power of two >= k
- * and C the decodes per lane, plus 4 bytes per block hash and the leader
- * table).
+ * larger than the handle's work buffers hold -- every earlier batch's, in
+ * whatever form, or what netkv_reserve sized them for -- and then grows them
+ * (about 104 + 8*K*ceil(D/(64*C)) bytes per request, K the next power of two
+ * >= k and C the decodes per lane, plus 4 bytes per block hash and the leader
+ * table).  How a batch is selected (which of three forms of the same results)
+ * depends on its size, k, the pool and how far the snapshot's costs separate
+ * its groups of 64 decodes, which the load calls measure.
  * EINVAL: NULL pointers, k out of range; ENOTREADY: snapshot or cache
  * missing; n_req = 0 is a no-op. */
 netkv_status netkv_select_batch(netkv_handle h, const netkv_requests_t *req, uint32_t k,
@@ -284,7 +286,8 @@ netkv_status netkv_route2_of(netkv_handle h, const netkv_requests_t *req, uint32
  * so ordering on `stream` (and a graph capture of it) covers them.
  * Asynchronous; grows internal buffers on first use (n_scen * P * D * 4
  * bytes of per-scenario factors, 16 bytes per request of records, and the
- * selection's buffers, see netkv_reserve).  Invalid requests get index -1
+ * selection's buffers or, for small batches, 4 * D bytes per request, at most
+ * 16 MiB; see netkv_reserve).  Invalid requests get index -1
  * and score NaN in every scenario.  Scenario values are not validated
  * (values >= 1 give non-positive bandwidth and meaningless costs). */
 netkv_status netkv_rank_sweep(netkv_handle h, const netkv_requests_t *req, uint32_t n_scen,
@@ -323,8 +326,9 @@ netkv_status netkv_tier_counts(netkv_handle h, const netkv_requests_t *req, cons
  * applies the batch).  Asynchronous.  The prefix lengths come from the
  * batch selection's per-request records and leader rows (no per-pair
  * buffer): the work buffers are netkv_select_batch's at k = 1 plus
- * 16 bytes per request (records by batch index) and 16 bytes per request
- * for the per-prefill ordering, grown when a batch exceeds every earlier
+ * 16 bytes per request (records by batch index), 16 bytes per request
+ * for the per-prefill ordering and the ranking sweep's rows of small batches,
+ * grown when a batch exceeds every earlier
  * one (netkv_reserve sizes them ahead).  Runs of any length are valid. */
 netkv_status netkv_select_sequential(netkv_handle h, const netkv_requests_t *req, uint32_t cap,
                                      int32_t *out_idx, float *out_score, void *stream);

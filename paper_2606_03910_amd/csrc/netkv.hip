@@ -4048,7 +4048,6 @@ struct netkv_ctx {
     // the bounded selection: bound factors per (p, group), limits, match counts
     float2 *bnd_lo = nullptr, *bnd_lo2 = nullptr;
     float *bnd_xm = nullptr, *bnd_xg = nullptr;
-    uint32_t bnd_P = 0, bnd_D = 0;
     uint32_t *match_m = nullptr;
     uint64_t match_cap = 0;
     float *dlam = nullptr;        // [R][D] B_tok * j of a direct selection with records
@@ -4778,32 +4777,24 @@ bool bounded_batch(netkv_handle h, uint64_t R, uint64_t n_hashes, uint32_t k, bo
            (two ? tasks <= kBoundRouteTasks : !many || tasks <= kBoundManyTasks);
 }
 
-netkv_status ensure_bounds(netkv_handle h, uint64_t R, uint64_t n_hashes) {
-    const uint32_t ng = (h->D + kWave - 1) / kWave;
-    if (h->bnd_P != h->P || h->bnd_D != h->D) {
-        dfree(h->bnd_lo); dfree(h->bnd_lo2); dfree(h->bnd_xm); dfree(h->bnd_xg);
-        h->bnd_P = h->bnd_D = 0;
-        if (dalloc(h->bnd_lo, (uint64_t)h->P * ng) != hipSuccess || dalloc(h->bnd_lo2, (uint64_t)h->P * ng) != hipSuccess ||
-            dalloc(h->bnd_xm, (uint64_t)ng * kWave) != hipSuccess || dalloc(h->bnd_xg, ng) != hipSuccess)
-            return fail(h, NETKV_ENOMEM, "bound table allocation failed");
-        h->bnd_P = h->P;
-        h->bnd_D = h->D;
-    }
-    if (R > h->match_cap) {
-        dfree(h->match_m);
-        h->match_cap = 0;
-        if (dalloc(h->match_m, R) != hipSuccess) return fail(h, NETKV_ENOMEM, "match scratch allocation failed");
-        h->match_cap = R;
-    }
-    return ensure_hv(h, h->sc, n_hashes);
+// Pools of the bounded selection, whose tables are sized with the snapshot's.
+bool bound_pool(uint32_t D) { return D <= kBoundMaxGroups * kWave; }
+
+netkv_status ensure_match(netkv_handle h, uint64_t R) {
+    if (R <= h->match_cap || !bound_pool(h->D)) return NETKV_OK;
+    dfree(h->match_m);
+    h->match_cap = 0;
+    if (dalloc(h->match_m, R) != hipSuccess) return fail(h, NETKV_ENOMEM, "match scratch allocation failed");
+    h->match_cap = R;
+    return NETKV_OK;
 }
 
 netkv_status run_bounded(netkv_handle h, const netkv_requests_t *req, uint32_t k, int32_t *idx, float *score,
                          hipStream_t st, bool route2) {
     const uint64_t R = req->n_req;
     const uint32_t ng = (h->D + kWave - 1) / kWave;
-    netkv_status e = ensure_bounds(h, R, req->n_hashes);
-    if (e) return e;
+    netkv_status e = ensure_match(h, R);
+    if (e || (e = ensure_hv(h, h->sc, req->n_hashes))) return e;
     const bool two = route2 && h->have_route;
     Snap sn = make_snap(h);
     const Table t = make_table(h);
@@ -4906,6 +4897,31 @@ netkv_status select_owned(netkv_handle h, const netkv_requests_t *req, uint32_t 
     if (want_hotr && (e = ensure_hotr(h, req->n_req))) return e;
     return run_select(h, h->sc, req, k, idx, score, po, pairs, max_blocks, st, route2, true,
                       want_hotr ? h->sc.hotr : nullptr, score_pairs);
+}
+
+// After a selection that did not use all of them: the work buffers that any
+// form of a batch of this size uses, so that a later one -- with per-pair
+// outputs, more of k, other congestion, routes or options -- allocates no more
+// than for a batch of this size before.  The selection's kernels run meanwhile.
+// Not while the stream is captured, where nothing can be allocated, and no
+// error of the call, whose results do not need them.
+void size_ahead(netkv_handle h, const netkv_requests_t *req, uint32_t k, hipStream_t st) {
+    const Geometry geo = geometry(h, k);
+    const uint64_t R = req->n_req, elems = R * geo.ngroup * geo.K;
+    const Scratch &sc = h->sc;
+    const bool match = R <= h->match_cap || !bound_pool(h->D);
+    if (match && R <= sc.order_cap && elems <= sc.partial_cap && req->n_hashes <= sc.hv_cap && sc.lead_D == h->D &&
+        lead_capacity(R, h->D) <= sc.lead_cap)
+        return;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (ensure_scratch(h, h->sc, R, elems, req->n_hashes, st) || ensure_match(h, R)) {
+        (void)hipGetLastError();
+        h->err.clear();
+    }
 }
 
 // ---- work buffers carved from the static scratch array (no allocation)
@@ -5264,6 +5280,7 @@ netkv_status netkv_oracle_load(netkv_handle h, const netkv_oracle_t *o, void *st
                     (bad & 2) ? " util outside [0,1) or NaN" : "", (bad & 4) ? " batch_size > beta_max" : "");
     if (!h->have_snap || h->P != P || h->D != D) {
         dfree(h->sl); dfree(h->dbase); dfree(h->dxlim);
+        dfree(h->bnd_lo); dfree(h->bnd_lo2); dfree(h->bnd_xm); dfree(h->bnd_xg);
         // route maps and rows of another shape no longer apply
         dfree(h->rt1); dfree(h->rt2); dfree(h->ru1); dfree(h->ru2); dfree(h->sr);
         h->rt1 = h->rt2 = nullptr;
@@ -5273,6 +5290,11 @@ netkv_status netkv_oracle_load(netkv_handle h, const netkv_oracle_t *o, void *st
         if (dalloc(h->sl, (uint64_t)P * sl_pitch(D) + kRowPad) != hipSuccess || dalloc(h->dbase, D) != hipSuccess ||
             dalloc(h->dxlim, D) != hipSuccess)
             return fail(h, NETKV_ENOMEM, "snapshot allocation failed");
+        const uint32_t ng = (D + kWave - 1) / kWave;
+        if (bound_pool(D) && (dalloc(h->bnd_lo, (uint64_t)P * ng) != hipSuccess ||
+                              dalloc(h->bnd_lo2, (uint64_t)P * ng) != hipSuccess ||
+                              dalloc(h->bnd_xm, (uint64_t)ng * kWave) != hipSuccess || dalloc(h->bnd_xg, ng) != hipSuccess))
+            return fail(h, NETKV_ENOMEM, "bound table allocation failed");
     }
     std::swap(h->tier_map, sp.tier_map);
     std::swap(h->util, sp.util);
@@ -5781,10 +5803,13 @@ netkv_status netkv_select_batch(netkv_handle h, const netkv_requests_t *req, uin
         want_pairs = po.j || po.feas || po.score;
     }
     if (!want_pairs && direct_batch(h, req->n_req, req->n_hashes, kDirectTasks))
-        return run_direct(h, req, k, out_idx, out_score, s, true);
-    if (!want_pairs && bounded_batch(h, req->n_req, req->n_hashes, k, h->have_route))
-        return run_bounded(h, req, k, out_idx, out_score, s, true);
-    return select_owned(h, req, k, out_idx, out_score, po, want_pairs, 0xFFFFFFFFu, s, true);
+        st = run_direct(h, req, k, out_idx, out_score, s, true);
+    else if (!want_pairs && bounded_batch(h, req->n_req, req->n_hashes, k, h->have_route))
+        st = run_bounded(h, req, k, out_idx, out_score, s, true);
+    else
+        st = select_owned(h, req, k, out_idx, out_score, po, want_pairs, 0xFFFFFFFFu, s, true);
+    if (!st) size_ahead(h, req, k, s);
+    return st;
 }
 
 netkv_status netkv_select_batch_noalloc(netkv_handle h, const netkv_requests_t *req, uint32_t k, int32_t *out_idx,
@@ -5834,7 +5859,7 @@ netkv_status netkv_reserve(netkv_handle h, uint32_t max_req, uint64_t max_hashes
         elems = std::max<uint64_t>(elems, (uint64_t)max_req * geo.ngroup * geo.K);
     }
     netkv_status st = ensure_scratch(h, h->sc, max_req, elems, max_hashes, (hipStream_t)stream);
-    if (!st && bounded_batch(h, max_req, 0, 1, false)) st = ensure_bounds(h, max_req, max_hashes);
+    if (!st) st = ensure_match(h, max_req);
     if (!st) st = ensure_hotr(h, max_req);
     if (!st) st = ensure_dlam(h, std::min<uint64_t>(max_req, kDirectRecordTasks / ((h->D + kWave - 1) / kWave)));
     if (!st) st = ensure_seq(h, max_req, h->P, true, true);
