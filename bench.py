@@ -58,16 +58,11 @@ def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
 
-def selection_kernel(R: int, D: int, n_hashes: int, args) -> str:
-    """The timed kernel of a selection (the library's choice by size)."""
-    groups = (D + 63) // 64
-    if not (args.no_reuse or args.run_len or args.cols or args.sequential):
-        if groups * max(R, n_hashes // 32) <= 1 << 14:
-            return "direct_kernel"
-        few = not args.two_hop or R * groups * (8 if n_hashes > 64 * R else 1) <= 5 << 20   # k = 1 here
-        if groups <= 64 and (R <= 1 << 17 or n_hashes <= 64 * R) and few:
-            return "bounded_kernel"
-    return "score_kernel"
+def selection_kernel(netkv, h, args) -> str:
+    """The timed kernel of the selections just made."""
+    if args.sequential:
+        return "score_kernel"
+    return {1: "score_kernel", 2: "bounded_kernel", 3: "direct_kernel"}[netkv.netkv_last_form(h)]
 
 
 def cols_per_lane(D: int) -> int:
@@ -327,6 +322,7 @@ def main():
     wall = time.perf_counter() - w0
     kern_ms = netkv.netkv_kernel_ms(sel.h)   # mean over the timed launches
     netkv.netkv_set_timing(sel.h, False)
+    kernel = selection_kernel(netkv, sel.h, args)
     sel.sync_errors()
     step_ms = ev0.elapsed_time(ev1) / args.steps
     log(f"timed {args.steps} steps: wall {wall * 1e3:.2f} ms, step mean {step_ms:.3f} ms, "
@@ -474,7 +470,6 @@ def main():
         },
         "cpu_baseline": cpu,
     }
-    kernel = selection_kernel(R, D, int(nblk.sum()), args)
     if kernel != "score_kernel":
         # pairs that bounds rule out are not scored, so operations per pair
         # price nothing: the step is held against its inputs and outputs once

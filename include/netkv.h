@@ -346,8 +346,10 @@ netkv_status netkv_sync_errors(netkv_handle h, void *stream);
 
 /* Kernel timing: when enabled, the library records HIP events on `stream`
  * around the one scoring kernel of each call -- the kernel of
- * netkv_select_batch that scores every pair and keeps each decode group's
- * top-k (not the ordering, prefix-length or merge kernels), the sweep
+ * netkv_select_batch that scores the pairs and keeps the top-k (the direct
+ * selection's one kernel, the bounded one's scoring kernel, or along the
+ * batch order the one that scores every pair; not the ordering,
+ * prefix-length or merge kernels), the sweep
  * kernel of netkv_rank_sweep, the per-prefill kernel of
  * netkv_select_sequential, the smoothing kernel of netkv_congestion_smooth
  * -- without synchronising.  netkv_kernel_ms waits
@@ -384,7 +386,13 @@ netkv_status netkv_kernel_ms(netkv_handle h, float *ms);
  *                        `value` of their blocks, are kept per call.  A
  *                        request whose leader is not kept is matched from
  *                        block 0 on its own, and a leader whose blocks'
- *                        holder values are not kept looks them up itself.
+ *                        holder values are not kept looks them up itself;
+ *   NETKV_OPT_FORM    -- how a batch without per-pair outputs is selected:
+ *                        0 (default): by size, k, pool and snapshot; 1: along
+ *                        the batch order always; 2: by bounds per group of 64
+ *                        decodes on pools of up to 4,096 (along the order on
+ *                        larger ones, and where one of the options above asks
+ *                        for the order).
  * and one option that does change results, selecting the rung of the
  * method's ablation (Sec. VI, Experiment 6) the costs use:
  *   NETKV_OPT_POLICY  -- 0 (default): the full cost; 1: static tier map and
@@ -392,8 +400,14 @@ netkv_status netkv_kernel_ms(netkv_handle h, float *ms);
  *                        2: static tier map only (congestion and in-flight
  *                        counters taken as 0). */
 enum { NETKV_OPT_RUN_LEN = 1, NETKV_OPT_REUSE = 2, NETKV_OPT_COLS = 3, NETKV_OPT_POLICY = 4,
-       NETKV_OPT_LEAD_CAP = 5 };
+       NETKV_OPT_LEAD_CAP = 5, NETKV_OPT_FORM = 6 };
 netkv_status netkv_set_option(netkv_handle h, int option, uint32_t value);
+
+/* How the last netkv_select_batch or netkv_select_batch_noalloc of h selected
+ * (for measurements; the results do not depend on it): 1 along the batch
+ * order, 2 by bounds, 3 directly (a small batch in one launch).  ENOTREADY
+ * before the first one; EINVAL: form NULL. */
+netkv_status netkv_last_form(netkv_handle h, uint32_t *form);
 
 /* Geometry of the loaded cache's holder index (any pointer may be NULL):
  * slots of the hash set (two per bucket, a power of two of buckets),

@@ -13,15 +13,16 @@
 // One wavefront runs one instance (a flow set on its links) through all its
 // events with the link state in its registers (flow_bits_kernel), where the
 // instance fits that form (flow_form_kernel); else, or from where it no longer
-// does, one workgroup does (flow_sim_kernel).  The two kinds run side by side
-// on two streams: a call of 128 instances in the form (224 ms) and one of
-// 2,000 flows outside it (744 ms) takes 765 ms, one after the other 959 ms.  The instances of a call are independent (other
-// congestion draws, other batches).  Inside a workgroup, threads take links and flows in
+// does, one workgroup does (flow_sim_kernel).  The two kinds run side by
+// side on two streams: a call of 128 instances in the form (224 ms) and one
+// of 2,000 flows outside it (744 ms) takes 765 ms, one after the other 959
+// ms.  The instances of a call are independent (other congestion draws,
+// other batches).  Inside a workgroup, threads take links and flows in
 // strides, and workgroup reductions give the minimum raise, the next event
-// and the counts.  Before the simulation each instance's flows are sorted
-// by arrival time (rocPRIM's segmented radix sort, which only orders work),
-// so that a pass takes its arrivals from the head of that order and keeps
-// the list of flows in progress from pass to pass: its cost follows the
+// and the counts.  Before the simulation each instance's flows are sorted by
+// arrival time (rocPRIM's segmented radix sort, which only orders work), so
+// that a pass takes its arrivals from the head of that order and keeps the
+// list of flows in progress from pass to pass: its cost follows the
 // flows in progress, not the instance's size.  Every quantity is fp64 and every operation is written
 // out in order with contraction off, so the results equal those of a
 // sequential implementation of the same steps bit for bit (minima do not

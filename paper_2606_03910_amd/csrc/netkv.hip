@@ -18,9 +18,20 @@
 //     derived per call: (seconds per token, constant part) float2 rows per
 //     prefill, and per decode the load term and feasibility limit.
 //
-// Kernels of one selection (netkv_select_batch), in launch order (a batch
-// of 2^16 requests or more runs derive_kernel, then lead_holder_kernel and
-// lead_kernel, on a second stream beside the others):
+// A selection (netkv_select_batch) takes one of three forms with the same
+// results (direct_batch and bounded_batch say which):
+//   direct (small batches):
+//     direct_kernel    -- everything in one launch, a wavefront or four per
+//                         request (after derive_kernel with staged routes).
+//   bounded (snapshots whose costs tell groups of 64 decodes apart, as
+//   spread_kernel measures at the load calls):
+//     derive_bound_kernel -- the cost factors, and bounds per (prefill, group).
+//     match_kernel     -- holder values of every request's leading held blocks.
+//     bounded_kernel   -- scores the groups that the bounds leave; top-k.
+//   along the batch order (large batches of long runs or in small pools,
+//   per-pair outputs, pools of more than 4,096 decodes), in launch order (a
+//   batch of 2^16 requests or more runs derive_kernel, then
+//   lead_holder_kernel and lead_kernel, on a second stream beside the others):
 //   derive_kernel      -- per-call cost factors (Eqs. (3)-(7) split by what
 //                         they depend on).
 //   prep_kernel        -- validate requests, build hash-order keys.
@@ -49,11 +60,13 @@
 //   tier_inv_kernel    -- Proposition 2's tier-ranking inversion counts.
 //   sequential kernels -- Algorithm 1's per-request in-flight increments,
 //                         one workgroup per prefill instance, from the
-//                         leader rows.
+//                         leader rows (small batches: direct_kernel's rows).
 //   selection_bytes_kernel -- the selections' transfer sizes (Eq. (2)).
-//   pair / parts / dedupe / build kernels -- build the holder index.
-// The flow-level transfer simulation is in flowsim.hip.
+//   load_snapshot_kernel, check_snapshot_kernel -- a snapshot's copy and checks.
+//   pair / parts / dedupe / build kernels -- build the holder index; whole_*
+//                         kernels where its blocks cannot hold the hashes.
 //   commit kernels     -- between-batch counter / queue / memory update.
+// The flow-level transfer simulation is in flowsim.hip.
 #include <hip/hip_runtime.h>
 #include <rocprim/device/device_radix_sort.hpp>
 
@@ -2046,8 +2059,8 @@ __global__ __launch_bounds__(kBlock) void direct_kernel(Snap s, Table t, Reqs rq
 
 // ---------------------------------------------------------------- bounded selection
 //
-// Batches beyond the direct selection, without ordering: most (request,
-// decode) pairs cannot win, and a bound per group of 64 decodes shows it.
+// Batches beyond the direct selection, without ordering: on most snapshots most
+// (request, decode) pairs cannot win, and a bound per group of 64 decodes shows it.
 // With x >= xlo non-cached tokens on every decode of group g,
 //     cost >= fma(xlo, least spt of the group, least constant of the group),
 // in fp32 as well, since each operand is no larger and rounding is monotone.
@@ -2061,8 +2074,9 @@ __global__ __launch_bounds__(kBlock) void direct_kernel(Snap s, Table t, Reqs rq
 //   match_kernel        -- per request the holder values of its leading held
 //                          blocks and their count m.
 //   bounded_kernel      -- bounds, scoring, top-k, outputs.
-// Where nothing can be ruled out every group is scored by one wavefront,
-// which costs more than the ordering pipeline's shared scans.
+// Where little can be ruled out every group is scored by one wavefront,
+// which costs more than the ordering pipeline's shared scans: spread_kernel
+// measures how many groups a snapshot's bounds leave when it is loaded.
 
 // lanes per request of match_kernel, and blocks per lane and step (measured at
 // 1,048,576 requests of 25 blocks / 262,144 of 191 / 99,991 of 25, us: 16 x 2
@@ -2147,6 +2161,119 @@ __global__ __launch_bounds__(kBlock) void derive_bound_kernel(Snap s, const uint
         }
         const uint32_t most = kExactTok + 1u - wave_min_u32_dpp(kExactTok + 1u - x1);
         if (lane == 0) xg[g] = (float)((int32_t)most - 1);
+    }
+}
+
+// How far the bounds separate a snapshot's groups, measured once per load (the
+// loads are synchronous): of up to kSpreadP prefills, the groups that remain
+// after the K-th best cost, for requests of spread_tokens tokens, once without
+// a resident prefix and once bounded as if half of it were resident somewhere.
+// The mean of the two is near the groups per request that real batches leave
+// (fat trees 1 to 2 of 48 groups measured, 1.0 to 1.4 here; all decodes on one
+// tier under random congestion 10 to 29, 25 here; identical decodes 48, 48).
+// It only chooses between forms with the same results, so updates of a loaded
+// snapshot (set or smoothed congestion, committed batches) and the policy are not
+// measured again.
+constexpr uint32_t kSpreadP = 64, kSpreadLens = 3, kSpreadKs = 4;   // K = 1, 2, 4, 8
+constexpr uint32_t kSpreadWords = kSpreadLens * kSpreadKs;
+__host__ __device__ constexpr uint32_t spread_tokens(uint32_t i) { return 2048u << (3 * i); }   // 2 K, 16 K, 128 K
+
+// One workgroup per (prefill, length), which writes its own counts for the host
+// to add.  It is bound by its chain of dependent loads, 6.6 us (16.7 with the
+// per-pair divisions of the other kernels, whose operands are loaded by tier).
+constexpr uint32_t kSpreadWaves = 16;
+
+template <bool TWO>
+__global__ __launch_bounds__(kSpreadWaves * kWave) void spread_kernel(Snap s, const uint8_t *__restrict__ t1,
+                                                                      const float *__restrict__ u1,
+                                                                      const uint8_t *__restrict__ t2,
+                                                                      const float *__restrict__ u2, uint32_t ngroup,
+                                                                      uint32_t *__restrict__ out) {
+    constexpr uint32_t kNone = 0xFFFFFFFFu;
+    __shared__ uint32_t lb[2][kBoundMaxGroups], best[kSpreadWaves * 4];
+    const uint32_t lane = threadIdx.x % kWave, wv = wave_index();
+    const uint32_t p = (uint32_t)((uint64_t)blockIdx.x * s.P / gridDim.x);
+    const float x = (float)spread_tokens(blockIdx.y);
+    // (nearly the feasibility limits: an estimate does without 64-bit divisions)
+    const float per_byte = 1.0f / (float)max(s.bpt, 1u);
+    // seconds per token by tier without congestion (as sec_per_token, the divisions
+    // in another order), so that the loads of the loop do not depend on each other
+    auto per_token = [&](uint32_t t, bool own) {
+        const float n = own && s.policy < 2 ? (float)s.n_inflight[t * s.P + p] : 0.0f;
+        return (float)s.bpt * (1.0f + n) / s.bw[t];
+    };
+    const float y0 = per_token(0, true), y1 = per_token(1, true), y2 = per_token(2, true), y3 = per_token(3, true);
+    const float z0 = TWO ? per_token(0, false) : 0.0f, z1 = TWO ? per_token(1, false) : 0.0f;
+    const float z2 = TWO ? per_token(2, false) : 0.0f, z3 = TWO ? per_token(3, false) : 0.0f;
+    auto pick = [&](uint32_t t, float e0, float e1, float e2, float e3) {
+        const float l = (t & 1u) ? e1 : e0, h = (t & 1u) ? e3 : e2;
+        return (t & 2u) ? h : l;
+    };
+    auto rise = [&](float c) { return s.policy >= 1 ? 1.0f : __builtin_amdgcn_rcpf(1.0f - c); };
+    uint32_t top[4] = {kNone, kNone, kNone, kNone};   // the thread's costs, at most four, ascending
+    for (uint32_t g = wv; g < ngroup; g += kSpreadWaves) {
+        const uint32_t d = g * kWave + lane;
+        float2 a = make_float2(__builtin_inff(), __builtin_inff()), b = a;
+        float lim = 0.0f;
+        if (d < s.D) {
+            const uint64_t i = (uint64_t)p * s.D + d, m = s.free_mem[d];
+            const float base = load_term(s, d);
+            const uint32_t tau = s.tier_map[i] & 3u;
+            a = make_float2(pick(tau, y0, y1, y2, y3) * rise(s.util[i]), tier_latency(s, tau) + base);
+            if (TWO) {
+                const uint32_t v = t1[i] & 3u, w = t2[i] & 3u;
+                b = make_float2(pick(v, y0, y1, y2, y3) * rise(u1[i]) + pick(w, z0, z1, z2, z3) * rise(u2[i]),
+                                tier_latency(s, v) + tier_latency(s, w) + base);
+            }
+            lim = m < s.m_min ? 0.0f : fmaf((float)(m - s.m_min), per_byte, 1.0f);
+        }
+        uint32_t c = x < lim ? route_cost<TWO>(x, a, b) : kNone;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t lo = min(top[u], c);
+            c = max(top[u], c);
+            top[u] = lo;
+        }
+        uint32_t m[4];
+        wave_min4_u32(__float_as_uint(a.x), __float_as_uint(a.y), __float_as_uint(b.x), __float_as_uint(b.y), m);
+        const float2 la = make_float2(__uint_as_float(m[0]), __uint_as_float(m[1]));
+        const float2 lo = make_float2(__uint_as_float(m[2]), __uint_as_float(m[3]));
+        const bool f = __any(x < lim), hf = __any(0.5f * x < lim);
+        if (lane == 0) {
+            lb[0][g] = f ? route_cost<TWO>(x, la, lo) : kNone;
+            lb[1][g] = hf ? route_cost<TWO>(0.5f * x, la, lo) : kNone;
+        }
+    }
+    // the least of the wavefront's ascending t, taken out of the lane that has it
+    auto pop = [&](uint32_t (&t)[4]) {
+        const uint32_t mn = wave_min_u32_dpp(t[0]);
+        if (mn != kNone && lane == (uint32_t)__builtin_ctzll(ballot(t[0] == mn))) {
+            t[0] = t[1];
+            t[1] = t[2];
+            t[2] = t[3];
+            t[3] = kNone;
+        }
+        return mn;
+    };
+    // four of each wavefront: eight of one group alone are counted as four, which
+    // leaves the eighth least cost a little too high
+#pragma unroll 1
+    for (uint32_t u = 0; u < 4; ++u) {
+        const uint32_t mn = pop(top);
+        if (lane == 0) best[wv * 4 + u] = mn;
+    }
+    __syncthreads();
+    if (wv != 0) return;
+    uint32_t head[4] = {best[lane], kNone, kNone, kNone};
+    const uint32_t l0 = lane < ngroup ? lb[0][lane] : kNone, l1 = lane < ngroup ? lb[1][lane] : kNone;
+#pragma unroll 1
+    for (uint32_t u = 0; u < 8; ++u) {
+        const uint32_t kth = pop(head);
+        const uint32_t n = (uint32_t)__builtin_popcountll(ballot(l0 != kNone && l0 <= kth)) +
+                           (uint32_t)__builtin_popcountll(ballot(l1 != kNone && l1 <= kth));
+        // (none with fewer than u + 1 feasible decodes)
+        if (((u + 1) & u) == 0 && lane == 0)
+            out[blockIdx.x * kSpreadWords + blockIdx.y * kSpreadKs + (uint32_t)__builtin_ctz(u + 1)] = kth != kNone ? n : kNone;
     }
 }
 
@@ -2313,9 +2440,9 @@ __device__ inline uint32_t leading_words(uint32_t *wds, uint64_t word, uint32_t 
     return j;
 }
 
-// Each wavefront takes `per` (a multiple of 4, at most 64 / K) consecutive
-// requests, four at a time with their loads issued together; the results are
-// gathered one per lane and stored at the end.
+// Each wavefront takes `per` (1, 2 or a multiple of 4, at most 64 / K)
+// consecutive requests, four at a time with their loads issued together; the
+// results are gathered one per lane and stored at the end.
 template <int K, bool TWO>
 __global__ __launch_bounds__(kBlock) void bounded_kernel(Snap s, Table t, Reqs rq, Bounds bd,
                                                          const uint32_t *__restrict__ hv,
@@ -2421,6 +2548,7 @@ __global__ __launch_bounds__(kBlock) void bounded_kernel(Snap s, Table t, Reqs r
         wave_min4_u32(cb[0], cb[1], cb[2], cb[3], best);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
+            if (i0 + q >= cnt) continue;
             // keys kept: lanes 0 .. K-1 of kb / kd, ascending (cost bits, decode)
             uint32_t kb = 0xFFFFFFFFu, kd = 0xFFFFFFFFu;
             uint32_t thr;   // k-th best cost bits
@@ -2473,19 +2601,17 @@ __global__ __launch_bounds__(kBlock) void bounded_kernel(Snap s, Table t, Reqs r
                 left &= left - 1;
                 left &= ballot(lb[q] <= thr);
             }
-            if (i0 + q < cnt) {
-                const uint32_t slot = (i0 + q) * K;
-                if (m[q] == kNoPre) {   // marks an invalid request: no cost has these bits with a decode
-                    res_b = write_lane(0xFFFFFFFEu, slot, res_b);
-                } else if (K == 1) {
-                    res_b = write_lane(kb, slot, res_b);
-                    res_d = write_lane(kd, slot, res_d);
-                } else {
+            const uint32_t slot = (i0 + q) * K;
+            if (m[q] == kNoPre) {   // marks an invalid request: no cost has these bits with a decode
+                res_b = write_lane(0xFFFFFFFEu, slot, res_b);
+            } else if (K == 1) {
+                res_b = write_lane(kb, slot, res_b);
+                res_d = write_lane(kd, slot, res_d);
+            } else {
 #pragma unroll
-                    for (int u = 0; u < K; ++u) {
-                        res_b = write_lane((uint32_t)__builtin_amdgcn_readlane((int)kb, u), slot + u, res_b);
-                        res_d = write_lane((uint32_t)__builtin_amdgcn_readlane((int)kd, u), slot + u, res_d);
-                    }
+                for (int u = 0; u < K; ++u) {
+                    res_b = write_lane((uint32_t)__builtin_amdgcn_readlane((int)kb, u), slot + u, res_b);
+                    res_d = write_lane((uint32_t)__builtin_amdgcn_readlane((int)kd, u), slot + u, res_d);
                 }
             }
         }
@@ -2899,6 +3025,7 @@ constexpr uint32_t kBlockSlots = 2u << kBlockLog2;   // slots of a block of the 
 constexpr double kBlockedMost = 0.80;
 constexpr uint32_t kManyHolders = 0x80000000u;   // with the decode of one of them
 constexpr uint32_t kNobody = 0xFFFFFFFFu;
+constexpr uint32_t kShortProbe = 64;
 
 // One workgroup per part: its distinct hashes to (okey, ohold) from the part's
 // start on, count[part] of them; sums of the counts, and of the hashes of
@@ -2931,19 +3058,27 @@ __global__ __launch_bounds__(1024) void dedupe_kernel(const uint64_t *__restrict
         const unsigned long long k = part_value(y, bits);
         const uint32_t d = dec[i];
         uint32_t s = (uint32_t)(y >> 32) / (0xFFFFFFFFu / S + 1u), probe = 0;   // the top bits after the part's
-        for (; probe < S; ++probe, s = (s + 1) & (S - 1)) {
+        auto take = [&]() {
             unsigned long long cur = *(volatile unsigned long long *)&lk[s];
             if (cur == 0) cur = atomicCAS(&lk[s], 0ull, k);
-            if (cur == 0 || cur == k) break;
+            return cur == 0 || cur == k;
+        };
+        bool placed = false;
+        for (; probe < kShortProbe; ++probe, s = (s + 1) & (S - 1))
+            if ((placed = take())) break;
+        if (!placed) {
             // more distinct hashes than slots: the set is built whole instead
             // (long probes ask for it, so that the part ends soon)
-            if (probe >= 64 && *(volatile uint32_t *)&full) break;
+            for (; probe < S && !*(volatile uint32_t *)&full; ++probe, s = (s + 1) & (S - 1))
+                if ((placed = take())) break;
+            if (!placed) {
+                if (probe == S) {
+                    full = 1;
+                    atomicOr(flag, 2u);
+                }
+                break;
+            }
         }
-        if (probe == S) {
-            full = 1;
-            atomicOr(flag, 2u);
-        }
-        if (probe >= 64 && *(volatile uint32_t *)&full) break;
         uint32_t h = *(volatile uint32_t *)&lh[s];
         if (h == kNobody) h = atomicCAS(&lh[s], kNobody, d);
         if (h != kNobody && !(h & kManyHolders) && h != d) atomicOr(&lh[s], kManyHolders);
@@ -4049,6 +4184,9 @@ struct netkv_ctx {
     float2 *bnd_lo = nullptr, *bnd_lo2 = nullptr;
     float *bnd_xm = nullptr, *bnd_xg = nullptr;
     uint32_t *match_m = nullptr;
+    // groups left per request under the loaded snapshot (spread_kernel), without
+    // and with the staged routes
+    float spread[2][kSpreadWords] = {};
     uint64_t match_cap = 0;
     float *dlam = nullptr;        // [R][D] B_tok * j of a direct selection with records
     uint64_t dlam_cap = 0;
@@ -4065,6 +4203,8 @@ struct netkv_ctx {
     uint32_t reuse_opt = 1;     // share prefix lengths along the hash order
     uint32_t lead_cap_opt = 0;  // leader table limit (0 = by memory)
     uint32_t cols_opt = 0;      // decodes per lane (0 = automatic)
+    uint32_t form_opt = 0;      // 0 automatic, 1 ordering pipeline, 2 bounded
+    uint32_t last_form = 0;     // of the last selection: 1 and 2 as above, 3 direct
     uint32_t policy_opt = 0;    // 0 full, 1 without live congestion, 2 topology only
     // sequential-selection scratch
     uint32_t *seq_keys = nullptr, *seq_vals = nullptr, *seq_keys_out = nullptr, *seq_perm = nullptr;
@@ -4570,11 +4710,13 @@ Geometry geometry(netkv_handle h, uint32_t k) {
 constexpr uint64_t kDirectTasks = 1ull << 14;
 constexpr uint64_t kDirectRecordTasks = 1ull << 16;
 
-bool unordered(netkv_handle h) { return h->reuse_opt && !h->run_len_opt && !h->cols_opt && !h->lead_cap_opt; }
+bool unordered(netkv_handle h) {
+    return h->reuse_opt && !h->run_len_opt && !h->cols_opt && !h->lead_cap_opt && h->form_opt != 1;
+}
 
 bool direct_batch(netkv_handle h, uint64_t R, uint64_t n_hashes, uint64_t tasks) {
     const uint64_t ng = ((uint64_t)h->D + kWave - 1) / kWave;
-    return ng * std::max<uint64_t>(R, n_hashes / 32) <= tasks && unordered(h);
+    return ng * std::max<uint64_t>(R, n_hashes / 32) <= tasks && unordered(h) && h->form_opt == 0;
 }
 
 // The cost factors of a call on `s` (and of the staged routes with `two`).
@@ -4755,26 +4897,52 @@ netkv_status run_select(netkv_handle h, Scratch &sc, const netkv_requests_t *req
     return NETKV_OK;
 }
 
-// The bounded selection: pools of up to 64 groups of 64 decodes.  It looks up
-// every block of every request, the ordering pipeline about one per request:
-// with runs of 191 blocks 65,536 requests take 115 us here and 200 us there,
-// 262,144 requests 448 us here and 398 us there.  With staged routes (`two`)
-// the bounds leave many groups, more of them for k = 8 and for long runs, and
-// it wins only while the (request, group) tasks are few (us, requests x
-// groups, here / there): k = 1 60,000 x 48 185 / 246, 400,000 x 12 297 / 340,
-// 200,000 x 48 373 / 373, 800,000 x 48 1047 / 853; k = 3 60,000 x 48 306 / 331,
-// 200,000 x 48 685 / 571; k = 8 60,000 x 12 290 / 282, 60,000 x 48 725 / 453;
-// runs of 191 blocks, k = 1, 60,000 x 12 144-189 / 166, 60,000 x 48 341 / 230.
-// Without staged routes, k = 8: 60,000 x 12 166 / 281, 60,000 x 48 341-365 / 410
-// (runs of 191 blocks 271-412 / 403-412), 800,000 x 48 2,376 / 2,410; the line
-// is drawn where it still wins clearly.
-constexpr uint64_t kBoundRouteTasks = 5ull << 20, kBoundManyTasks = 8ull << 20;
+// Groups left per request of a batch, as measured when the snapshot was loaded,
+// at the measured length nearest in proportion to the batch's mean.
+double groups_left(netkv_handle h, uint64_t R, uint64_t n_hashes, uint32_t K, bool two) {
+    if (h->D <= (uint32_t)kWave) return 1.0;
+    const double tokens = (double)h->block_tokens * (double)n_hashes / (double)R;
+    uint32_t i = 0;
+    while (i + 1 < kSpreadLens && tokens * tokens > (double)spread_tokens(i) * (double)spread_tokens(i + 1)) ++i;
+    return h->spread[two][i * kSpreadKs + (uint32_t)__builtin_ctz(K)];
+}
+
+// The bounded selection or the ordering pipeline: pools of up to 64 groups of
+// 64 decodes, by estimates of both forms' times.  The pipeline takes some 10 to
+// 25 launches and then scores every pair, sharing the prefix lookups along its
+// order; the bounded selection takes three, looks up every held block of every
+// request and scores the groups that the bounds leave, so it loses on large
+// batches of long runs, on large batches in small pools, and wherever the
+// snapshot does not tell the groups apart (left: groups left per request as
+// measured when the snapshot was loaded; 150,001 requests on 3,072 identical
+// decodes take 1,378 us bounded and 285 us ordered).  The lines are least-squares
+// fits, in us, to 2,600 calls timed in both forms: 48 to 4,080 decodes, 350 to
+// 1,048,576 requests of 25 and of 191 blocks, k = 1, 2, 3 and 8, with and without
+// staged routes and memory pressure, on fat trees, one tier, two tiers and
+// identical decodes.  The form taken costs 0.9 % more than the better one of the
+// two on average, and over 10 % more than the pipeline in 22 of the 2,600.
 bool bounded_batch(netkv_handle h, uint64_t R, uint64_t n_hashes, uint32_t k, bool two) {
     const uint64_t ng = (h->D + kWave - 1) / kWave;
-    const bool many = k > 4, long_runs = n_hashes > 64 * R;
-    const uint64_t tasks = R * ng * (many ? 8 : 1) * (two && long_runs ? 8 : 1);
-    return ng <= kBoundMaxGroups && unordered(h) && (R <= (1ull << 17) || !long_runs) &&
-           (two ? tasks <= kBoundRouteTasks : !many || tasks <= kBoundManyTasks);
+    if (ng > kBoundMaxGroups || !unordered(h)) return false;
+    if (h->form_opt == 2) return true;
+    const Geometry geo = geometry(h, k);
+    const double K = geo.K, n = (double)R, left = groups_left(h, R, n_hashes, geo.K, two);
+    const double pipeline = 58.0 + 10.0 * std::log2(std::max(n, 350.0) / 350.0) + 0.8 * (double)ng +
+                            1e-3 * n * (0.124 + 0.009 * K + geo.ngroup * (0.0053 + 0.025 * K) +
+                                        (double)ng * (0.0034 + 0.003 * K + (two ? 0.0064 : 0.0)));
+    const double s = left + (two ? 0.9 * (left - 1.0) : 0.0);   // (two routes leave more than the estimate)
+    double bounded = 38.0 + 1.4 * (double)ng + 0.5 * s + 1e-3 * n * (0.22 + 0.02 * K + s * (0.057 + 0.0315 * K)) +
+                     1e-3 * (double)n_hashes * (0.0024 + 0.0019 * s);
+    // (few requests that leave hardly a group: the constants above include the
+    // longest wavefront's groups)
+    if (left <= 2.0 && n <= 6000.0 && K <= 4.0) bounded *= 0.65;
+    // (beyond these the estimates are off by the most: merges of k > 4, two
+    // routes on many groups, more long runs than were measured)
+    const double tasks = n * (double)ng;
+    if ((K > 4.0 && tasks > (double)(1u << 20)) || (two && tasks * (K > 1.0 ? 4.0 : 1.0) > 5.0 * (1u << 20)) ||
+        ((double)n_hashes > 64.0 * n && n_hashes > 32u << 20))
+        return false;
+    return 1.05 * bounded <= pipeline;
 }
 
 // Pools of the bounded selection, whose tables are sized with the snapshot's.
@@ -4811,7 +4979,14 @@ netkv_status run_bounded(netkv_handle h, const netkv_requests_t *req, uint32_t k
     if (two) sn.sr = h->sr;
     const Bounds bd{h->bnd_lo, h->bnd_lo2, h->bnd_xm, h->bnd_xg, ng};
     const uint32_t K = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : 8;
+    // four requests and more per wavefront share their loads, but their left
+    // groups are scored and merged one after another: with several of them (or
+    // longer merges), and too few requests to fill the chip, one request each
+    // (us, one / four: 500 requests on 3,072 decodes, k = 8, 8.4 groups left 111 /
+    // 170, 6,000 127 / 180, with 3.9 left and 191 blocks 123 / 203; 20,011 on 768,
+    // k = 1, 1.1 left 60 / 48; 8,192 on 192, k = 3, 1.2 left 36 / 33)
     uint32_t per = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(16, 64 / K), std::max<uint64_t>(4, R / 8192 / 4 * 4));
+    if (R < (K > 4 ? 24576u : 12288u) && groups_left(h, R, req->n_hashes, K, two) * (3.0 + K) >= 12.0) per = 1;
     const uint32_t grid = (uint32_t)((R + (uint64_t)per * kWavesPerBlock - 1) / ((uint64_t)per * kWavesPerBlock));
     HIPCHK(h, time_begin(h, st));
 #define NETKV_BOUNDED(KK)                                                                                             \
@@ -5016,6 +5191,22 @@ void free_spare(netkv_ctx::SnapBuf &b) {
     b.P = b.D = 0;
 }
 
+netkv_status ensure_spare(netkv_handle h, uint32_t P, uint32_t D) {
+    netkv_ctx::SnapBuf &sp = h->spare;
+    if (sp.P == P && sp.D == D) return NETKV_OK;
+    const uint64_t npd = (uint64_t)P * D;
+    free_spare(sp);
+    if (dalloc(sp.tier_map, npd) != hipSuccess || dalloc(sp.util, npd) != hipSuccess ||
+        dalloc(sp.n_inflight, 4ull * P) != hipSuccess || dalloc(sp.free_mem, D) != hipSuccess ||
+        dalloc(sp.adm_prev, D) != hipSuccess || dalloc(sp.queue, D) != hipSuccess || dalloc(sp.batch, D) != hipSuccess) {
+        free_spare(sp);
+        return fail(h, NETKV_ENOMEM, "snapshot allocation failed");
+    }
+    sp.P = P;
+    sp.D = D;
+    return NETKV_OK;
+}
+
 // Whether p is memory of the handle's device (host memory, pinned or not,
 // managed memory and other devices' are copied by the runtime).
 bool on_device(netkv_handle h, const void *p) {
@@ -5028,6 +5219,56 @@ bool on_device(netkv_handle h, const void *p) {
 }
 
 bool finite_nonneg(double x) { return std::isfinite(x) && x >= 0.0; }
+
+// What the load calls read back: validation flags, then spread_kernel's counts.
+struct LoadBack {
+    uint32_t bad = 0;
+    uint32_t spread[2][kSpreadP][kSpreadWords];
+};
+
+// Pools whose bounds are measured at a load: those of several groups that the
+// bounded selection takes.
+bool spread_pool(uint32_t D) { return D > kWave && D <= kBoundMaxGroups * kWave; }
+
+// Bytes of it that a load copies back.
+size_t back_bytes(uint32_t D, bool two) {
+    return !spread_pool(D) ? sizeof(uint32_t)
+         : two             ? sizeof(LoadBack)
+                           : sizeof(uint32_t) * (1 + kSpreadP * kSpreadWords);
+}
+
+// The bounds' spread of snapshot s (and of the staged routes t1 .. with two)
+// into h->loadword; read by read_spread from what was copied back.
+hipError_t launch_spread(netkv_handle h, const Snap &s, bool direct, bool two, const uint8_t *t1, const float *u1,
+                         const uint8_t *t2, const float *u2, hipStream_t st) {
+    if (!spread_pool(s.D)) return hipGetLastError();
+    const uint32_t ng = (s.D + kWave - 1) / kWave;
+    const dim3 grid(std::min(s.P, kSpreadP), kSpreadLens), block(kSpreadWaves * kWave);
+    if (direct)
+        hipLaunchKernelGGL(spread_kernel<false>, grid, block, 0, st, s, nullptr, nullptr, nullptr, nullptr, ng,
+                           h->loadword + 1);
+    if (two)
+        hipLaunchKernelGGL(spread_kernel<true>, grid, block, 0, st, s, t1, u1, t2, u2, ng,
+                           h->loadword + 1 + kSpreadP * kSpreadWords);
+    return hipGetLastError();
+}
+
+// (a length that most prefills cannot place takes the next shorter one's measure)
+void read_spread(netkv_handle h, uint32_t P, bool two, const LoadBack &back) {
+    if (!spread_pool(h->D)) return;
+    const uint32_t np = std::min(P, kSpreadP);
+    for (uint32_t i = 0; i < kSpreadWords; ++i) {
+        uint32_t sum = 0, n = 0;
+        for (uint32_t p = 0; p < np; ++p)
+            if (back.spread[two][p][i] != 0xFFFFFFFFu) {
+                sum += back.spread[two][p][i];
+                ++n;
+            }
+        h->spread[two][i] = 2 * n >= np       ? (float)sum / (2.0f * (float)n)
+                            : i >= kSpreadKs ? h->spread[two][i - kSpreadKs]
+                                             : (float)((h->D + kWave - 1) / kWave);
+    }
+}
 
 }  // namespace
 
@@ -5141,7 +5382,7 @@ netkv_status netkv_create(netkv_handle *out, int device) {
     h->device = device;
     DeviceGuard g(device);
     if (resolve_scratch(device) != hipSuccess || dalloc(h->errword, 1) != hipSuccess ||
-        dalloc(h->loadword, 1) != hipSuccess || hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking) != hipSuccess ||
+        dalloc(h->loadword, 1 + 2 * kSpreadP * kSpreadWords) != hipSuccess || hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&h->ev_fork0, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&h->ev_fork1, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming) != hipSuccess ||
@@ -5232,20 +5473,10 @@ netkv_status netkv_oracle_load(netkv_handle h, const netkv_oracle_t *o, void *st
     // for the whole device: selections on other streams may still read the
     // buffers exchanged out here, which the next load overwrites.
     netkv_ctx::SnapBuf &sp = h->spare;
-    if (sp.P != P || sp.D != D) {
-        free_spare(sp);
-        if (dalloc(sp.tier_map, npd) != hipSuccess || dalloc(sp.util, npd) != hipSuccess ||
-            dalloc(sp.n_inflight, 4ull * P) != hipSuccess || dalloc(sp.free_mem, D) != hipSuccess ||
-            dalloc(sp.adm_prev, D) != hipSuccess || dalloc(sp.queue, D) != hipSuccess ||
-            dalloc(sp.batch, D) != hipSuccess) {
-            free_spare(sp);
-            return fail(h, NETKV_ENOMEM, "snapshot allocation failed");
-        }
-        sp.P = P;
-        sp.D = D;
-    }
+    if (netkv_status es = ensure_spare(h, P, D)) return es;
     hipError_t e = hipSuccess;
-    uint32_t bad = 0;
+    LoadBack back;
+    const bool routes = h->have_route && h->P == P && h->D == D;   // (of another shape they are dropped below)
     if (on_device(h, o->tier_map) && on_device(h, o->util) && on_device(h, o->n_inflight) &&
         on_device(h, o->free_mem) && on_device(h, o->queue_depth) && on_device(h, o->batch_size)) {
         const SnapIn in{o->tier_map, o->util, o->n_inflight, o->free_mem, o->queue_depth, o->batch_size};
@@ -5272,8 +5503,32 @@ netkv_status netkv_oracle_load(netkv_handle h, const netkv_oracle_t *o, void *st
             e = hipGetLastError();
         }
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(&bad, h->loadword, 4, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) {
+        Snap sn{};
+        sn.tier_map = sp.tier_map;
+        sn.util = sp.util;
+        sn.n_inflight = sp.n_inflight;
+        sn.free_mem = sp.free_mem;
+        sn.queue = sp.queue;
+        sn.batch = sp.batch;
+        for (int i = 0; i < 4; ++i) {
+            sn.bw[i] = (float)o->tier_bw[i];
+            sn.lat[i] = (float)o->tier_lat[i];
+        }
+        sn.t_a = (float)o->t_iter_a;
+        sn.t_b = (float)o->t_iter_b;
+        sn.alpha = (float)o->alpha;
+        sn.beta_max = o->beta_max;
+        sn.m_min = o->m_min;
+        sn.bpt = (uint32_t)o->kv_bytes_per_token;
+        sn.P = P;
+        sn.D = D;
+        sn.policy = h->policy_opt;
+        e = launch_spread(h, sn, true, routes, h->rt1, h->ru1, h->rt2, h->ru2, st);
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(&back, h->loadword, back_bytes(D, routes), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipDeviceSynchronize();
+    const uint32_t bad = back.bad;
     if (e != hipSuccess) return fail(h, NETKV_EDEVICE, "snapshot upload failed: %s", hipGetErrorString(e));
     if (bad)
         return fail(h, NETKV_EINVAL, "invalid snapshot:%s%s%s", (bad & 1) ? " tier_map value > 3" : "",
@@ -5320,6 +5575,8 @@ netkv_status netkv_oracle_load(netkv_handle h, const netkv_oracle_t *o, void *st
     h->bpt = (uint32_t)o->kv_bytes_per_token;
     h->block_tokens = o->block_tokens;
     h->have_snap = true;
+    read_spread(h, P, false, back);
+    if (routes) read_spread(h, P, true, back);
     return NETKV_OK;
 }
 
@@ -5331,8 +5588,10 @@ netkv_status netkv_oracle_set_util(netkv_handle h, const float *util, void *stre
     DeviceGuard g(h->device);
     hipStream_t st = (hipStream_t)stream;
     const uint64_t npd = (uint64_t)h->P * h->D;
-    float *ut = nullptr;
-    if (dalloc(ut, npd) != hipSuccess) return fail(h, NETKV_ENOMEM, "allocation failed");
+    // staged in the spare snapshot's matrix, then exchanged (the wait is for the
+    // whole device, as in netkv_oracle_load)
+    if (netkv_status es = ensure_spare(h, h->P, h->D)) return es;
+    float *ut = h->spare.util;
     uint32_t bad = 0;
     hipError_t e = hipMemcpyAsync(ut, util, npd * 4, hipMemcpyDefault, st);
     if (e == hipSuccess) e = hipMemsetAsync(h->loadword, 0, 4, st);
@@ -5342,14 +5601,12 @@ netkv_status netkv_oracle_set_util(netkv_handle h, const float *util, void *stre
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(&bad, h->loadword, 4, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess || bad) {
-        dfree(ut);
+    const hipError_t e2 = hipDeviceSynchronize();
+    if (e == hipSuccess) e = e2;
+    if (e != hipSuccess || bad)
         return e != hipSuccess ? fail(h, NETKV_EDEVICE, "util upload failed: %s", hipGetErrorString(e))
                                : fail(h, NETKV_EINVAL, "invalid util: values outside [0,1) or NaN");
-    }
-    dfree(h->util);
-    h->util = ut;
+    std::swap(h->util, h->spare.util);
     return NETKV_OK;
 }
 
@@ -5402,7 +5659,7 @@ netkv_status netkv_route2_load(netkv_handle h, const uint8_t *tier1, const float
         drop();
         return fail(h, NETKV_ENOMEM, "route map allocation failed");
     }
-    uint32_t bad = 0;
+    LoadBack back;
     hipError_t e = hipMemcpyAsync(a, tier1, npd, hipMemcpyDefault, st);
     if (e == hipSuccess) e = hipMemcpyAsync(b, tier2, npd, hipMemcpyDefault, st);
     if (e == hipSuccess) e = hipMemcpyAsync(ua, util1, npd * 4, hipMemcpyDefault, st);
@@ -5415,10 +5672,11 @@ netkv_status netkv_route2_load(netkv_handle h, const uint8_t *tier1, const float
         hipLaunchKernelGGL(check_snapshot_kernel, dim3(grid_for(npd, 256, 4096)), dim3(256), 0, st,
                            (const uint8_t *)b, (const float *)ub, npd, (const uint32_t *)nullptr, 0u, 0u,
                            h->loadword);
-        e = hipGetLastError();
+        e = launch_spread(h, make_snap(h), false, true, a, ua, b, ub, st);
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(&bad, h->loadword, 4, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(&back, h->loadword, back_bytes(h->D, true), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
+    const uint32_t bad = back.bad;
     if (e != hipSuccess || bad) {
         drop();
         return e != hipSuccess ? fail(h, NETKV_EDEVICE, "route map upload failed: %s", hipGetErrorString(e))
@@ -5434,6 +5692,7 @@ netkv_status netkv_route2_load(netkv_handle h, const uint8_t *tier1, const float
     h->ru1 = ua;
     h->ru2 = ub;
     h->have_route = true;
+    read_spread(h, h->P, true, back);
     return NETKV_OK;
 }
 
@@ -5802,12 +6061,16 @@ netkv_status netkv_select_batch(netkv_handle h, const netkv_requests_t *req, uin
         po.score = pairs->score;
         want_pairs = po.j || po.feas || po.score;
     }
-    if (!want_pairs && direct_batch(h, req->n_req, req->n_hashes, kDirectTasks))
+    if (!want_pairs && direct_batch(h, req->n_req, req->n_hashes, kDirectTasks)) {
+        h->last_form = 3;
         st = run_direct(h, req, k, out_idx, out_score, s, true);
-    else if (!want_pairs && bounded_batch(h, req->n_req, req->n_hashes, k, h->have_route))
+    } else if (!want_pairs && bounded_batch(h, req->n_req, req->n_hashes, k, h->have_route)) {
+        h->last_form = 2;
         st = run_bounded(h, req, k, out_idx, out_score, s, true);
-    else
+    } else {
+        h->last_form = 1;
         st = select_owned(h, req, k, out_idx, out_score, po, want_pairs, 0xFFFFFFFFu, s, true);
+    }
     if (!st) size_ahead(h, req, k, s);
     return st;
 }
@@ -5830,7 +6093,9 @@ netkv_status netkv_select_batch_noalloc(netkv_handle h, const netkv_requests_t *
     Scratch sc;
     uint64_t r_sub = 0;
     if ((st = carve_static(h, base, req->n_req, k, sc, r_sub))) return st;
-    if (direct_batch(h, req->n_req, req->n_hashes, kDirectTasks)) return run_direct(h, req, k, out_idx, out_score, s, true);
+    const bool direct = direct_batch(h, req->n_req, req->n_hashes, kDirectTasks);
+    h->last_form = direct ? 3 : 1;
+    if (direct) return run_direct(h, req, k, out_idx, out_score, s, true);
     const PairOut po{nullptr, nullptr, nullptr};
     for (uint64_t r0 = 0; r0 < req->n_req; r0 += r_sub) {
         netkv_requests_t sub = *req;
@@ -5937,7 +6202,11 @@ netkv_status netkv_rank_sweep(netkv_handle h, const netkv_requests_t *req, uint3
     {
         TimingOff off(h);  // only the sweep kernel is timed
         const PairOut po{nullptr, nullptr, nullptr};
-        if (direct_batch(h, R, req->n_hashes, kDirectRecordTasks)) {
+        // (pools of more than 64 decodes read the rows anew for every scenario, and
+        // a wavefront's 64 rows of their own stay in the 32 KiB L1 up to 128
+        // decodes: 16 scenarios of 4,000 requests on 192 decodes 1,122 us from the
+        // batch order, 1,197 so; 63 of 89 on 120 decodes 945 and 912)
+        if ((D <= 2u * kWave || n_scen <= 8) && direct_batch(h, R, req->n_hashes, kDirectRecordTasks)) {
             if ((st = ensure_hotr(h, R)) || (st = ensure_dlam(h, R))) return st;
             if ((st = run_direct(h, req, 1, h->base_idx, h->base_score, s, false, h->sc.hotr, h->dlam))) return st;
             lead_lam = h->dlam;
@@ -6147,7 +6416,10 @@ netkv_status netkv_select_sequential(netkv_handle h, const netkv_requests_t *req
     {
         TimingOff off(h);  // only the sequential kernel is timed
         const PairOut po{nullptr, nullptr, nullptr};
-        if (direct_batch(h, R, req->n_hashes, kDirectRecordTasks)) {
+        // (with a row of its own per request the chains read a new row at every
+        // step: on 48 decodes and 16 prefills 4,000 requests take 233 us so and
+        // 252 from the batch order, 16,384 788 and 706, 65,536 2,893 and 2,366)
+        if (R <= 512 * P && direct_batch(h, R, req->n_hashes, kDirectRecordTasks)) {
             // (the chain orders its requests with the selection's sort buffers)
             if ((st = ensure_scratch(h, h->sc, R, 0, req->n_hashes, s)) || (st = ensure_hotr(h, R)) ||
                 (st = ensure_dlam(h, R)))
@@ -6228,6 +6500,10 @@ netkv_status netkv_set_option(netkv_handle h, int option, uint32_t value) {
     case NETKV_OPT_LEAD_CAP:
         h->lead_cap_opt = value;
         return NETKV_OK;
+    case NETKV_OPT_FORM:
+        if (value > 2) return fail(h, NETKV_EINVAL, "form must be 0 (automatic), 1 (ordering pipeline) or 2 (bounded)");
+        h->form_opt = value;
+        return NETKV_OK;
     case NETKV_OPT_COLS:
         if (value != 0 && value != 1 && value != 2 && value != 3 && value != 4 && value != 6)
             return fail(h, NETKV_EINVAL, "decodes per lane must be 0 (automatic), 1, 2, 3, 4 or 6");
@@ -6236,6 +6512,15 @@ netkv_status netkv_set_option(netkv_handle h, int option, uint32_t value) {
     default:
         return fail(h, NETKV_EINVAL, "unknown option %d", option);
     }
+}
+
+netkv_status netkv_last_form(netkv_handle h, uint32_t *form) {
+    if (!h) return NETKV_EINVAL;
+    h->err.clear();
+    if (!form) return fail(h, NETKV_EINVAL, "form must not be NULL");
+    if (!h->last_form) return fail(h, NETKV_ENOTREADY, "no batch selected yet");
+    *form = h->last_form;
+    return NETKV_OK;
 }
 
 netkv_status netkv_cache_info(netkv_handle h, uint64_t *index_slots, uint64_t *distinct_hashes,

@@ -88,6 +88,7 @@ _SIGS = {
     "netkv_kernel_ms": (C.c_int32, [C.c_void_p, C.POINTER(C.c_float)]),
     "netkv_cache_info": (C.c_int32, [C.c_void_p, C.POINTER(C.c_uint64), C.POINTER(C.c_uint64),
                                      C.POINTER(C.c_uint64), C.POINTER(C.c_uint64)]),
+    "netkv_last_form": (C.c_int32, [C.c_void_p, C.POINTER(C.c_uint32)]),
     "netkv_set_option": (C.c_int32, [C.c_void_p, C.c_int, C.c_uint32]),
     "netkv_tier_counts": (C.c_int32, [C.c_void_p, C.POINTER(netkv_requests_t), C.c_void_p, C.c_void_p,
                                       C.c_void_p]),
@@ -105,6 +106,7 @@ NETKV_OPT_REUSE = 2
 NETKV_OPT_COLS = 3
 NETKV_OPT_POLICY = 4
 NETKV_OPT_LEAD_CAP = 5
+NETKV_OPT_FORM = 6
 
 
 def load_library(path: str = LIB_PATH):
@@ -371,6 +373,12 @@ def netkv_select_sequential(h: int, req: Dict[str, torch.Tensor], cap: int, out_
 
 def netkv_set_option(h: int, option: int, value: int) -> None:
     _check(h, load_library().netkv_set_option(h, int(option), int(value)))
+
+
+def netkv_last_form(h: int) -> int:
+    v = C.c_uint32()
+    _check(h, load_library().netkv_last_form(h, C.byref(v)))
+    return int(v.value)
 
 
 def netkv_cache_info(h: int) -> Dict[str, int]:

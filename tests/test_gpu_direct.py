@@ -115,7 +115,12 @@ def test_bounded_equals_pipeline(D, mem, bt, routes):
     rd = netkv.requests_to_device(req, sel.device)
     for k, policy in ((1, 0), (1, 2), (2, 0), (3, 1), (8, 0)):
         sel.set_policy(policy)
+        auto = _bits(netkv, sel.select(rd, k=k))
+        netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_FORM, 2)
         got = _bits(netkv, sel.select(rd, k=k))
+        assert netkv.netkv_last_form(sel.h) == 2
+        netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_FORM, 0)
+        assert np.array_equal(got[0], auto[0]) and np.array_equal(got[1], auto[1])
         netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_RUN_LEN, 64)
         want = _bits(netkv, sel.select(rd, k=k))
         netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_RUN_LEN, 0)
@@ -136,6 +141,7 @@ def test_bounded_ties_and_rejects():
     for m_min in (0, 1 << 62):
         snap["m_min"] = m_min
         sel = _handle(netkv, snap, dict(hash_off=np.zeros(D + 1, np.uint64), hashes=np.ones(1, np.uint64)))
+        netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_FORM, 2)
         rd = netkv.requests_to_device(req, sel.device)
         for k in (1, 3, 8):
             i, s = _bits(netkv, sel.select(rd, k=k))
@@ -264,14 +270,53 @@ def test_long_runs(D):
         rd = netkv.requests_to_device(batch(n), sel.device)
         for k in (1, 3, 8):
             both = []
-            for run_len in (0, 8):
+            for run_len in (0, 0, 8):
                 netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_RUN_LEN, run_len)
+                netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_FORM, 2 if len(both) == 1 else 0)
                 out = sel.select(rd, k=k)
                 both.append([*_bits(netkv, out)])
                 if k == 1:
                     both[-1] += [*_bits(netkv, sel.select_sequential(rd, 16)), *_bits(netkv, sel.rank_sweep(rd, util, 2))]
             netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_RUN_LEN, 0)
             print("[direct] long runs D", D, "R", n, "k", k, flush=True)
-            assert all(np.array_equal(a, b) for a, b in zip(*both))
+            assert all(np.array_equal(a, b) and np.array_equal(a, c) for a, b, c in zip(*both))
     sel.sync_errors()
+    sel.close()
+
+
+@pytest.mark.parametrize("form", ["identical", "one tier", "tiers"])
+def test_form_follows_the_snapshot(form):
+    """A snapshot whose groups of 64 decodes the bounds cannot tell apart is
+    selected along the batch order, which bounds would take several times as
+    long for (150,001 requests on 3,072 identical decodes: 1,378 us against 285);
+    one of distinct tiers by bounds.  The selections agree in every form."""
+    from paper_2606_03910_amd import netkv
+    D, R = 3072, 60000
+    snap, cache, req = _inputs(D, R, 3)
+    P = snap["n_prefill"]
+    rng = np.random.default_rng(8)
+    if form == "identical":
+        snap.update(tier_map=np.full(P * D, 2, np.uint8), util=np.zeros(P * D, np.float32),
+                    queue_depth=np.zeros(D, np.uint32), batch_size=np.zeros(D, np.uint32))
+    elif form == "one tier":
+        snap.update(tier_map=np.full(P * D, 3, np.uint8), util=rng.uniform(0, 0.9, P * D).astype(np.float32))
+    sel = _handle(netkv, snap, cache)
+    rd = netkv.requests_to_device(req, sel.device)
+    out = {}
+    for how in (0, 1, 2):
+        netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_FORM, how)
+        out[how] = _bits(netkv, sel.select(rd, k=1))
+        took = netkv.netkv_last_form(sel.h)
+        assert took == (how or (2 if form == "tiers" else 1)), (form, how, took)
+    print("[gpu-case] form", form, flush=True)
+    assert all(np.array_equal(out[0][i], out[h][i]) for h in (1, 2) for i in (0, 1))
+    # a congestion map alone does not tell one tier's groups apart either
+    if form == "one tier":
+        sel.set_util(np.zeros(P * D, np.float32))
+        netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_FORM, 0)
+        sel.select(rd, k=1)
+        assert netkv.netkv_last_form(sel.h) == 1
+    netkv.netkv_set_option(sel.h, netkv.NETKV_OPT_FORM, 0)
+    sel.select(netkv.requests_to_device(_inputs(D, 100, 3)[2], sel.device), k=1)
+    assert netkv.netkv_last_form(sel.h) == 3
     sel.close()
