@@ -4916,11 +4916,11 @@ double groups_left(netkv_handle h, uint64_t R, uint64_t n_hashes, uint32_t K, bo
 // snapshot does not tell the groups apart (left: groups left per request as
 // measured when the snapshot was loaded; 150,001 requests on 3,072 identical
 // decodes take 1,378 us bounded and 285 us ordered).  The lines are least-squares
-// fits, in us, to 2,600 calls timed in both forms: 48 to 4,080 decodes, 350 to
+// fits, in us, to 2,608 calls timed in both forms: 48 to 4,080 decodes, 350 to
 // 1,048,576 requests of 25 and of 191 blocks, k = 1, 2, 3 and 8, with and without
 // staged routes and memory pressure, on fat trees, one tier, two tiers and
-// identical decodes.  The form taken costs 0.9 % more than the better one of the
-// two on average, and over 10 % more than the pipeline in 22 of the 2,600.
+// identical decodes.  The form taken costs 1.6 % more than the better one of the
+// two on average, and over 10 % more than the pipeline in 18 of them.
 bool bounded_batch(netkv_handle h, uint64_t R, uint64_t n_hashes, uint32_t k, bool two) {
     const uint64_t ng = (h->D + kWave - 1) / kWave;
     if (ng > kBoundMaxGroups || !unordered(h)) return false;

@@ -65,11 +65,11 @@ def test_noalloc_selection_replays_from_a_graph(nk):
 @pytest.mark.parametrize("n", [300, 100000])
 def test_forms_share_their_buffers(nk, n, how):
     """One plain selection, or a reservation (whatever options are set then),
-    sizes the work buffers for every form of a batch of its size: per-pair outputs, staged routes, the ordering pipeline and the
-    bounds of another snapshot of the same decodes (with more prefills) are
-    captured afterwards, where nothing can be allocated, and their replays equal
-    another handle's eager results.  300 requests are selected directly,
-    100,000 by bounds."""
+    sizes the work buffers for every form of a batch of its size: per-pair
+    outputs, staged routes, the ordering pipeline and the bounds of another
+    snapshot of the same decodes (with more prefills) are captured afterwards,
+    where nothing can be allocated, and their replays equal another handle's
+    eager results.  300 requests are selected directly, 100,000 by bounds."""
     print("[gpu-case] forms after one", how, n, flush=True)
     cfg = W.scaled(W.CONFIGS["c0"], n_requests=n, cluster=W.Cluster(8, 4, 4, 2))
     D = cfg.n_decode
