@@ -4982,11 +4982,14 @@ netkv_status run_bounded(netkv_handle h, const netkv_requests_t *req, uint32_t k
     // four requests and more per wavefront share their loads, but their left
     // groups are scored and merged one after another: with several of them (or
     // longer merges), and too few requests to fill the chip, one request each
-    // (us, one / four: 500 requests on 3,072 decodes, k = 8, 8.4 groups left 111 /
-    // 170, 6,000 127 / 180, with 3.9 left and 191 blocks 123 / 203; 20,011 on 768,
-    // k = 1, 1.1 left 60 / 48; 8,192 on 192, k = 3, 1.2 left 36 / 33)
+    // (us, one / four: 500 requests on 3,072 decodes, k = 8, 12 groups left 103 /
+    // 160, 8,192 130 / 185, 16,000 172 / 250; 20,011 on 768, k = 1, 1.1 left 60 /
+    // 48; 8,192 on 192, k = 3, 1.2 left 36 / 33; k = 8, 2 left on 78 decodes, 6,000
+    // 34 / 36, 11,000 41 / 39, 24,000 66 / 55; 5.4 left on 768 16,000 86 / 92,
+    // 24,000 111 / 105)
     uint32_t per = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(16, 64 / K), std::max<uint64_t>(4, R / 8192 / 4 * 4));
-    if (R < (K > 4 ? 24576u : 12288u) && groups_left(h, R, req->n_hashes, K, two) * (3.0 + K) >= 12.0) per = 1;
+    const double merges = groups_left(h, R, req->n_hashes, K, two) * (3.0 + K);
+    if (merges >= 12.0 && (double)R < (K > 4 ? std::min(20480.0, 360.0 * merges) : 12288.0)) per = 1;
     const uint32_t grid = (uint32_t)((R + (uint64_t)per * kWavesPerBlock - 1) / ((uint64_t)per * kWavesPerBlock));
     HIPCHK(h, time_begin(h, st));
 #define NETKV_BOUNDED(KK)                                                                                             \
